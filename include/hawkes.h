@@ -305,7 +305,7 @@ hawkes_status hawkes_mlp_train_step(float *d_params, float *d_adam_m, float *d_a
  * allocate device memory (code under HIP graph capture, tight serving or
  * training loops, harnesses that forbid allocation).  Same arguments and
  * results except that the workspace and the FP64 gradient are not passed: they
- * live in a fixed device array of the library, about 4.3 MB per GPU, taken once
+ * live in a fixed device array of the library, about 5.2 MB per GPU, taken once
  * per device on the first call there and held until the process ends.  The
  * call allocates nothing and calls no allocating routine.
  *   B  at most hawkes_mlp_noalloc_max_batch() (4096); a larger batch returns

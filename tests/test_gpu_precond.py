@@ -257,3 +257,40 @@ def test_learned_preconditioner_gain(gpu):
     assert loss1 < 0.2 * loss0
     assert loss1 < 0.8 * var
     assert err_learned < err_identity
+
+
+@pytest.mark.parametrize("B", [1, 15, 33, 257, 8192 + 45])
+def test_mlp_batch_edges_match_oracle(gpu, B):
+    """Batches that end inside a 16- or 32-sample group, and one beyond the
+    largest number of blocks (each block then takes several groups): forward,
+    gradient and loss.  FP32 chains of at most 64 products: 64 * 2^-24 = 4e-6
+    relative on a value, and on the gradient 1e-4 of its entry or a thousandth
+    of its largest one, as above."""
+    import torch
+
+    from paper_2103_03348_amd import _lib
+
+    L = _lib.lib()
+    rng = np.random.default_rng(100 + B)
+    p = (omlp.init(seed=3) + 0.1 * rng.standard_normal(omlp.N_PARAMS)).astype(np.float32)
+    X = rng.standard_normal((B, 12)).astype(np.float32)
+    T = rng.standard_normal(B).astype(np.float32)
+    # the parameters at an odd 4-byte offset: the kernel assumes no wider alignment
+    store = torch.zeros(omlp.N_PARAMS + 1, dtype=torch.float32, device="cuda:0")
+    dp = store[1:]
+    dp.copy_(_t(p))
+    dX, dT = _t(X), _t(T)
+    y = torch.empty(B, dtype=torch.float32, device="cuda:0")
+    _lib.check(L.hawkes_mlp_forward(_lib.ptr(dp), _lib.ptr(dX), B, _lib.ptr(y), _lib.stream_handle()), "fwd")
+    yref, _ = omlp.forward(p.astype(np.float64), X.astype(np.float64))
+    np.testing.assert_allclose(y.cpu().numpy(), yref, rtol=1e-5, atol=1e-5)
+    work = torch.empty(int(L.hawkes_mlp_workspace_floats(B)), dtype=torch.float32, device="cuda:0")
+    grad = torch.empty(omlp.N_PARAMS, dtype=torch.float64, device="cuda:0")
+    loss = torch.empty(1, dtype=torch.float64, device="cuda:0")
+    _lib.check(L.hawkes_mlp_grad(_lib.ptr(dp), _lib.ptr(dX), B, None, _lib.ptr(dT), B, _lib.ptr(work),
+                                 _lib.ptr(grad), _lib.ptr(loss), None, _lib.stream_handle()), "grad")
+    lref, gref = omlp.loss_and_grad(p.astype(np.float64), X.astype(np.float64), T.astype(np.float64))
+    torch.cuda.synchronize()
+    assert loss.item() == pytest.approx(lref, rel=1e-5)
+    scale = np.abs(gref) + 1e-3 * np.abs(gref).max()
+    assert np.max(np.abs(grad.cpu().numpy() - gref) / scale) < 1e-4
