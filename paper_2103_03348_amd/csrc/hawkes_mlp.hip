@@ -91,7 +91,7 @@ __global__ __launch_bounds__(MLP_THREADS) void k_mlp_batch(const float *__restri
                                                            double *__restrict__ loss_part, int *__restrict__ err) {
     struct Lds {
         float h1[MLP_BS][MLP_LDH];
-        float ysum[MLP_BS / 16][4][16];
+        double ysum[MLP_BS / 16][4][16];
         float d1[GRAD ? MLP_BS : 1][MLP_LDH];
         float d2[GRAD ? MLP_BS : 1][MLP_LDH];
         float x[GRAD ? MLP_BS : 1][16];  // columns 12..15 stay zero
@@ -155,24 +155,24 @@ __global__ __launch_bounds__(MLP_THREADS) void k_mlp_batch(const float *__restri
 #pragma unroll
         for (int t = 0; t < 16; ++t) a = __builtin_amdgcn_mfma_f32_16x16x4f32(w2[t], bop[t], a, 0, 0, 0);
         mlp_f4 h2;
-        float yp = 0.0f;
+        double yp = 0.0;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             h2[r] = tanhf(a[r]);
-            yp = fmaf(w3[r], h2[r], yp);
+            yp = fma((double)w3[r], (double)h2[r], yp);
         }
         // output: the lane groups' and wavefronts' partial sums
         yp += __shfl_xor(yp, 16);
         yp += __shfl_xor(yp, 32);
         if (q == 0) L.ysum[sg][ng][c] = yp;
         __syncthreads();
-        const float y = ((L.ysum[sg][0][c] + L.ysum[sg][1][c]) + L.ysum[sg][2][c]) + L.ysum[sg][3][c] + b3;
+        const double y = ((L.ysum[sg][0][c] + L.ysum[sg][1][c]) + L.ysum[sg][2][c]) + L.ysum[sg][3][c] + (double)b3;
         if (!GRAD) {
-            if (live && ng == 0 && q == 0) y_out[s] = y;
+            if (live && ng == 0 && q == 0) y_out[s] = (float)y;
             continue;  // the next group's writes of h1 follow this group's ysum barrier
         }
         // back-propagation: dy = 2 (y - t) / B, d2 = dy w3 (1 - h2^2), d1 = (W2^T d2) (1 - h1^2)
-        const float r = ok ? y - tgt : 0.0f;
+        const float r = ok ? (float)(y - (double)tgt) : 0.0f;
         const float dy = 2.0f * r / (float)B;
         if (ng == 0 && q == 0) {
             r2 += (double)r * (double)r;
