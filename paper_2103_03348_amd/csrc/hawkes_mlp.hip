@@ -154,6 +154,8 @@ __global__ __launch_bounds__(MLP_THREADS) void k_mlp_batch(const float *__restri
         a = mlp_f4{b2[0], b2[1], b2[2], b2[3]};
 #pragma unroll
         for (int t = 0; t < 16; ++t) a = __builtin_amdgcn_mfma_f32_16x16x4f32(w2[t], bop[t], a, 0, 0, 0);
+        // the output is summed in FP64: an FP32 sum's error is most of what separates
+        // the gradient (a sum of residuals that nearly cancel) from its FP64 value
         mlp_f4 h2;
         double yp = 0.0;
 #pragma unroll
@@ -315,17 +317,38 @@ __global__ __launch_bounds__(MLP_APPLY_WAVES * HK_WAVE) void k_mlp_apply(const d
 
 // ---- features -------------------------------------------------------------------------------
 // Disc and time-window counts around each free event, exact by their
-// definition: a spatial grid of cells of size 3h over all events (counting
-// sort: per-cell counts, one exclusive scan, a scatter of the events' times
-// and coordinates into cell order) gives each free event the candidates in the
-// cells that a disc of radius 3h (the largest radius) around it touches;
-// the candidates are then tested exactly.  Distances are dx * dx + dy * dy and
-// radii r * r, each rounded once in FP64 (no contraction), so every count is
-// the same integer as the definition's.
+// definition: a counting sort of all events by grid cell gives each free event
+// the candidates near it, and what decides a count is the FP64 distance and
+// time of each candidate.  Distances are dx * dx + dy * dy and radii r * r, each
+// rounded once in FP64 (no contraction), so every count is the same integer as
+// the definition's.
+//
+// The sort takes the events in time order in `nb` runs of `per` events, and
+// keeps every cell's events in the order of the runs: off[b (cells + 1) + c] is
+// the first of cell c's events from runs >= b.  A free event's time windows
+// (-1/omega .. 6/omega: a few of hundreds of 1/omega) then meet only the cell's
+// events of two or three runs, and the two counts over all times need a
+// distance alone.  Cells are h wide where at most kFeatCells of them cover the
+// events (else 2 h or 3 h, else 3 h and one run): a cell inside the 3h disc is
+// counted whole, so only the cells that a circle crosses are tested.
+//
+// N = 100,000, 6,874 free events: cells of 3h whose every event was tested for
+// all nine sums, in two passes, took 257 us (bound by L2: 3 GB of candidates)
+// after 123 us of counting sort by global atomics (contended in the clusters);
+// this form 79 us after 27 (sums of 440 and 110 us per
+// prediction with the network).
 struct FeatGrid {
-    double gx0, gy0, s;  // origin and cell size 3h
+    double gx0, gy0, s;  // origin and cell size
     int nx, ny;
+    int nb, per;         // runs of the time-ordered events, events per run
 };
+
+constexpr int kFeatCells = 8192;  // cells of a run's histogram in LDS (32 KB)
+constexpr int kFeatRuns = 64;     // one lane per run in k_features
+constexpr int kFeatGroup = 256;   // cells per block of the offsets kernel
+constexpr int kFeatThreads = 1024;
+constexpr int kFeatTests = 4;     // candidates a lane of k_features loads together
+constexpr int kFeatBatch = 4;     // events a thread of the sort loads together
 
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return min(max(v, lo), hi); }
 
@@ -335,7 +358,114 @@ __device__ __forceinline__ int cell_x(double x, const FeatGrid &G) {
 __device__ __forceinline__ int cell_y(double y, const FeatGrid &G) {
     return clampi((int)floor((y - G.gy0) / G.s), 0, G.ny - 1);
 }
+__device__ __forceinline__ int64_t cell_of(const double *__restrict__ xy, int64_t e, const FeatGrid &G) {
+    return (int64_t)cell_y(xy[2 * e + 1], G) * G.nx + cell_x(xy[2 * e], G);
+}
 
+// Per run (one block): its events per cell, and their sums over kFeatGroup cells.
+__global__ __launch_bounds__(kFeatThreads) void k_cell_hist(const double *__restrict__ xy, const int *__restrict__ perm,
+                                                           int64_t n, const FeatGrid G, int *__restrict__ off,
+                                                           int *__restrict__ gsum) {
+    __shared__ int cnt[kFeatCells];
+    const int cells = G.nx * G.ny, b = blockIdx.x;
+    for (int c = threadIdx.x; c < kFeatCells; c += kFeatThreads) cnt[c] = 0;
+    const int64_t i1 = min(n, (int64_t)(b + 1) * G.per);
+    for (int64_t i0 = (int64_t)b * G.per; i0 < i1; i0 += kFeatBatch * kFeatThreads) {
+        int cell[kFeatBatch];
+#pragma unroll
+        for (int k = 0; k < kFeatBatch; ++k) {
+            const int64_t i = i0 + k * kFeatThreads + threadIdx.x;
+            cell[k] = i < i1 ? (int)cell_of(xy, perm[i], G) : -1;
+        }
+        if (i0 == (int64_t)b * G.per) __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kFeatBatch; ++k)
+            if (cell[k] >= 0) atomicAdd(&cnt[cell[k]], 1);
+    }
+    __syncthreads();
+    for (int c = threadIdx.x; c < cells; c += kFeatThreads) off[(int64_t)b * (cells + 1) + c] = cnt[c];
+    const int l = threadIdx.x % 32, g = threadIdx.x / 32;
+    int v = 0;
+#pragma unroll
+    for (int k = 0; k < kFeatGroup / 32; ++k) v += cnt[g * kFeatGroup + 32 * k + l];
+    for (int o = 16; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    if (l == 0) gsum[b * (kFeatCells / kFeatGroup) + g] = v;
+}
+
+// Counts to offsets in place: a block has kFeatGroup cells; the events of the
+// groups before it come from the runs' sums.
+__global__ __launch_bounds__(kFeatGroup) void k_cell_off(const int *__restrict__ gsum, int64_t n, const FeatGrid G,
+                                                         int *__restrict__ off) {
+    __shared__ int sh[kFeatGroup];
+    const int cells = G.nx * G.ny, c = blockIdx.x * kFeatGroup + threadIdx.x;
+    constexpr int groups = kFeatCells / kFeatGroup;
+    int v = 0;
+    for (int k = threadIdx.x; k < G.nb * groups; k += kFeatGroup)
+        if (k % groups < (int)blockIdx.x) v += gsum[k];
+    sh[threadIdx.x] = v;
+    __syncthreads();
+    for (int h = kFeatGroup / 2; h > 0; h >>= 1) {
+        if (threadIdx.x < h) sh[threadIdx.x] += sh[threadIdx.x + h];
+        __syncthreads();
+    }
+    const int base = sh[0];
+    __syncthreads();
+    // the cell's counts of every run, loaded together
+    int cnt[kFeatRuns], tot = 0;
+#pragma unroll
+    for (int b = 0; b < kFeatRuns; ++b) cnt[b] = b < G.nb && c < cells ? off[(int64_t)b * (cells + 1) + c] : 0;
+#pragma unroll
+    for (int b = 0; b < kFeatRuns; ++b) tot += cnt[b];
+    sh[threadIdx.x] = tot;
+    __syncthreads();
+    for (int h = 1; h < kFeatGroup; h <<= 1) {
+        const int o = threadIdx.x >= h ? sh[threadIdx.x - h] : 0;
+        __syncthreads();
+        sh[threadIdx.x] += o;
+        __syncthreads();
+    }
+    int run = base + sh[threadIdx.x] - tot;
+#pragma unroll
+    for (int b = 0; b < kFeatRuns; ++b) {
+        if (b < G.nb && c < cells) off[(int64_t)b * (cells + 1) + c] = run;
+        run += cnt[b];
+    }
+    if (c == 0) off[cells] = (int)n;  // end of the last cell
+}
+
+// Per run: its events to their places (the order inside a cell and run does not
+// matter: counts are integers and feature 8 is summed in fixed point).
+__global__ __launch_bounds__(kFeatThreads) void k_cell_place(const double *__restrict__ t, const double *__restrict__ xy,
+                                                            const int *__restrict__ perm, int64_t n, const FeatGrid G,
+                                                            const int *__restrict__ off, double *__restrict__ ct,
+                                                            double2 *__restrict__ cxy) {
+    __shared__ int next[kFeatCells];
+    const int cells = G.nx * G.ny, b = blockIdx.x;
+    for (int c = threadIdx.x; c < cells; c += kFeatThreads) next[c] = off[(int64_t)b * (cells + 1) + c];
+    const int64_t i1 = min(n, (int64_t)(b + 1) * G.per);
+    for (int64_t i0 = (int64_t)b * G.per; i0 < i1; i0 += kFeatBatch * kFeatThreads) {
+        double x[kFeatBatch], y[kFeatBatch], tt[kFeatBatch];
+#pragma unroll
+        for (int k = 0; k < kFeatBatch; ++k) {
+            const int64_t i = i0 + k * kFeatThreads + threadIdx.x;
+            const int64_t e = i < i1 ? perm[i] : 0;
+            x[k] = xy[2 * e];
+            y[k] = xy[2 * e + 1];
+            tt[k] = t[e];
+        }
+        if (i0 == (int64_t)b * G.per) __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kFeatBatch; ++k) {
+            if (i0 + k * kFeatThreads + threadIdx.x >= i1) break;
+            const int q = atomicAdd(&next[cell_y(y[k], G) * G.nx + cell_x(x[k], G)], 1);
+            ct[q] = tt[k];
+            cxy[q] = make_double2(x[k], y[k]);
+        }
+    }
+}
+
+// The same sort with one run for grids too large for LDS (a wide domain over
+// small cells: few events share one), by global atomics.
 __global__ void k_fill_zero(int *__restrict__ a, int64_t n) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         a[i] = 0;
@@ -344,7 +474,7 @@ __global__ void k_fill_zero(int *__restrict__ a, int64_t n) {
 __global__ void k_cell_count(const double *__restrict__ xy, int64_t n, const FeatGrid G, int *__restrict__ cnt) {
     const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (e >= n) return;
-    atomicAdd(&cnt[(int64_t)cell_y(xy[2 * e + 1], G) * G.nx + cell_x(xy[2 * e], G)], 1);
+    atomicAdd(&cnt[cell_of(xy, e, G)], 1);
 }
 
 // Exclusive scan of the cell counts by one block: each thread scans a
@@ -379,23 +509,26 @@ __global__ __launch_bounds__(kScanThreads) void k_cell_scan(const int *__restric
     }
 }
 
-// Events into cell order (the order inside a cell does not matter for counts).
 __global__ void k_cell_scatter(const double *__restrict__ t, const double *__restrict__ xy, int64_t n,
                                const FeatGrid G, const int *__restrict__ start, int *__restrict__ fill,
-                               double *__restrict__ ct, double *__restrict__ cx, double *__restrict__ cy) {
+                               double *__restrict__ ct, double2 *__restrict__ cxy) {
     const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (e >= n) return;
-    const double x = xy[2 * e], y = xy[2 * e + 1];
-    const int64_t c = (int64_t)cell_y(y, G) * G.nx + cell_x(x, G);
+    const int64_t c = cell_of(xy, e, G);
     const int64_t q = start[c] + atomicAdd(&fill[c], 1);
     ct[q] = t[e];
-    cx[q] = x;
-    cy[q] = y;
+    cxy[q] = make_double2(xy[2 * e], xy[2 * e + 1]);
 }
 
-// One wavefront per free event: the lanes split the candidates of the cells a
-// disc of radius 3h touches, count, and the counts are summed across the
-// wavefront (integers: exact in any order).
+// One wavefront per free event; its lanes take the grid rows of the 3h disc
+// side by side (8 or 16 lanes a row), so that the rows' loads are in flight
+// together.  The counts are summed across the wavefront (integers: exact in any
+// order).
+//
+// A cell counts as inside the 3h disc, or as out of reach of a disc, with a
+// margin of 1e-6 cells, far above the rounding of its edges (positions relative
+// to the grid's origin are within 2^26 2^-53 cells); whatever is nearer is
+// tested.  The runs a time window meets are found with a margin in the same way.
 //
 // Feature 8 is the forward sum of the squared excitation kernel,
 //   S_m = sum over e with r2_e < (3h)^2, 0 < dt_e <= 6/omega of
@@ -409,10 +542,10 @@ __global__ void k_cell_scatter(const double *__restrict__ t, const double *__res
 __global__ __launch_bounds__(256) void k_features(const double *__restrict__ t, const double *__restrict__ xy,
                                                   const int64_t *__restrict__ cidx, const int *__restrict__ pos,
                                                   const int *__restrict__ slot, const int *__restrict__ g,
-                                                  const double *__restrict__ z, int64_t m, int64_t n, double t0,
-                                                  double t1, double h, double tau_x, double omega, const FeatGrid G,
-                                                  const int *__restrict__ start, const double *__restrict__ ct,
-                                                  const double *__restrict__ cx, const double *__restrict__ cy,
+                                                  const double *__restrict__ ts, const double *__restrict__ z,
+                                                  int64_t m, int64_t n, double t0, double t1, double h, double omega,
+                                                  const FeatGrid G, const int *__restrict__ off,
+                                                  const double *__restrict__ ct, const double2 *__restrict__ cxy,
                                                   float *__restrict__ feat) {
 #pragma clang fp contract(off)
     const int lane = threadIdx.x & (HK_WAVE - 1);
@@ -424,74 +557,166 @@ __global__ __launch_bounds__(256) void k_features(const double *__restrict__ t, 
     const double r0 = h * h, h3 = 3.0 * h, r1 = h3 * h3;
     const double w1 = 1.0 / omega, w3 = 3.0 / omega, w6 = 6.0 / omega;
     const double inv_h2 = 1.0 / (h * h);
-    const int x_lo = cell_x(xm - h3, G), x_hi = cell_x(xm + h3, G);
-    const int y_lo = cell_y(ym - h3, G), y_hi = cell_y(ym + h3, G);
-    int c[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-    double amax = -INFINITY;  // largest exponent of feature 8's terms
-    for (int yy = y_lo; yy <= y_hi; ++yy) {
-        const int64_t row = (int64_t)yy * G.nx;
-        for (int q = start[row + x_lo] + lane; q < start[row + x_hi + 1]; q += HK_WAVE) {
-            const double dx = cx[q] - xm, dy = cy[q] - ym;
-            const double d2 = dx * dx + dy * dy;
-            const double dt = ct[q] - tm;
-            const bool prev = dt >= -w1 && dt < 0.0, next = dt > 0.0 && dt <= w1, next3 = dt > 0.0 && dt <= w3;
-            if (d2 < r1) {
-                c[1] += 1;
-                c[6] += prev;
-                c[7] += next;
-                if (dt > 0.0 && dt <= w6) {
-                    c[2] += 1;
-                    amax = fmax(amax, -2.0 * omega * dt - d2 * inv_h2);
-                }
-                if (d2 < r0) {
-                    c[0] += 1;
-                    c[3] += prev;
-                    c[4] += next;
-                    c[5] += next3;
+    // the runs that hold events of the time windows: the last one that starts
+    // before the earliest window, up to the last that starts inside the latest
+    int b_lo = 0, b_hi = 0;
+    if (G.nb > 1) {
+        const double slack = 1e-9 * w6 + 1e-15 * fabs(tm);
+        const bool in = lane < G.nb && (int64_t)lane * G.per < n;
+        const double tb = in ? ts[(int64_t)lane * G.per] : INFINITY;
+        b_lo = max(0, (int)__popcll(__ballot(tb < tm - w1 - slack)) - 1);
+        b_hi = max(b_lo, (int)__popcll(__ballot(tb <= tm + w6 + slack)) - 1);
+    }
+    const int64_t stride = (int64_t)G.nx * G.ny + 1;
+    const int *__restrict__ w_lo = off + b_lo * stride;
+    // (past the last run a cell ends where the next begins)
+    const int *__restrict__ w_hi = b_hi + 1 < G.nb ? off + (b_hi + 1) * stride : off + 1;
+    // positions in cells relative to the grid's origin
+    const double inv_s = 1.0 / G.s, um = (xm - G.gx0) * inv_s, vm = (ym - G.gy0) * inv_s;
+    const double R0 = h * inv_s, R1 = h3 * inv_s, tol = 1e-6;
+    const int y_lo = clampi((int)floor(vm - R1 - tol), 0, G.ny - 1), y_hi = clampi((int)floor(vm + R1 + tol), 0, G.ny - 1);
+    // at most 8 rows and columns (6 h over cells of at least h)
+    const int lpr = y_hi - y_lo < 4 ? 16 : 8;
+    const int lr = lane % lpr, yy = y_lo + lane / lpr;
+    const int64_t row = (int64_t)yy * G.nx;
+    const bool live = yy <= y_hi;
+
+    int c[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    int xa = 0, xb = -1;  // the columns the 3h disc reaches in the lane's row
+    int wq = 0, wn = 0;   // first event and number of events in the time windows' runs, of column xa + lr
+    if (live) {
+        // least and largest distance in y to the row's cells
+        const double below = (double)yy - vm, above = (double)(yy + 1) - vm;
+        const double dn = fmax(0.0, fmax(below, -above)), df = fmax(fabs(below), fabs(above));
+        // the 3h disc: cells it reaches, cells inside it
+        const double wo = sqrt(fmax(0.0, R1 * R1 - dn * dn)) + tol;
+        xa = clampi((int)floor(um - wo), 0, G.nx - 1);
+        xb = clampi((int)floor(um + wo), 0, G.nx - 1);
+        if (lr <= xb - xa) {
+            wq = w_lo[row + xa + lr];
+            wn = w_hi[row + xa + lr] - wq;
+        }
+        const double wi = sqrt(fmax(0.0, R1 * R1 - df * df)) - tol;
+        const int xi = max(xa, (int)floor(um - wi) + 1), xj = min(xb, (int)floor(um + wi) - 1);
+        const int qa = off[row + xa], qb = off[row + xb + 1];
+        int qi = qb, qj = qb;  // [qa, qi) and [qj, qb) are tested, [qi, qj) counted whole
+        if (wi > 0.0 && xi <= xj) {
+            qi = off[row + xi];
+            qj = off[row + xj + 1];
+            if (lr == 0) c[1] += qj - qi;
+        }
+        const int left = qi - qa, tests = left + (qb - qj);
+        for (int s = lr; s < tests; s += kFeatTests * lpr) {
+            double2 p[kFeatTests];
+#pragma unroll
+            for (int u = 0; u < kFeatTests; ++u) {
+                const int su = min(s + u * lpr, tests - 1);
+                p[u] = cxy[su < left ? qa + su : qj + (su - left)];
+            }
+#pragma unroll
+            for (int u = 0; u < kFeatTests; ++u) {
+                const double dx = p[u].x - xm, dy = p[u].y - ym;
+                c[1] += dx * dx + dy * dy < r1 && s + u * lpr < tests;
+            }
+        }
+        // the h disc over all times
+        if (dn <= R0 + tol) {
+            const double wh = sqrt(fmax(0.0, R0 * R0 - dn * dn)) + tol;
+            const int ha = clampi((int)floor(um - wh), 0, G.nx - 1), hb = clampi((int)floor(um + wh), 0, G.nx - 1);
+            const int q1 = off[row + hb + 1];
+            for (int q = off[row + ha] + lr; q < q1; q += kFeatTests * lpr) {
+                double2 p[kFeatTests];
+#pragma unroll
+                for (int u = 0; u < kFeatTests; ++u) p[u] = cxy[min(q + u * lpr, q1 - 1)];
+#pragma unroll
+                for (int u = 0; u < kFeatTests; ++u) {
+                    const double dx = p[u].x - xm, dy = p[u].y - ym;
+                    c[0] += dx * dx + dy * dy < r0 && q + u * lpr < q1;
                 }
             }
         }
     }
+    // the time windows: one candidate, and its exponent in feature 8 (-inf: no term)
+    const auto window = [&](int q) {
+        const double2 p = cxy[q];
+        const double dx = p.x - xm, dy = p.y - ym;
+        const double d2 = dx * dx + dy * dy;
+        const double dt = ct[q] - tm;
+        const bool prev = dt >= -w1 && dt < 0.0, next = dt > 0.0 && dt <= w1, next3 = dt > 0.0 && dt <= w3;
+        if (!(d2 < r1)) return -(double)INFINITY;
+        c[6] += prev;
+        c[7] += next;
+        if (d2 < r0) {
+            c[3] += prev;
+            c[4] += next;
+            c[5] += next3;
+        }
+        if (!(dt > 0.0 && dt <= w6)) return -(double)INFINITY;
+        c[2] += 1;
+        return -2.0 * omega * dt - d2 * inv_h2;
+    };
+    // each column's first lpr candidates are loaded together, one per lane (nearly
+    // always all of them); their exponents are kept
+    double ae[8], amax = -INFINITY;  // largest exponent of feature 8's terms
+    int cq[8], cn[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        cq[i] = __shfl(wq, lane - lr + i);
+        cn[i] = __shfl(wn, lane - lr + i);
+        ae[i] = lr < cn[i] ? window(cq[i] + lr) : -INFINITY;
+        amax = fmax(amax, ae[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+        for (int s = lr + lpr; s < cn[i]; s += lpr) amax = fmax(amax, window(cq[i] + s));
 #pragma unroll
     for (int a = 0; a < 8; ++a) {
 #pragma unroll
-        for (int off = 1; off < HK_WAVE; off <<= 1) c[a] += __shfl_xor(c[a], off);
+        for (int o = 1; o < HK_WAVE; o <<= 1) c[a] += __shfl_xor(c[a], o);
     }
 #pragma unroll
-    for (int off = 1; off < HK_WAVE; off <<= 1) amax = fmax(amax, __shfl_xor(amax, off));
+    for (int o = 1; o < HK_WAVE; o <<= 1) amax = fmax(amax, __shfl_xor(amax, o));
     // feature 8's terms relative to the largest, in fixed point (2^36 units)
     long long ksum = 0;
     if (amax > -INFINITY) {
-        for (int yy = y_lo; yy <= y_hi; ++yy) {
-            const int64_t row = (int64_t)yy * G.nx;
-            for (int q = start[row + x_lo] + lane; q < start[row + x_hi + 1]; q += HK_WAVE) {
-                const double dx = cx[q] - xm, dy = cy[q] - ym;
+        const auto term = [&](double a) {  // a <= amax
+            return llrint((double)exp2f((float)((a - amax) * 1.4426950408889634)) * 68719476736.0);
+        };
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            if (ae[i] > -INFINITY) ksum += term(ae[i]);
+            for (int s = lr + lpr; s < cn[i]; s += lpr) {
+                const int q = cq[i] + s;
+                const double2 p = cxy[q];
+                const double dx = p.x - xm, dy = p.y - ym;
                 const double d2 = dx * dx + dy * dy;
                 const double dt = ct[q] - tm;
-                if (d2 < r1 && dt > 0.0 && dt <= w6) {
-                    const double rel = (-2.0 * omega * dt - d2 * inv_h2) - amax;  // <= 0
-                    ksum += llrint((double)exp2f((float)(rel * 1.4426950408889634)) * 68719476736.0);
-                }
+                if (d2 < r1 && dt > 0.0 && dt <= w6) ksum += term(-2.0 * omega * dt - d2 * inv_h2);
             }
         }
 #pragma unroll
-        for (int off = 1; off < HK_WAVE; off <<= 1) ksum += __shfl_xor(ksum, off);
+        for (int o = 1; o < HK_WAVE; o <<= 1) ksum += __shfl_xor(ksum, o);
     }
-    if (lane == 0) {
-        float f[MLP_IN];
-        // the event itself is inside every disc
-        for (int a = 0; a < 2; ++a) f[a] = (float)log1p((double)(c[a] - 1));
-        f[2] = (float)log1p((double)c[2]);
-        for (int a = 3; a < 8; ++a) f[a] = (float)log1p((double)c[a]);
+    // lane a forms feature a (the event itself is inside every disc)
+    if (lane >= MLP_IN) return;
+    int cnt = lane < 2 ? c[0] - 1 : c[2];
+    if (lane == 1) cnt = c[1] - 1;
+#pragma unroll
+    for (int a = 3; a < 8; ++a)
+        if (lane == a) cnt = c[a];
+    float f = (float)log1p((double)cnt);
+    if (lane == 8) {
         // log2 S_m = log2(ksum) - 36 + a_max / ln 2 (S_m = 0: the floor)
         const double l2s = ksum > 0 ? log2((double)ksum) - 36.0 + amax * 1.4426950408889634 : -INFINITY;
-        f[8] = (float)(fmax(l2s, HK_KSUM_LOG2_FLOOR) * 0.125);
-        f[9] = (float)z[k];
-        f[10] = (float)((double)g[pos[r]] / (double)n);
-        const double span = t1 - t0;
-        f[11] = (float)(span > 0.0 ? (t1 - tm) / span : 0.0);
-        for (int j = 0; j < MLP_IN; ++j) feat[(int64_t)k * MLP_IN + j] = f[j];
+        f = (float)(fmax(l2s, HK_KSUM_LOG2_FLOOR) * 0.125);
     }
+    if (lane == 9) f = (float)z[k];
+    if (lane == 10) f = (float)((double)g[pos[r]] / (double)n);
+    if (lane == 11) {
+        const double span = t1 - t0;
+        f = (float)(span > 0.0 ? (t1 - tm) / span : 0.0);
+    }
+    feat[(int64_t)k * MLP_IN + lane] = f;
 }
 
 // ---- curvature and mass update ---------------------------------------------------------
@@ -658,31 +883,50 @@ extern "C" hawkes_status hawkes_features(hawkes_plan p, const hawkes_hyper *hy, 
     FeatGrid G;
     G.gx0 = gx0;
     G.gy0 = gy0;
-    G.s = 3.0 * hy->h;
-    const double nx = floor((p->xmax - gx0) / G.s) + 1.0, ny = floor((p->ymax - gy0) / G.s) + 1.0;
-    if (!(nx * ny < (double)(1 << 26))) return HAWKES_E_UNSUPPORTED;
-    G.nx = (int)nx;
-    G.ny = (int)ny;
-    const int64_t cells = (int64_t)G.nx * G.ny, n = p->n;
-    // int workspace: counts [cells], starts [cells + 1], fill [cells]; then
-    // (8-byte aligned) the events' times and coordinates in cell order [3 n]
-    const int64_t ints = ((3 * cells + 1 + 1) / 2) * 2;
+    const auto fits = [&](double size, double most) {
+        G.s = size;
+        const double nx = floor((p->xmax - gx0) / G.s) + 1.0, ny = floor((p->ymax - gy0) / G.s) + 1.0;
+        if (!(nx * ny <= most)) return false;
+        G.nx = (int)nx;
+        G.ny = (int)ny;
+        return true;
+    };
+    if (!fits(3.0 * hy->h, (double)((1 << 26) - 1))) return HAWKES_E_UNSUPPORTED;
+    const bool lds = fits(hy->h, kFeatCells) || fits(2.0 * hy->h, kFeatCells) || fits(3.0 * hy->h, kFeatCells);
+    const int64_t n = p->n, cells = (int64_t)G.nx * G.ny;
+    // runs of at least 256 events
+    G.nb = lds ? (int)std::min<int64_t>(kFeatRuns, (n + 255) / 256) : 1;
+    G.per = (int)((n + G.nb - 1) / G.nb);
+    // int workspace: offsets [nb][cells + 1], then the runs' group sums, or one
+    // run's counts and fill marks; then (16-byte aligned) the events' coordinates
+    // and times in cell order [3 n]
+    const int64_t offs = G.nb * (cells + 1);
+    const int64_t ints = (offs + (lds ? (int64_t)G.nb * (kFeatCells / kFeatGroup) : 2 * cells) + 3) / 4 * 4;
     hawkes_status st = hk_subset_grid(p, ints + 6 * n, stream);
     if (st != HAWKES_OK) return st;
-    int *cnt = hk_subset_grid_ptr(p), *start = cnt + cells, *fill = start + cells + 1;
-    double *ct = (double *)(cnt + ints), *cxs = ct + n, *cys = cxs + n;
-    hipLaunchKernelGGL(k_fill_zero, dim3(std::min<int64_t>(nblk(cells, 256), 4096)), dim3(256), 0, stream, cnt,
-                       cells);
-    hipLaunchKernelGGL(k_cell_count, dim3(nblk(n, 256)), dim3(256), 0, stream, d_xy, n, G, cnt);
-    hipLaunchKernelGGL(k_cell_scan, dim3(1), dim3(kScanThreads), 0, stream, cnt, cells, start, fill);
-    hipLaunchKernelGGL(k_cell_scatter, dim3(nblk(n, 256)), dim3(256), 0, stream, d_t, d_xy, n, G, start, fill, ct,
-                       cxs, cys);
+    int *off = hk_subset_grid_ptr(p), *rest = off + offs;
+    double2 *cxy = (double2 *)(off + ints);
+    double *ct = (double *)(cxy + n);
+    if (lds) {
+        hipLaunchKernelGGL(k_cell_hist, dim3(G.nb), dim3(kFeatThreads), 0, stream, d_xy, p->perm, n, G, off, rest);
+        hipLaunchKernelGGL(k_cell_off, dim3(nblk(cells, kFeatGroup)), dim3(kFeatGroup), 0, stream, rest, n, G, off);
+        hipLaunchKernelGGL(k_cell_place, dim3(G.nb), dim3(kFeatThreads), 0, stream, d_t, d_xy, p->perm, n, G, off, ct,
+                           cxy);
+    } else {
+        int *cnt = rest, *fill = rest + cells;
+        hipLaunchKernelGGL(k_fill_zero, dim3(std::min<int64_t>(nblk(cells, 256), 4096)), dim3(256), 0, stream, cnt,
+                           cells);
+        hipLaunchKernelGGL(k_cell_count, dim3(nblk(n, 256)), dim3(256), 0, stream, d_xy, n, G, cnt);
+        hipLaunchKernelGGL(k_cell_scan, dim3(1), dim3(kScanThreads), 0, stream, cnt, cells, off, fill);
+        hipLaunchKernelGGL(k_cell_scatter, dim3(nblk(n, 256)), dim3(256), 0, stream, d_t, d_xy, n, G, off, fill, ct,
+                           cxy);
+    }
     int64_t m;
     const int64_t *cidx;
     const int *pos, *slot;
     hk_subset_view(p, &m, &cidx, &pos, &slot);
     hipLaunchKernelGGL(k_features, dim3(nblk(m * HK_WAVE, 256)), dim3(256), 0, stream, d_t, d_xy, cidx, pos, slot,
-                       p->g, d_z, m, n, p->t0, p->t1, hy->h, hy->tau_x, hy->omega, G, start, ct, cxs, cys, d_feat);
+                       p->g, p->ts, d_z, m, n, p->t0, p->t1, hy->h, hy->omega, G, off, ct, cxy, d_feat);
     HK_CHECK(hipGetLastError());
     return HAWKES_OK;
 }

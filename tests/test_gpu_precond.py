@@ -294,3 +294,29 @@ def test_mlp_batch_edges_match_oracle(gpu, B):
     assert loss.item() == pytest.approx(lref, rel=1e-5)
     scale = np.abs(gref) + 1e-3 * np.abs(gref).max()
     assert np.max(np.abs(grad.cpu().numpy() - gref) / scale) < 1e-4
+
+
+@pytest.mark.parametrize("n,h", [(40, 0.3), (1500, 3.0), (1500, 0.3), (1500, 0.2), (1500, 0.13), (1500, 0.05),
+                                 (17000, 0.6)])
+def test_features_over_cell_sizes_match_oracle(gpu, n, h):
+    """One run or several of the time-ordered events, cells of h, 2h and 3h, and
+    the grid too large for LDS; tied times and repeated locations among the
+    events.  Counts are integers: their log1p agrees to FP32 rounding."""
+    import torch
+
+    from paper_2103_03348_amd import _lib
+
+    es = synth.small(n, seed=n, ties=n // 10, dup_xy=n // 10, all_free=False)
+    es.hyper = es.hyper[:5] + (h,)
+    plan = _plan_with_subset(es)
+    sub = es.subset[:200]
+    z = np.log(es.theta[es.subset])
+    gx0, gy0 = float(es.x.min()) - 1e-9, float(es.y.min()) - 1e-9
+    feat = torch.empty((es.subset.shape[0], 12), dtype=torch.float32, device="cuda:0")
+    hy = _lib.Hyper.of(es.hyper)
+    dt, dxy, dz = _t(es.t), _t(np.stack([es.x, es.y], 1)), _t(z)
+    _lib.check(_lib.lib().hawkes_features(plan.handle, ctypes.byref(hy), _lib.ptr(dt), _lib.ptr(dxy), _lib.ptr(dz),
+                                          gx0, gy0, _lib.ptr(feat), _lib.stream_handle()), "features")
+    torch.cuda.synchronize()
+    ref = ofeat.features(es.t, es.x, es.y, sub, z[:200], es.hyper, es.t0, gx0, gy0)
+    np.testing.assert_allclose(feat.cpu().numpy()[:200], ref, rtol=1e-6, atol=1e-6)
