@@ -110,8 +110,8 @@ __device__ __forceinline__ void two_sum_acc(float &hi, float &lo, float v) {
 }
 
 // ------------------------------------------------------------------------------------
-// Per evaluation, before the row pass: the sorted FP32 rates (gathered from the
-// caller's order when FROM_CALLER, else already in theta_s), and for the split
+// Per evaluation, before the row pass: the sorted FP32 rates (0 where `member`
+// marks a sorted event whose excitation is left out), and for the split
 // excitation time factor the staged rate of each event,
 // theta_v_j = theta_j exp(omega (t_j - T_c)) with T_c its chunk's first time,
 // plus a flag per chunk that spans more than `span_max` in time (those chunks
@@ -119,8 +119,8 @@ __device__ __forceinline__ void two_sum_acc(float &hi, float &lo, float v) {
 // tstep_c = exp(-omega (T_{c+1} - T_c)) (0 for the last chunk), with which the
 // pair passes carry a row's or column's own split factor from one chunk to the
 // next instead of evaluating it anew.  One wavefront per chunk.
-template <bool FROM_CALLER>
 __global__ __launch_bounds__(256) void k_tfac(const double *__restrict__ theta, const int *__restrict__ perm,
+                                              const unsigned char *__restrict__ member,
                                               const double *__restrict__ ts, int64_t n, double omega,
                                               double span_max, float *__restrict__ theta_s,
                                               float *__restrict__ theta_v, int *__restrict__ chunk_precise,
@@ -128,15 +128,12 @@ __global__ __launch_bounds__(256) void k_tfac(const double *__restrict__ theta, 
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;  // grid covers npad exactly
     const int lane = threadIdx.x & (HK_WAVE - 1);
     double th = 0.0;
-    if (FROM_CALLER) {
-        if (i < n) {
-            th = theta[perm[i]];
-            if (!(th >= 0.0) || !isfinite(th)) atomicOr(status, HK_ST_BADTHETA);
-        }
-        theta_s[i] = (float)th;
-    } else {
-        th = (double)theta_s[i];
+    if (i < n) {
+        th = theta[perm[i]];
+        if (!(th >= 0.0) || !isfinite(th)) atomicOr(status, HK_ST_BADTHETA);
+        if (member && member[i]) th = 0.0;
     }
+    theta_s[i] = (float)th;
     const double dti = ts[i] - ts[i - lane];
     const bool precise = __any(i < n && dti > span_max);
     theta_v[i] = (!precise && th > 0.0) ? (float)(th * exp(omega * dti)) : (float)th;
@@ -1178,8 +1175,8 @@ extern "C" hawkes_status hawkes_eval(hawkes_plan p, const hawkes_hyper *hyper, c
     const int64_t npad = p->npad;
 
     hk_prof_mark(p, HK_PROF_EVAL, true, stream);
-    hipLaunchKernelGGL(k_tfac<true>, dim3((unsigned)(npad / 256)), dim3(256), 0, stream, d_theta, p->perm, p->ts,
-                       p->n, kc.omega, kc.span_max, p->theta_s, p->theta_v, p->chunk_precise, p->tstep, p->status);
+    hipLaunchKernelGGL(k_tfac, dim3((unsigned)(npad / 256)), dim3(256), 0, stream, d_theta, p->perm,
+                       (const unsigned char *)nullptr, p->ts, p->n, kc.omega, kc.span_max, p->theta_s, p->theta_v, p->chunk_precise, p->tstep, p->status);
     hk_prof_mark(p, HK_PROF_ROW, true, stream);
 #define HK_ROW(M)                                                                                              \
     hipLaunchKernelGGL(k_row<M>, dim3(p->n_row_blocks), dim3(HK_TILE), 0, stream, p->ts, p->xs, p->ys,          \
@@ -1214,9 +1211,9 @@ extern "C" hawkes_status hawkes_eval(hawkes_plan p, const hawkes_hyper *hyper, c
     return HAWKES_OK;
 }
 
-void hk_launch_row_loglik(hawkes_plan p, const PairConst &kc, hipStream_t stream) {
-    hipLaunchKernelGGL(k_tfac<false>, dim3((unsigned)(p->npad / 256)), dim3(256), 0, stream, (const double *)nullptr,
-                       p->perm, p->ts, p->n, kc.omega, kc.span_max, p->theta_s, p->theta_v, p->chunk_precise, p->tstep, p->status);
+void hk_launch_row_loglik(hawkes_plan p, const PairConst &kc, const double *d_theta, const unsigned char *member,
+                          hipStream_t stream) {
+    hipLaunchKernelGGL(k_tfac, dim3((unsigned)(p->npad / 256)), dim3(256), 0, stream, d_theta, p->perm, member, p->ts, p->n, kc.omega, kc.span_max, p->theta_s, p->theta_v, p->chunk_precise, p->tstep, p->status);
     hipLaunchKernelGGL(k_row<HK_MODE_LOGLIK>, dim3(p->n_row_blocks), dim3(HK_TILE), 0, stream, p->ts, p->xs, p->ys,
                        p->theta_v, p->chunk_precise, p->tstep, p->g, p->row_items, p->row_block0, p->colpart_off, p->rowpart,
                        p->colpart, kc);

@@ -13,6 +13,7 @@
 //
 // Kernels:
 //   k_sub_static   partial sums of the static row pass -> lambda_static_i
+//   k_sum_blocks   its integral term
 //   k_sub_offset   temporal-trend offsets beta t_k (Sec. 2.2)
 //   k_sub_theta    theta_k = exp(z_k + beta t_k) into the caller's theta, and the
 //                  subset entries staged in time order for the subset passes
@@ -39,6 +40,7 @@ struct hk_subset {
     int *pos;            // [mpad] sorted position of subset entry r (time order); pad = INT_MAX
     int *slot;           // [mpad] caller's subset slot k of entry r
     int64_t *cidx;       // [m] caller index of slot k (copy of the caller's idx)
+    unsigned char *member;  // [npad] 1 where the sorted event is in the subset
     // row pass schedule: (row chunk, range of subset entries before its end)
     int n_ritems;
     hk_item *ritems;     // (row chunk, entry begin, entry end, seg)
@@ -169,104 +171,103 @@ __global__ void k_sub_layout(const double *__restrict__ key, const int *__restri
 }
 
 // ---- static part ---------------------------------------------------------------------
-// theta with the subset entries zeroed, sorted, FP32
-__global__ void k_sub_static_theta(const double *__restrict__ theta, const int *__restrict__ perm,
-                                   const int *__restrict__ pos, int64_t m, int64_t n, int64_t npad,
-                                   float *__restrict__ theta_s, int *__restrict__ status) {
-    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i < npad) {
-        float v = 0.0f;
-        if (i < n) {
-            double th = theta[perm[i]];
-            if (!(th >= 0.0) || !isfinite(th)) atomicOr(status, HK_ST_BADTHETA);
-            v = (float)th;
-        }
-        theta_s[i] = v;
-    }
-}
-
-__global__ void k_sub_zero_subset(const int *__restrict__ pos, int64_t m, float *__restrict__ theta_s) {
+__global__ void k_sub_member(const int *__restrict__ pos, int64_t m, unsigned char *__restrict__ member) {
     int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (r < m) theta_s[pos[r]] = 0.0f;
+    if (r < m) member[pos[r]] = 1;
 }
 
-// lambda_static_i from the row pass partials (log-likelihood mode: B0, X0) and
-// the integral term of everything that does not depend on the subset rates.
-__global__ __launch_bounds__(256) void k_sub_static(const double *__restrict__ ts, const double *__restrict__ xs,
-                                                    const double *__restrict__ ys, const int *__restrict__ g,
-                                                    const double *__restrict__ theta,
-                                                    const int *__restrict__ perm, const float *__restrict__ theta_s,
-                                                    int64_t n, int ntiles, const int *__restrict__ row_item0,
-                                                    const int *__restrict__ row_nseg,
-                                                    const float *__restrict__ rowpart,
-                                                    const float *__restrict__ colpart,
-                                                    const int64_t *__restrict__ colpart_off, const FinConst fc,
-                                                    double *__restrict__ lam_static, double *__restrict__ blockpart) {
-    __shared__ double sh[HK_WAVES];
-    __shared__ double red[HK_WAVES][2];
-    __shared__ uint64_t low_mask[HK_WAVES];
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+__global__ void k_sub_clear(unsigned char *__restrict__ member, int64_t npad) {
+    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (i < npad) member[i] = 0;
+}
+
+// lambda_static_i from the row pass partials (log-likelihood mode: B0, X0), the
+// integral term of everything that does not depend on the subset rates, and
+// a_r = theta0 (1 - exp(-omega (T1 - t_r))) of the subset entries.  One block
+// per 64-event chunk; its wavefronts split the chunk's row pieces and column
+// partials, as in the evaluation's row finalisation (one thread per event,
+// summing its 10 to 370 pieces one after the other, took 43 us at N = 23,422
+// and 743 us at 250,000; this form 7 and 130 us).
+constexpr int SUB_STATIC_WAVES = 8;
+__global__ __launch_bounds__(SUB_STATIC_WAVES * HK_WAVE) void k_sub_static(
+    const double *__restrict__ ts, const double *__restrict__ xs, const double *__restrict__ ys,
+    const int *__restrict__ g, const double *__restrict__ theta, const int *__restrict__ perm,
+    const float *__restrict__ theta_s, int64_t n, int ntiles, const int *__restrict__ row_item0,
+    const int *__restrict__ row_nseg, const float *__restrict__ rowpart, const float *__restrict__ colpart,
+    const FinConst fc, const int *__restrict__ pos, int64_t m, int64_t mpad, double *__restrict__ a_sub,
+    double *__restrict__ lam_static, double *__restrict__ blockpart) {
+    __shared__ double part[SUB_STATIC_WAVES][2][HK_WAVE];
+    __shared__ double red[SUB_STATIC_WAVES][2];
     const int lane = threadIdx.x & (HK_WAVE - 1), wq = threadIdx.x / HK_WAVE;
-    double lam_part = 0.0;
-    double ls = 1.0;
-    if (i < n) {
-        const int I = (int)(i / HK_TILE), r = (int)(i % HK_TILE);
-        // the log-likelihood-only row pass: B0 (row and column partials) and X0
+    const int64_t i = (int64_t)blockIdx.x * HK_WAVE + lane;
+    const int64_t ra = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;  // the grid covers mpad (mpad <= npad)
+    if (ra < mpad) a_sub[ra] = ra < m ? fc.theta0 * -expm1(-fc.omega * (fc.t1 - ts[pos[ra]])) : 0.0;
+    {
+        const int I = (int)(i / HK_TILE), r = (int)(i % HK_TILE), it0 = row_item0[I], ns = row_nseg[I];
         double b0 = 0.0, x0 = 0.0;
-        for (int sg = 0; sg < row_nseg[I]; ++sg) {
-            const float *rp = rowpart + (int64_t)(row_item0[I] + sg) * HK_NROW * HK_TILE + r;
+#pragma unroll 4
+        for (int sg = wq; sg < ns; sg += SUB_STATIC_WAVES) {
+            const float *rp = rowpart + (int64_t)(it0 + sg) * HK_NROW * HK_TILE + r;
             b0 += rp[0];
             x0 += rp[5 * HK_TILE];
         }
-        for (int J = I; J < ntiles; ++J) b0 += (double)colpart[colpart_off[J] + i];
-        ls = fc.c_b * b0 * fc.corr + fc.c_e * x0 * fc.corr;
+#pragma unroll 4
+        for (int J = I + wq; J < ntiles; J += SUB_STATIC_WAVES)
+            b0 += (double)colpart[(int64_t)HK_NCOL * HK_TILE * J * (J + 1) / 2 + i];
+        part[wq][0][lane] = b0;
+        part[wq][1][lane] = x0;
     }
+    __syncthreads();
+    double b0 = part[0][0][lane], x0 = part[0][1][lane];
+    for (int q = 1; q < SUB_STATIC_WAVES; ++q) {
+        b0 += part[q][0][lane];
+        x0 += part[q][1][lane];
+    }
+    double ls = i < n ? fc.c_b * b0 * fc.corr + fc.c_e * x0 * fc.corr : 1.0;
     // rows whose static intensity is below fc.lam_exact (the FP32 pair terms may
     // have lost more than 2^-30 of it) are recomputed from the definitions in
     // FP64 by the whole block, one row at a time: background over every j != i,
-    // excitation from the earlier fixed-rate events (theta_s is zero on the subset)
-    const uint64_t mine = __ballot(i < n && ls < fc.lam_exact);
-    if (lane == 0) low_mask[wq] = mine;
-    __syncthreads();
-    for (int w = 0; w < HK_WAVES; ++w) {
-        for (uint64_t mk = low_mask[w]; mk != 0; mk &= mk - 1) {
-            const int rr = __ffsll((unsigned long long)mk) - 1;
-            const int64_t ir = blockIdx.x * (int64_t)blockDim.x + w * HK_WAVE + rr;
-            const double xi = xs[ir], yi = ys[ir], tsi = ts[ir];
-            const int gi = g[ir];
-            const double kb = 0.5 / (fc.tau_x * fc.tau_x), kt = 0.5 / (fc.tau_t * fc.tau_t);
-            const double kh = 0.5 / (fc.h * fc.h);
-            double B0 = 0.0, X0 = 0.0;
-            for (int64_t j = threadIdx.x; j < n; j += blockDim.x) {
-                if (j == ir) continue;
-                const double dx = xi - xs[j], dy = yi - ys[j];
-                const double r2 = dx * dx + dy * dy;
-                const double dt = tsi - ts[j];
-                B0 += exp(-(r2 * kb) - dt * dt * kt);
-                if (j < gi && theta_s[j] != 0.0f) X0 += theta[perm[j]] * exp(-fc.omega * dt - r2 * kh);
-            }
-            for (int off = 32; off > 0; off >>= 1) {
-                B0 += __shfl_xor(B0, off);
-                X0 += __shfl_xor(X0, off);
-            }
-            if (lane == 0) {
-                red[wq][0] = B0;
-                red[wq][1] = X0;
-            }
-            __syncthreads();
-            if (threadIdx.x == w * HK_WAVE + rr) {
-                double b = red[0][0], x = red[0][1];
-                for (int q = 1; q < HK_WAVES; ++q) {
-                    b += red[q][0];
-                    x += red[q][1];
-                }
-                ls = fc.c_b * b + fc.c_e * x;
-            }
-            __syncthreads();
+    // excitation from the earlier fixed-rate events (theta_s is zero on the
+    // subset); every wavefront derives the same mask
+    for (uint64_t mk = __ballot(i < n && ls < fc.lam_exact); mk != 0; mk &= mk - 1) {
+        const int rr = __ffsll((unsigned long long)mk) - 1;
+        const int64_t ir = (int64_t)blockIdx.x * HK_WAVE + rr;
+        const double xi = xs[ir], yi = ys[ir], tsi = ts[ir];
+        const int gi = g[ir];
+        const double kb = 0.5 / (fc.tau_x * fc.tau_x), kt = 0.5 / (fc.tau_t * fc.tau_t);
+        const double kh = 0.5 / (fc.h * fc.h);
+        double B0 = 0.0, X0 = 0.0;
+        for (int64_t j = threadIdx.x; j < n; j += SUB_STATIC_WAVES * HK_WAVE) {
+            if (j == ir) continue;
+            const double dx = xi - xs[j], dy = yi - ys[j];
+            const double r2 = dx * dx + dy * dy;
+            const double dt = tsi - ts[j];
+            B0 += exp(-(r2 * kb) - dt * dt * kt);
+            if (j < gi && theta_s[j] != 0.0f) X0 += theta[perm[j]] * exp(-fc.omega * dt - r2 * kh);
         }
+        for (int off = 32; off > 0; off >>= 1) {
+            B0 += __shfl_xor(B0, off);
+            X0 += __shfl_xor(X0, off);
+        }
+        if (lane == 0) {
+            red[wq][0] = B0;
+            red[wq][1] = X0;
+        }
+        __syncthreads();
+        if (lane == rr) {
+            double b = red[0][0], x = red[0][1];
+            for (int q = 1; q < SUB_STATIC_WAVES; ++q) {
+                b += red[q][0];
+                x += red[q][1];
+            }
+            ls = fc.c_b * b + fc.c_e * x;
+        }
+        __syncthreads();
     }
+    if (wq != 0) return;
+    lam_static[i] = ls;
+    double lam_part = 0.0;
     if (i < n) {
-        lam_static[i] = ls;
         // integral term: background (all events) + excitation of the fixed-rate events
         const double ti = ts[i];
         const double u1 = (fc.t1 - ti) / fc.tau_t, u0 = (fc.t0 - ti) / fc.tau_t;
@@ -274,34 +275,29 @@ __global__ __launch_bounds__(256) void k_sub_static(const double *__restrict__ t
         const double one_m = -expm1(-fc.omega * (fc.t1 - ti));
         const double th_fixed = theta_s[i] == 0.0f ? 0.0 : theta[perm[i]];  // subset entries are zeroed
         lam_part = fc.mu0 * Cn + fc.theta0 * th_fixed * one_m;
-    } else if (i < (int64_t)ntiles * HK_TILE) {
-        lam_static[i] = 1.0;
     }
-    // fixed-order block sum
+    // fixed-order sum
     for (int off = 32; off > 0; off >>= 1) lam_part += __shfl_xor(lam_part, off);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = lam_part;
-    __syncthreads();
-    if (threadIdx.x == 0) blockpart[blockIdx.x] = ((sh[0] + sh[1]) + sh[2]) + sh[3];
+    if (lane == 0) blockpart[blockIdx.x] = lam_part;
 }
 
-__global__ void k_sum_blocks(const double *__restrict__ part, int nb, double *__restrict__ out) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        double s = 0.0, c = 0.0;
-        for (int b = 0; b < nb; ++b) {
-            const double v = part[b];
-            const double t = s + v;
-            c += fabs(s) >= fabs(v) ? (s - t) + v : (v - t) + s;
-            s = t;
-        }
-        out[0] = s + c;
+// One wavefront: the chunks' sums, each lane's share by a Neumaier sum, then a
+// butterfly that carries the corrections (fixed order).
+__global__ __launch_bounds__(HK_WAVE) void k_sum_blocks(const double *__restrict__ part, int nb, double *__restrict__ out) {
+    double s = 0.0, c = 0.0;
+    const auto add = [&](double v) {
+        const double t = s + v;
+        c += fabs(s) >= fabs(v) ? (s - t) + v : (v - t) + s;
+        s = t;
+    };
+#pragma unroll 8
+    for (int b = threadIdx.x; b < nb; b += HK_WAVE) add(part[b]);
+    for (int off = 32; off > 0; off >>= 1) {
+        const double s2 = __shfl_xor(s, off), c2 = __shfl_xor(c, off);
+        add(s2);
+        c += c2;
     }
-}
-
-__global__ void k_sub_a(const double *__restrict__ ts, const int *__restrict__ pos, int64_t m, int64_t mpad,
-                        const FinConst fc, double *__restrict__ a) {
-    int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (r >= mpad) return;
-    a[r] = r < m ? fc.theta0 * -expm1(-fc.omega * (fc.t1 - ts[pos[r]])) : 0.0;
+    if (threadIdx.x == 0) out[0] = s + c;
 }
 
 // ---- per-evaluation kernels ---------------------------------------------------------------
@@ -318,16 +314,17 @@ __global__ void k_sub_offset(const double *__restrict__ ts, const int *__restric
     if (r < m) off[slot[r]] = beta * ts[pos[r]];
 }
 
-// theta_k = exp(z_k) into the caller's full rate vector, and the staged subset
-// entries of this evaluation in time order: pre-scaled coordinates, times, the
-// rate with the split time factor of its 64-entry chunk, the chunk's split flag
-// and step factor.  One wavefront per chunk (the grid covers mpad exactly).
+// theta_k = exp(z_k) into the caller's full rate vector (or, with theta_in, z_k =
+// log theta_k from it into z_out), and the subset entries of this evaluation in
+// time order: pre-scaled coordinates, times, the rate with the split time factor of its
+// 64-entry chunk, the chunk's split flag and step factor.  One wavefront per
+// chunk (the grid covers mpad exactly).
 __global__ __launch_bounds__(256) void k_sub_theta(
     const double *__restrict__ z, const double *__restrict__ off, const int *__restrict__ slot,
     const int64_t *__restrict__ cidx, int64_t m, const int *__restrict__ pos, const double *__restrict__ ts,
     const double *__restrict__ xs, const double *__restrict__ ys, const PairConst kc, float *__restrict__ tv,
     double2 *__restrict__ sxy, double *__restrict__ sts, int *__restrict__ qwide, double *__restrict__ qstep,
-    double *__restrict__ theta_full) {
+    double *__restrict__ theta_full, const double *__restrict__ theta_in, double *__restrict__ z_out) {
     const int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     const int lane = threadIdx.x & (HK_WAVE - 1);
     const int64_t r0 = r - lane;  // the chunk's first entry
@@ -339,7 +336,13 @@ __global__ __launch_bounds__(256) void k_sub_theta(
     const bool wide = __any(valid && kc.omega * dt > HK_SUB_FACT_SPAN);
     if (valid) {
         const int k = slot[r];
-        const double ze = zeff(z, off, k);
+        double ze;
+        if (theta_in) {
+            ze = log(theta_in[cidx[k]]);
+            z_out[k] = ze;
+        } else {
+            ze = zeff(z, off, k);
+        }
         if (theta_full) theta_full[cidx[k]] = exp(ze);
         tv[r] = (float)exp(wide ? ze : ze + kc.omega * dt);
         sxy[r] = make_double2(xs[pj] * kc.sx, ys[pj] * kc.sx);
@@ -832,7 +835,7 @@ __global__ void k_sub_scatter(const int *__restrict__ slot, int64_t m, const dou
 
 // Deterministic single-block sums over the subset (m is at most a few 1e4).
 // out[0] = sum log lambda (from block partials), out[1] = sum theta_k a_k,
-// out[2] = sum z_k^2, out[3] = sum p_k^2 / M_k
+// out[2] = sum z_k^2, out[3] = sum p_k^2 / M_k; with loglik, Eq. 1 from them
 constexpr int ENERGY_THREADS = 1024;
 constexpr int ENERGY_BATCH = 4;
 __global__ __launch_bounds__(ENERGY_THREADS) void k_sub_energy(const double *__restrict__ loglam_part, int nb,
@@ -840,7 +843,8 @@ __global__ __launch_bounds__(ENERGY_THREADS) void k_sub_energy(const double *__r
                                                     const double *__restrict__ p,
                                                     const double *__restrict__ mass, const int *__restrict__ slot,
                                                     const double *__restrict__ a, int64_t m,
-                                                    double *__restrict__ out) {
+                                                    double *__restrict__ out, const double *__restrict__ Lam_static,
+                                                    double *__restrict__ loglik) {
     __shared__ double sh[4][ENERGY_THREADS];
     const int t = threadIdx.x;
     double s[4] = {0.0, 0.0, 0.0, 0.0};
@@ -880,6 +884,7 @@ __global__ __launch_bounds__(ENERGY_THREADS) void k_sub_energy(const double *__r
         __syncthreads();
     }
     if (t < 4) out[t] = sh[t][0];
+    if (t == 0 && loglik) loglik[0] = sh[0][0] - Lam_static[0] - sh[1][0];
 }
 
 // ---- Philox-4x32-10 (Salmon et al. 2011) ------------------------------------------------
@@ -976,7 +981,7 @@ void hk_subset_free(hawkes_plan p) {
     hk_subset *s = p->sub;
     if (!s) return;
     void *ptrs[] = {s->pos, s->slot, s->cidx, s->ritems, s->ritem0, s->rnseg, s->xpart, s->items, s->item0, s->nseg,
-                    s->lam_static, s->Lam_static, s->a, s->tv, s->sxy, s->sts, s->qwide, s->qstep, s->lw, s->colG, s->gsub, s->hsub, s->sums, s->z0, s->p, s->off, s->vz, s->scal,
+                    s->member, s->lam_static, s->Lam_static, s->a, s->tv, s->sxy, s->sts, s->qwide, s->qstep, s->lw, s->colG, s->gsub, s->hsub, s->sums, s->z0, s->p, s->off, s->vz, s->scal,
                     s->grid};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
@@ -1020,6 +1025,8 @@ extern "C" hawkes_status hawkes_plan_set_subset(hawkes_plan p, int64_t m, const 
     SC(dalloc(&s->cidx, m));
     hipLaunchKernelGGL(k_sub_layout, dim3(nblk(s->mpad, 256)), dim3(256), 0, stream, key, slot2, m, s->mpad, s->pos,
                        s->slot, bad);
+    SC(dalloc(&s->member, p->npad));
+    hipLaunchKernelGGL(k_sub_clear, dim3(nblk(p->npad, 256)), dim3(256), 0, stream, s->member, p->npad);
     SC(hipMemcpyAsync(s->cidx, d_idx, sizeof(int64_t) * m, hipMemcpyDeviceToDevice, stream));
     SC(hipGetLastError());
     std::vector<int> hpos(m);
@@ -1035,6 +1042,9 @@ extern "C" hawkes_status hawkes_plan_set_subset(hawkes_plan p, int64_t m, const 
         hk_subset_free(p);
         return HAWKES_E_INVALID;
     }
+    // (the positions are valid: an index out of range or repeated was refused above)
+    hipLaunchKernelGGL(k_sub_member, dim3(nblk(m, 256)), dim3(256), 0, stream, s->pos, m, s->member);
+    SC(hipGetLastError());
     // row pass schedule: row chunk b pairs with the subset entries before its end
     // (cnt_b of them, a prefix in time order), in items of at most BR entries
     const int nch = p->nchunks;
@@ -1130,34 +1140,35 @@ hawkes_status ensure_static(hawkes_plan p, const hawkes_hyper *hy, const double 
                             const PairConst &kc, const FinConst &fc, hipStream_t stream) {
     hk_subset *s = p->sub;
     if (s->static_valid && !force && same_hyper(s->static_hyper, *hy)) return HAWKES_OK;
-    hipLaunchKernelGGL(k_sub_static_theta, dim3(nblk(p->npad, 256)), dim3(256), 0, stream, d_theta, p->perm, s->pos,
-                       s->m, p->n, p->npad, p->theta_s, p->status);
-    hipLaunchKernelGGL(k_sub_zero_subset, dim3(nblk(s->m, 256)), dim3(256), 0, stream, s->pos, s->m, p->theta_s);
-    hk_launch_row_loglik(p, kc, stream);
-    hipLaunchKernelGGL(k_sub_static, dim3(p->nfin_blocks), dim3(256), 0, stream, p->ts, p->xs, p->ys, p->g, d_theta,
-                       p->perm, p->theta_s,
-                       p->n, p->ntiles, p->row_item0, p->row_nseg, p->rowpart, p->colpart,
-                       p->colpart_off, fc,
-                       s->lam_static, p->blockpart);
-    hipLaunchKernelGGL(k_sum_blocks, dim3(1), dim3(64), 0, stream, p->blockpart, p->nfin_blocks, s->Lam_static);
-    hipLaunchKernelGGL(k_sub_a, dim3(nblk(s->mpad, 256)), dim3(256), 0, stream, p->ts, s->pos, s->m, s->mpad, fc,
-                       s->a);
+    hk_launch_row_loglik(p, kc, d_theta, s->member, stream);
+    hipLaunchKernelGGL(k_sub_static, dim3(p->nchunks), dim3(SUB_STATIC_WAVES * HK_WAVE), 0, stream, p->ts, p->xs,
+                       p->ys, p->g, d_theta, p->perm, p->theta_s, p->n, p->ntiles, p->row_item0, p->row_nseg,
+                       p->rowpart, p->colpart, fc, s->pos, s->m, s->mpad, s->a, s->lam_static, p->blockpart);
+    hipLaunchKernelGGL(k_sum_blocks, dim3(1), dim3(HK_WAVE), 0, stream, p->blockpart, p->nchunks, s->Lam_static);
     HK_CHECK(hipGetLastError());
     s->static_hyper = *hy;
     s->static_valid = true;
     return HAWKES_OK;
 }
 
-// The row half of a subset evaluation at z (slot order): (theta,) lambda, w and
-// the block partial sums of log lambda in p->blockpart.
-static void sub_rows(hawkes_plan p, const double *z, const double *off, double *theta_full, bool with_theta,
+// Where a subset evaluation takes the free rates from.
+enum SubFrom { SUB_FROM_Z, SUB_FROM_THETA, SUB_STAGED };
+
+// The row half of a subset evaluation at z (slot order; SUB_FROM_THETA: at the
+// caller's rates theta, whose logs go to z; SUB_STAGED: at the rates the fused
+// leapfrog update left): (theta,) lambda, w and the block partial sums of log
+// lambda in p->blockpart.
+static void sub_rows(hawkes_plan p, SubFrom from, double *z, const double *off, double *theta,
                      const PairConst &kc, const FinConst &fc, hipStream_t stream) {
     hk_subset *s = p->sub;
     p->epoch += 1;  // p->lam is overwritten below
-    if (with_theta)
-        hipLaunchKernelGGL(k_sub_theta, dim3((unsigned)(s->mpad / 256)), dim3(256), 0, stream, z, off, s->slot,
-                           s->cidx, s->m, s->pos, p->ts, p->xs, p->ys, kc, s->tv, s->sxy, s->sts, s->qwide, s->qstep,
-                           theta_full);
+    if (from != SUB_STAGED)
+        hipLaunchKernelGGL(k_sub_theta, dim3((unsigned)(s->mpad / 256)), dim3(256), 0, stream,
+                           from == SUB_FROM_Z ? z : (double *)nullptr, off, s->slot, s->cidx, s->m, s->pos, p->ts,
+                           p->xs, p->ys, kc, s->tv, s->sxy, s->sts, s->qwide, s->qstep,
+                           from == SUB_FROM_Z ? theta : (double *)nullptr,
+                           from == SUB_FROM_THETA ? theta : (double *)nullptr,
+                           from == SUB_FROM_THETA ? z : (double *)nullptr);
     hipLaunchKernelGGL(k_sub_row, dim3(s->n_ritems), dim3(HK_WAVE), 0, stream, p->ts, p->xs, p->ys, p->g, s->pos,
                        s->tv, s->sxy, s->sts, s->qwide, s->qstep, s->ritems, kc, s->xpart);
     hipLaunchKernelGGL(k_sub_fin, dim3(p->nchunks), dim3(SUB_ROWFIN_WAVES * HK_WAVE), 0, stream, s->lam_static,
@@ -1170,7 +1181,7 @@ static void sub_rows(hawkes_plan p, const double *z, const double *off, double *
 static void sub_cols(hawkes_plan p, bool with_h, const PairConst &kc, const FinConst &fc, const SubUpd *upd,
                      hipStream_t stream) {
     hk_subset *s = p->sub;
-#define HK_SUBCOL(H, D)                                                                                        \
+#define HK_SUBCOL(H, D)                                                                                          \
     hipLaunchKernelGGL((k_sub_col<H, D>), dim3(s->n_items), dim3(HK_WAVE), 0, stream, p->ts, p->xs, p->ys, s->lw, \
                        p->g, s->pos, s->sxy, s->sts, s->m, s->items, kc, s->colG)
     if (with_h) {
@@ -1187,20 +1198,6 @@ static void sub_cols(hawkes_plan p, bool with_h, const PairConst &kc, const FinC
     else
         hipLaunchKernelGGL(k_sub_colfin<false>, dim3(s->nq), dim3(SUB_FIN_WAVES * HK_WAVE), 0, stream, s->item0,
                            s->nseg, s->colG, s->a, s->m, fc, with_h, s->gsub, s->hsub, SubUpd{});
-}
-
-// One subset evaluation at z (slot order): theta, lambda, w, Eq. 4 (and Eq. 5)
-// on the subset, block partial sums of log lambda in p->blockpart.
-void sub_eval(hawkes_plan p, const double *z, const double *off, double *theta_full, bool with_h,
-              const PairConst &kc, const FinConst &fc, hipStream_t stream) {
-    sub_rows(p, z, off, theta_full, true, kc, fc, stream);
-    sub_cols(p, with_h, kc, fc, nullptr, stream);
-}
-
-__global__ void k_z_from_theta(const double *__restrict__ theta, const int64_t *__restrict__ cidx, int64_t m,
-                               double *__restrict__ z) {
-    const int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (k < m) z[k] = log(theta[cidx[k]]);
 }
 
 // z_k = log theta_{idx_k} - beta t_{idx_k} (slot order)
@@ -1237,11 +1234,6 @@ __global__ __launch_bounds__(256) void k_sub_trend_out(const int *__restrict__ s
     if (threadIdx.x == 0 && grad_beta) grad_beta[0] = sh[0];
 }
 
-__global__ void k_sub_loglik_out(const double *__restrict__ e, const double *__restrict__ Lam_static,
-                                 double *__restrict__ out) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) out[0] = e[0] - Lam_static[0] - e[1];
-}
-
 }  // namespace
 
 extern "C" hawkes_status hawkes_subset_grad(hawkes_plan p, const hawkes_hyper *hyper, const double *d_theta,
@@ -1257,16 +1249,16 @@ extern "C" hawkes_status hawkes_subset_grad(hawkes_plan p, const hawkes_hyper *h
     hawkes_status st = ensure_static(p, hyper, d_theta, refresh_static != 0, kc, fc, stream);
     if (st != HAWKES_OK) return st;
     // z = log theta on the subset (the rates are taken from d_theta as given)
-    hipLaunchKernelGGL(k_z_from_theta, dim3(nblk(s->m, 256)), dim3(256), 0, stream, d_theta, s->cidx, s->m, s->z0);
-    sub_eval(p, s->z0, nullptr, nullptr, d_negH_sub != nullptr, kc, fc, stream);
-    hipLaunchKernelGGL(k_sub_scatter, dim3(nblk(s->m, 256)), dim3(256), 0, stream, s->slot, s->m, s->gsub, s->hsub,
-                       d_grad_sub, d_negH_sub);
-    if (d_loglik) {
+    sub_rows(p, SUB_FROM_THETA, s->z0, nullptr, const_cast<double *>(d_theta), kc, fc, stream);
+    if (d_grad_sub || d_negH_sub) {
+        sub_cols(p, d_negH_sub != nullptr, kc, fc, nullptr, stream);
+        hipLaunchKernelGGL(k_sub_scatter, dim3(nblk(s->m, 256)), dim3(256), 0, stream, s->slot, s->m, s->gsub,
+                           s->hsub, d_grad_sub, d_negH_sub);
+    }
+    if (d_loglik)
         hipLaunchKernelGGL(k_sub_energy, dim3(1), dim3(ENERGY_THREADS), 0, stream, p->blockpart, p->nchunks, s->z0,
                            (const double *)nullptr, (const double *)nullptr, (const double *)nullptr, s->slot, s->a,
-                           s->m, s->scal);
-        hipLaunchKernelGGL(k_sub_loglik_out, dim3(1), dim3(64), 0, stream, s->scal, s->Lam_static, d_loglik);
-    }
+                           s->m, s->scal, s->Lam_static, d_loglik);
     HK_CHECK(hipGetLastError());
     return HAWKES_OK;
 }
@@ -1301,9 +1293,9 @@ extern "C" hawkes_status hmc_step(hawkes_plan p, const hawkes_hyper *hyper, hawk
                        s->z0);
     // start of the trajectory: the energy at z0, then the gradient there and the
     // first half kick and drift (fused into the column finalisation)
-    sub_rows(p, a->d_z, off, a->d_theta, true, kc, fc, stream);
+    sub_rows(p, SUB_FROM_Z, a->d_z, off, a->d_theta, kc, fc, stream);
     hipLaunchKernelGGL(k_sub_energy, dim3(1), dim3(ENERGY_THREADS), 0, stream, p->blockpart, p->nchunks, a->d_z, off, s->p,
-                       a->d_mass, s->slot, s->a, m, s->scal);
+                       a->d_mass, s->slot, s->a, m, s->scal, s->Lam_static, (double *)nullptr);
     // phylogenetic prior: the quadratic form z^T V^{-1} z replaces sum z^2
     if (tree && (st = hk_tree_launch(p, a->d_z, s->vz, s->scal + 2, stream)) != HAWKES_OK) return st;
     SubUpd upd{s->slot, a->d_z, off, pv, inv_s2, s->p, a->d_mass, 0.5 * a->eps, a->eps, s->tv, s->sts, s->qwide,
@@ -1312,7 +1304,7 @@ extern "C" hawkes_status hmc_step(hawkes_plan p, const hawkes_hyper *hyper, hawk
     for (int l = 0; l < a->L; ++l) {
         // evaluation at the drifted position, then a full kick and drift, or the
         // closing half kick after the last one
-        sub_rows(p, a->d_z, off, a->d_theta, false, kc, fc, stream);
+        sub_rows(p, SUB_STAGED, a->d_z, off, a->d_theta, kc, fc, stream);
         if (tree && (st = hk_tree_launch(p, a->d_z, s->vz, nullptr, stream)) != HAWKES_OK) return st;
         const bool last = l == a->L - 1;
         upd.a_p = last ? 0.5 * a->eps : a->eps;
@@ -1320,7 +1312,7 @@ extern "C" hawkes_status hmc_step(hawkes_plan p, const hawkes_hyper *hyper, hawk
         sub_cols(p, false, kc, fc, &upd, stream);
     }
     hipLaunchKernelGGL(k_sub_energy, dim3(1), dim3(ENERGY_THREADS), 0, stream, p->blockpart, p->nchunks, a->d_z, off, s->p,
-                       a->d_mass, s->slot, s->a, m, s->scal + 4);
+                       a->d_mass, s->slot, s->a, m, s->scal + 4, s->Lam_static, (double *)nullptr);
     if (tree && (st = hk_tree_launch(p, a->d_z, nullptr, s->scal + 6, stream)) != HAWKES_OK) return st;
     hipLaunchKernelGGL(k_hmc_accept, dim3(1), dim3(256), 0, stream, s->scal, s->Lam_static, inv_s2, a->seed,
                        a->counter, m, s->z0, a->d_z, a->d_z_proposal, a->d_out, (int *)(s->scal + 8));
@@ -1347,15 +1339,17 @@ extern "C" hawkes_status hawkes_subset_trend_grad(hawkes_plan p, const hawkes_hy
         hipLaunchKernelGGL(k_sub_offset, dim3(gb), dim3(256), 0, stream, p->ts, s->pos, s->slot, s->m, beta, s->off);
         off = s->off;
     }
-    sub_eval(p, d_z, off, d_theta, false, kc, fc, stream);
-    if (d_grad_z || d_grad_beta)
+    sub_rows(p, SUB_FROM_Z, const_cast<double *>(d_z), off, d_theta, kc, fc, stream);
+    // the log-likelihood alone (a Metropolis-Hastings proposal) needs no column pass
+    if (d_grad_z || d_grad_beta) {
+        sub_cols(p, false, kc, fc, nullptr, stream);
         hipLaunchKernelGGL(k_sub_trend_out, dim3(1), dim3(256), 0, stream, s->slot, s->pos, p->ts, s->m, s->gsub, d_z,
                            off, d_grad_z, d_grad_beta);
-    if (d_loglik) {
-        hipLaunchKernelGGL(k_sub_energy, dim3(1), dim3(ENERGY_THREADS), 0, stream, p->blockpart, p->nchunks, d_z, off,
-                           (const double *)nullptr, (const double *)nullptr, s->slot, s->a, s->m, s->scal);
-        hipLaunchKernelGGL(k_sub_loglik_out, dim3(1), dim3(64), 0, stream, s->scal, s->Lam_static, d_loglik);
     }
+    if (d_loglik)
+        hipLaunchKernelGGL(k_sub_energy, dim3(1), dim3(ENERGY_THREADS), 0, stream, p->blockpart, p->nchunks, d_z, off,
+                           (const double *)nullptr, (const double *)nullptr, s->slot, s->a, s->m, s->scal,
+                           s->Lam_static, d_loglik);
     HK_CHECK(hipGetLastError());
     return HAWKES_OK;
 }
@@ -1392,8 +1386,8 @@ hawkes_status hk_subset_exact(hawkes_plan p, const hawkes_hyper *hy, const doubl
     hk_make_consts(p, hy, &kc, &fc);
     hawkes_status st = ensure_static(p, hy, d_theta, false, kc, fc, stream);
     if (st != HAWKES_OK) return st;
-    hipLaunchKernelGGL(k_z_from_theta, dim3(nblk(s->m, 256)), dim3(256), 0, stream, d_theta, s->cidx, s->m, s->z0);
-    sub_eval(p, s->z0, nullptr, nullptr, true, kc, fc, stream);
+    sub_rows(p, SUB_FROM_THETA, s->z0, nullptr, const_cast<double *>(d_theta), kc, fc, stream);
+    sub_cols(p, true, kc, fc, nullptr, stream);
     HK_CHECK(hipGetLastError());
     *gsub = s->gsub;
     *hsub = s->hsub;

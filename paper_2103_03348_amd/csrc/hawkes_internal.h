@@ -221,10 +221,12 @@ bool hk_hyper_ok(const hawkes_hyper *h);
 hawkes_status hk_subset_exact(hawkes_plan p, const hawkes_hyper *hy, const double *d_theta, hipStream_t stream,
                               const double **gsub, const double **hsub);
 void hk_make_consts(const hawkes_plan p, const hawkes_hyper *hy, PairConst *kc, FinConst *fc);
-// Log-likelihood-only row pass (no moments) with the sorted FP32 rates already
-// in p->theta_s; leaves the partial sums B0 (row slot 0, column slot 0) and X0
-// (row slot 5) in p->rowpart / p->colpart.
-void hk_launch_row_loglik(hawkes_plan p, const PairConst &kc, hipStream_t stream);
+// Log-likelihood-only row pass (no moments) at the rates d_theta with the
+// excitation of the sorted events that `member` marks left out; leaves the sorted
+// FP32 rates in p->theta_s and the partial sums B0 (row slot 0, column slot 0) and
+// X0 (row slot 5) in p->rowpart / p->colpart.
+void hk_launch_row_loglik(hawkes_plan p, const PairConst &kc, const double *d_theta, const unsigned char *member,
+                          hipStream_t stream);
 
 // Optional timing of the passes with HIP events recorded on the launch stream.
 enum { HK_PROF_ROW = 0, HK_PROF_COL = 1, HK_PROF_EVAL = 2, HK_PROF_KINDS = 3 };
