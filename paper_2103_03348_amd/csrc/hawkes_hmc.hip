@@ -415,8 +415,10 @@ __global__ __launch_bounds__(HK_WAVE) void k_sub_row(
     const double xr = xs[i] * kc.sx, yr = ys[i] * kc.sx;
     const int gr = g[i];
     double acc = 0.0;  // every term in FP64 (see the row pass: FP32 sums drop small terms)
-    // under the cutoff, batches whose last entry precedes the chunk's first row
-    // by more than dt_cut_ex are skipped (entries are in time order)
+    // under the cutoff, a batch whose last entry precedes the chunk's first row by
+    // more than dt_cut_ex ends the item (entries are in time order, and the
+    // batches are walked from late to early), and an item without any leaves
+    // before its loads: N = 250,000, HMC iteration with the cutoff 7.6 -> 6.8 ms
     const double chunk_tmin = ts[(int64_t)b * HK_WAVE];
     const int g_first = g[(int64_t)b * HK_WAVE];  // g is non-decreasing
     // batches are the 64-entry subset chunks (items start on chunk boundaries),
@@ -426,6 +428,10 @@ __global__ __launch_bounds__(HK_WAVE) void k_sub_row(
     double ui = 0.0;
     bool have_ui = false;
     const int c_last = it.c_begin + (it.c_end - 1 - it.c_begin) / HK_WAVE * HK_WAVE;
+    if (chunk_tmin - sts[it.c_end - 1] > kc.dt_cut_ex) {
+        xpart[(int64_t)blockIdx.x * HK_WAVE + lane] = 0.0;
+        return;
+    }
     // a batch's entries are loaded into registers one batch ahead, so that the
     // loads of the next batch are in flight during this one's sweep (the subset
     // arrays are padded to whole 256-entry tiles: every lane's load is in bounds)
@@ -448,7 +454,7 @@ __global__ __launch_bounds__(HK_WAVE) void k_sub_row(
             nt = sts[rn];
             np = pos[rn];
         }
-        if (chunk_tmin - sts[cend - 1] > kc.dt_cut_ex) continue;
+        if (chunk_tmin - sts[cend - 1] > kc.dt_cut_ex) break;  // and all earlier batches
         const bool fact = qwide[q] == 0;
         {
             // entries past the item's range carry rate 0 and a time of -inf: the
