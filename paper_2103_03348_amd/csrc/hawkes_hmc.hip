@@ -33,6 +33,7 @@
 #include <vector>
 
 #include "hawkes_internal.h"
+#include "hawkes_tree.h"
 
 struct hk_subset {
     int64_t m;           // subset size
@@ -397,17 +398,25 @@ __device__ __forceinline__ void sub_row_sweep(const double2 *__restrict__ rxy, c
 
 // One item: the 64 rows of a chunk against a range of the subset entries that
 // precede the chunk's end (64 at a time through LDS); the rows' partial sums go
-// to the item's slot.
+// to the item's slot.  With TREE, the first blocks take the phylogenetic prior's
+// low step at the same z, one subtree each.
+template <bool TREE>
 __global__ __launch_bounds__(HK_WAVE) void k_sub_row(
     const double *__restrict__ ts, const double *__restrict__ xs, const double *__restrict__ ys, const int *__restrict__ g,
     const int *__restrict__ pos, const float *__restrict__ tv, const double2 *__restrict__ sxy,
     const double *__restrict__ sts, const int *__restrict__ qwide, const double *__restrict__ qstep,
-    const hk_item *__restrict__ ritems, const PairConst kc, double *__restrict__ xpart) {
+    const hk_item *__restrict__ ritems, const PairConst kc, double *__restrict__ xpart, const TreeDense tree,
+    const double *__restrict__ z) {
+    if (TREE && (int)blockIdx.x < tree.R) {
+        hk_tree_low(tree, z, blockIdx.x);
+        return;
+    }
+    const int item = (int)blockIdx.x - (TREE ? tree.R : 0);
     __shared__ double2 rxy[HK_WAVE];
     __shared__ float rv[HK_WAVE];
     __shared__ double rtd[HK_WAVE];
     __shared__ int rpos[HK_WAVE];
-    const hk_item it = ritems[blockIdx.x];
+    const hk_item it = ritems[item];
     const int b = it.tile;
     const int lane = threadIdx.x;
     const int64_t i = (int64_t)b * HK_WAVE + lane;
@@ -429,7 +438,7 @@ __global__ __launch_bounds__(HK_WAVE) void k_sub_row(
     bool have_ui = false;
     const int c_last = it.c_begin + (it.c_end - 1 - it.c_begin) / HK_WAVE * HK_WAVE;
     if (chunk_tmin - sts[it.c_end - 1] > kc.dt_cut_ex) {
-        xpart[(int64_t)blockIdx.x * HK_WAVE + lane] = 0.0;
+        xpart[(int64_t)item * HK_WAVE + lane] = 0.0;
         return;
     }
     // a batch's entries are loaded into registers one batch ahead, so that the
@@ -490,7 +499,7 @@ __global__ __launch_bounds__(HK_WAVE) void k_sub_row(
         }
         __syncthreads();
     }
-    xpart[(int64_t)blockIdx.x * HK_WAVE + lane] = acc;
+    xpart[(int64_t)item * HK_WAVE + lane] = acc;
 }
 
 // One block per 64-row chunk.  Its SUB_ROWFIN_WAVES wavefronts split the
@@ -499,6 +508,10 @@ __global__ __launch_bounds__(HK_WAVE) void k_sub_row(
 // partial-sum reads are in flight together; wavefront 0 then finalises the
 // rows.  The chunk's sum of log lambda goes to blockpart[chunk], and the
 // subset column pass's weight w_i = c_e / lambda_i to lw as its log2 (FP64).
+//
+// With TREE, the first blocks take the phylogenetic prior's top step at the same z
+// (its low step rode on the row pass).
+template <bool TREE>
 __global__ __launch_bounds__(SUB_ROWFIN_WAVES * HK_WAVE) void k_sub_fin(const double *__restrict__ lam_static,
                                                  const int *__restrict__ ritem0, const int *__restrict__ rnseg,
                                                  const double *__restrict__ xpart, const double *__restrict__ ts,
@@ -508,9 +521,18 @@ __global__ __launch_bounds__(SUB_ROWFIN_WAVES * HK_WAVE) void k_sub_fin(const do
                                                  const int *__restrict__ qwide, int64_t m,
                                                  int64_t n, int64_t npad, const FinConst fc,
                                                  double *__restrict__ lam, double *__restrict__ lw,
-                                                 double *__restrict__ blockpart, int *__restrict__ status) {
+                                                 double *__restrict__ blockpart, int *__restrict__ status,
+                                                 const TreeDense tree, double *__restrict__ vz) {
+    const int first = TREE ? hk_tree_top_blocks(tree.R) : 0;
+    if (TREE) {
+        static_assert(SUB_ROWFIN_WAVES * HK_WAVE == HK_TREE_TOP_THREADS, "threads of the prior's blocks");
+        if ((int)blockIdx.x < first) {
+            hk_tree_top(tree, blockIdx.x, vz);
+            return;
+        }
+    }
     __shared__ double part[SUB_ROWFIN_WAVES][HK_WAVE];
-    const int b = blockIdx.x, lane = threadIdx.x & (HK_WAVE - 1);
+    const int b = (int)blockIdx.x - first, lane = threadIdx.x & (HK_WAVE - 1);
     const int wq = __builtin_amdgcn_readfirstlane(threadIdx.x / HK_WAVE);
     const int64_t i0 = (int64_t)b * HK_WAVE;  // the chunk's first event
     const int64_t i = i0 + lane;
@@ -841,7 +863,8 @@ __global__ void k_sub_scatter(const int *__restrict__ slot, int64_t m, const dou
 
 // Deterministic single-block sums over the subset (m is at most a few 1e4).
 // out[0] = sum log lambda (from block partials), out[1] = sum theta_k a_k,
-// out[2] = sum z_k^2, out[3] = sum p_k^2 / M_k; with loglik, Eq. 1 from them
+// out[2] = sum z_k^2 (or, with quad, the sum of its n_quad parts), out[3] = sum
+// p_k^2 / M_k; with loglik, Eq. 1 from them
 constexpr int ENERGY_THREADS = 1024;
 constexpr int ENERGY_BATCH = 4;
 __global__ __launch_bounds__(ENERGY_THREADS) void k_sub_energy(const double *__restrict__ loglam_part, int nb,
@@ -849,12 +872,14 @@ __global__ __launch_bounds__(ENERGY_THREADS) void k_sub_energy(const double *__r
                                                     const double *__restrict__ p,
                                                     const double *__restrict__ mass, const int *__restrict__ slot,
                                                     const double *__restrict__ a, int64_t m,
+                                                    const double *__restrict__ quad, int n_quad,
                                                     double *__restrict__ out, const double *__restrict__ Lam_static,
                                                     double *__restrict__ loglik) {
     __shared__ double sh[4][ENERGY_THREADS];
     const int t = threadIdx.x;
     double s[4] = {0.0, 0.0, 0.0, 0.0};
     for (int b = t; b < nb; b += ENERGY_THREADS) s[0] += loglam_part[b];
+    for (int b = t; b < n_quad; b += ENERGY_THREADS) s[2] += quad[b];
     // a thread's entries are gathered ENERGY_BATCH at a time (the loads through
     // the slot issue together), then summed in entry order
     for (int64_t base = t; base < m; base += (int64_t)ENERGY_BATCH * ENERGY_THREADS) {
@@ -878,7 +903,7 @@ __global__ __launch_bounds__(ENERGY_THREADS) void k_sub_energy(const double *__r
         for (int e = 0; e < ENERGY_BATCH; ++e) {
             if (base + (int64_t)e * ENERGY_THREADS >= m) break;
             s[1] += exp(off ? zk[e] + ok[e] : zk[e]) * ak[e];
-            s[2] += zk[e] * zk[e];
+            if (!quad) s[2] += zk[e] * zk[e];
             if (p) s[3] += pk[e] * pk[e] / mk[e];
         }
     }
@@ -1164,8 +1189,8 @@ enum SubFrom { SUB_FROM_Z, SUB_FROM_THETA, SUB_STAGED };
 // caller's rates theta, whose logs go to z; SUB_STAGED: at the rates the fused
 // leapfrog update left): (theta,) lambda, w and the block partial sums of log
 // lambda in p->blockpart.
-static void sub_rows(hawkes_plan p, SubFrom from, double *z, const double *off, double *theta,
-                     const PairConst &kc, const FinConst &fc, hipStream_t stream) {
+static void sub_rows(hawkes_plan p, SubFrom from, double *z, const double *off, double *theta, const PairConst &kc,
+                     const FinConst &fc, hipStream_t stream, const TreeDense *tree = nullptr) {
     hk_subset *s = p->sub;
     p->epoch += 1;  // p->lam is overwritten below
     if (from != SUB_STAGED)
@@ -1175,11 +1200,18 @@ static void sub_rows(hawkes_plan p, SubFrom from, double *z, const double *off, 
                            from == SUB_FROM_Z ? theta : (double *)nullptr,
                            from == SUB_FROM_THETA ? theta : (double *)nullptr,
                            from == SUB_FROM_THETA ? z : (double *)nullptr);
-    hipLaunchKernelGGL(k_sub_row, dim3(s->n_ritems), dim3(HK_WAVE), 0, stream, p->ts, p->xs, p->ys, p->g, s->pos,
-                       s->tv, s->sxy, s->sts, s->qwide, s->qstep, s->ritems, kc, s->xpart);
-    hipLaunchKernelGGL(k_sub_fin, dim3(p->nchunks), dim3(SUB_ROWFIN_WAVES * HK_WAVE), 0, stream, s->lam_static,
-                       s->ritem0, s->rnseg, s->xpart, p->ts, p->xs, p->ys, p->g, s->pos, s->tv, s->sts, s->qwide,
-                       s->m, p->n, p->npad, fc, p->lam, s->lw, p->blockpart, p->status);
+#define HK_SUBROWS(T, LOW, TOP, TD)                                                                                 \
+    do {                                                                                                            \
+        hipLaunchKernelGGL(k_sub_row<T>, dim3(s->n_ritems + (LOW)), dim3(HK_WAVE), 0, stream, p->ts, p->xs, p->ys,    \
+                           p->g, s->pos, s->tv, s->sxy, s->sts, s->qwide, s->qstep, s->ritems, kc, s->xpart, TD, z);  \
+        hipLaunchKernelGGL(k_sub_fin<T>, dim3(p->nchunks + (TOP)), dim3(SUB_ROWFIN_WAVES * HK_WAVE), 0, stream,       \
+                           s->lam_static, s->ritem0, s->rnseg, s->xpart, p->ts, p->xs, p->ys, p->g, s->pos, s->tv,    \
+                           s->sts, s->qwide, s->m, p->n, p->npad, fc, p->lam, s->lw, p->blockpart, p->status, TD,     \
+                           s->vz);                                                                                  \
+    } while (0)
+    if (tree) HK_SUBROWS(true, tree->R, hk_tree_top_blocks(tree->R), *tree);
+    else HK_SUBROWS(false, 0, 0, TreeDense{});
+#undef HK_SUBROWS
 }
 
 // The column half: Eq. 4 (and Eq. 5) on the subset, optionally with the fused
@@ -1264,7 +1296,7 @@ extern "C" hawkes_status hawkes_subset_grad(hawkes_plan p, const hawkes_hyper *h
     if (d_loglik)
         hipLaunchKernelGGL(k_sub_energy, dim3(1), dim3(ENERGY_THREADS), 0, stream, p->blockpart, p->nchunks, s->z0,
                            (const double *)nullptr, (const double *)nullptr, (const double *)nullptr, s->slot, s->a,
-                           s->m, s->scal, s->Lam_static, d_loglik);
+                           s->m, (const double *)nullptr, 0, s->scal, s->Lam_static, d_loglik);
     HK_CHECK(hipGetLastError());
     return HAWKES_OK;
 }
@@ -1297,29 +1329,35 @@ extern "C" hawkes_status hmc_step(hawkes_plan p, const hawkes_hyper *hyper, hawk
     }
     hipLaunchKernelGGL(k_hmc_init, dim3(gb), dim3(256), 0, stream, m, a->seed, a->counter, a->d_mass, a->d_z, s->p,
                        s->z0);
+    // the phylogenetic prior at an evaluation's z: as extra blocks of its row half,
+    // or, where its tree is too large for that, by a launch of its own
+    const TreeDense *td = tree ? hk_tree_dense(p) : nullptr;
+    const bool walk = tree && !td;
     // start of the trajectory: the energy at z0, then the gradient there and the
     // first half kick and drift (fused into the column finalisation)
-    sub_rows(p, SUB_FROM_Z, a->d_z, off, a->d_theta, kc, fc, stream);
+    sub_rows(p, SUB_FROM_Z, a->d_z, off, a->d_theta, kc, fc, stream, td);
+    // (under the phylogenetic prior the quadratic form z^T V^{-1} z stands in for sum z^2)
     hipLaunchKernelGGL(k_sub_energy, dim3(1), dim3(ENERGY_THREADS), 0, stream, p->blockpart, p->nchunks, a->d_z, off, s->p,
-                       a->d_mass, s->slot, s->a, m, s->scal, s->Lam_static, (double *)nullptr);
-    // phylogenetic prior: the quadratic form z^T V^{-1} z replaces sum z^2
-    if (tree && (st = hk_tree_launch(p, a->d_z, s->vz, s->scal + 2, stream)) != HAWKES_OK) return st;
+                       a->d_mass, s->slot, s->a, m, td ? td->quad : nullptr, td ? td->R : 0, s->scal, s->Lam_static,
+                       (double *)nullptr);
+    if (walk && (st = hk_tree_launch(p, a->d_z, s->vz, s->scal + 2, stream)) != HAWKES_OK) return st;
     SubUpd upd{s->slot, a->d_z, off, pv, inv_s2, s->p, a->d_mass, 0.5 * a->eps, a->eps, s->tv, s->sts, s->qwide,
                kc.omega};
     sub_cols(p, false, kc, fc, &upd, stream);
     for (int l = 0; l < a->L; ++l) {
         // evaluation at the drifted position, then a full kick and drift, or the
         // closing half kick after the last one
-        sub_rows(p, SUB_STAGED, a->d_z, off, a->d_theta, kc, fc, stream);
-        if (tree && (st = hk_tree_launch(p, a->d_z, s->vz, nullptr, stream)) != HAWKES_OK) return st;
         const bool last = l == a->L - 1;
+        sub_rows(p, SUB_STAGED, a->d_z, off, a->d_theta, kc, fc, stream, td);
+        if (walk && (st = hk_tree_launch(p, a->d_z, s->vz, nullptr, stream)) != HAWKES_OK) return st;
         upd.a_p = last ? 0.5 * a->eps : a->eps;
         upd.a_z = last ? 0.0 : a->eps;
         sub_cols(p, false, kc, fc, &upd, stream);
     }
     hipLaunchKernelGGL(k_sub_energy, dim3(1), dim3(ENERGY_THREADS), 0, stream, p->blockpart, p->nchunks, a->d_z, off, s->p,
-                       a->d_mass, s->slot, s->a, m, s->scal + 4, s->Lam_static, (double *)nullptr);
-    if (tree && (st = hk_tree_launch(p, a->d_z, nullptr, s->scal + 6, stream)) != HAWKES_OK) return st;
+                       a->d_mass, s->slot, s->a, m, td ? td->quad : nullptr, td ? td->R : 0, s->scal + 4, s->Lam_static,
+                       (double *)nullptr);
+    if (walk && (st = hk_tree_launch(p, a->d_z, nullptr, s->scal + 6, stream)) != HAWKES_OK) return st;
     hipLaunchKernelGGL(k_hmc_accept, dim3(1), dim3(256), 0, stream, s->scal, s->Lam_static, inv_s2, a->seed,
                        a->counter, m, s->z0, a->d_z, a->d_z_proposal, a->d_out, (int *)(s->scal + 8));
     hipLaunchKernelGGL(k_sub_theta_full, dim3(gb), dim3(256), 0, stream, a->d_z, off, s->cidx, m, a->d_theta);
@@ -1354,8 +1392,8 @@ extern "C" hawkes_status hawkes_subset_trend_grad(hawkes_plan p, const hawkes_hy
     }
     if (d_loglik)
         hipLaunchKernelGGL(k_sub_energy, dim3(1), dim3(ENERGY_THREADS), 0, stream, p->blockpart, p->nchunks, d_z, off,
-                           (const double *)nullptr, (const double *)nullptr, s->slot, s->a, s->m, s->scal,
-                           s->Lam_static, d_loglik);
+                           (const double *)nullptr, (const double *)nullptr, s->slot, s->a, s->m, (const double *)nullptr, 0,
+                           s->scal, s->Lam_static, d_loglik);
     HK_CHECK(hipGetLastError());
     return HAWKES_OK;
 }

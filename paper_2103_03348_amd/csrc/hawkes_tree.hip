@@ -26,9 +26,11 @@
 //    sibling c, and (V^{-1})_kk = 1 / u_k at tip k.
 //
 // The v, alpha, s depend on the tree only and are formed once on the host in
-// FP64.  On the device one block walks the levels of the tree (nodes grouped by
-// height, so that all children of a level are done before it), one thread per
-// node of a level, with a barrier between levels.
+// FP64.  On the device the prior is two dense steps over the tree cut into
+// subtrees (hawkes_tree.h), or, for a tree that needs too many of them, one block
+// walks the levels of the tree (nodes grouped by height, so that all children of
+// a level are done before it), one thread per node of a level, with a barrier
+// between levels.
 #include <hip/hip_runtime.h>
 #include <math.h>
 
@@ -36,6 +38,7 @@
 #include <vector>
 
 #include "hawkes_internal.h"
+#include "hawkes_tree.h"
 
 struct hk_tree {
     int64_t m;           // tips (= subset size)
@@ -53,6 +56,8 @@ struct hk_tree {
     double root_inv;     // 1 / (v_root + tau0)
     int *level0_h;       // host copy of level0 (launch loop bounds)
     double *pdiag;       // [m] diagonal of V^{-1}, tip (slot) order (device)
+    TreeDense dense;     // the cut tree (R = 0: none); its arrays are in `store`
+    void *store;
 };
 
 namespace {
@@ -115,6 +120,22 @@ __global__ __launch_bounds__(TREE_THREADS) void k_tree_prior(const double *__res
     if (tid == 0 && quad) quad[0] = red[0];
 }
 
+__global__ __launch_bounds__(HK_WAVE) void k_tree_low(const TreeDense t, const double *__restrict__ z) {
+    hk_tree_low(t, z, blockIdx.x);
+}
+
+__global__ __launch_bounds__(HK_TREE_TOP_THREADS) void k_tree_top(const TreeDense t, double *__restrict__ vz) {
+    hk_tree_top(t, blockIdx.x, vz);
+}
+
+// z^T V^{-1} z from the subtrees' parts, by one wavefront in a fixed order
+__global__ __launch_bounds__(HK_WAVE) void k_tree_quad(const TreeDense t, double *__restrict__ quad) {
+    double q = 0.0;
+    for (int r = threadIdx.x; r < t.R; r += HK_WAVE) q += t.quad[r];
+    for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o);
+    if (threadIdx.x == 0) quad[0] = q;
+}
+
 // log p(z) = -(m log(2 pi sigma^2) + log|V| + z^T V^{-1} z / sigma^2) / 2 and
 // its gradient -V^{-1} z / sigma^2
 __global__ void k_tree_logp(const double *__restrict__ quad, const double *__restrict__ vz, int64_t m,
@@ -135,7 +156,7 @@ hipError_t dalloc(T **p, size_t count) {
 void hk_tree_free(hawkes_plan p) {
     hk_tree *t = p->tree;
     if (!t) return;
-    void *ptrs[] = {t->order, t->level0, t->child, t->coef, t->mv, t->dd, t->pdiag};
+    void *ptrs[] = {t->order, t->level0, t->child, t->coef, t->mv, t->dd, t->pdiag, t->store};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
     delete[] t->level0_h;
@@ -147,11 +168,20 @@ int64_t hk_tree_tips(hawkes_plan p) { return p->tree ? p->tree->m : 0; }
 
 const double *hk_tree_precision_diag(hawkes_plan p) { return p->tree ? p->tree->pdiag : nullptr; }
 
+const TreeDense *hk_tree_dense(hawkes_plan p) { return p->tree && p->tree->dense.R > 0 ? &p->tree->dense : nullptr; }
+
 hawkes_status hk_tree_launch(hawkes_plan p, const double *d_z, double *d_vz, double *d_quad, hipStream_t stream) {
     hk_tree *t = p->tree;
     if (!t) return HAWKES_E_UNSUPPORTED;
-    hipLaunchKernelGGL(k_tree_prior, dim3(1), dim3(TREE_THREADS), 0, stream, d_z, t->m, t->order, t->level0,
-                       t->levels, t->child, t->coef, t->root, t->root_inv, t->mv, t->dd, d_vz, d_quad);
+    if (const TreeDense *td = hk_tree_dense(p)) {
+        hipLaunchKernelGGL(k_tree_low, dim3(td->R), dim3(HK_WAVE), 0, stream, *td, d_z);
+        hipLaunchKernelGGL(k_tree_top, dim3(hk_tree_top_blocks(td->R)), dim3(HK_TREE_TOP_THREADS), 0, stream, *td,
+                           d_vz ? d_vz : t->mv);
+        if (d_quad) hipLaunchKernelGGL(k_tree_quad, dim3(1), dim3(HK_WAVE), 0, stream, *td, d_quad);
+    } else {
+        hipLaunchKernelGGL(k_tree_prior, dim3(1), dim3(TREE_THREADS), 0, stream, d_z, t->m, t->order, t->level0,
+                           t->levels, t->child, t->coef, t->root, t->root_inv, t->mv, t->dd, d_vz, d_quad);
+    }
     HK_CHECK(hipGetLastError());
     return HAWKES_OK;
 }
@@ -256,9 +286,74 @@ extern "C" hawkes_status hawkes_plan_set_tree(hawkes_plan p, int64_t n_nodes, co
     std::vector<int> fill(start.begin(), start.end());
     for (int64_t v = m; v < n_nodes; ++v) order[fill[height[v] - 1]++] = (int)v;
 
+    // the cut: maximal subtrees of at most HK_TREE_SUB tips, in post-order
+    std::vector<int> tips(n_nodes, 0), subs, tip0(1, 0), tipv, subv;
+    for (int v : post) tips[v] = v < m ? 1 : tips[child[2 * v]] + tips[child[2 * v + 1]];
+    for (int v : post)
+        if (tips[v] <= HK_TREE_SUB && (parent[v] < 0 || tips[parent[v]] > HK_TREE_SUB)) subs.push_back(v);
+    const int R = (int)subs.size() <= HK_TREE_MAX_ROOTS ? (int)subs.size() : 0;
+    std::vector<int64_t> mat0;
+    std::vector<double> mat, wgt, Q((size_t)R * R), qrow(R);
+    if (R > 0) {
+        std::vector<double> mean(n_nodes, 0.0), adj(n_nodes, 0.0);
+        // the recursions over the internal nodes `in` (children before parents):
+        // from the means of what lies below them and the adjoint of the last one
+        const auto up_down = [&](const std::vector<int> &in) {
+            for (int v : in)
+                mean[v] = coef[3 * (size_t)v] * mean[child[2 * v]] + coef[3 * (size_t)v + 1] * mean[child[2 * v + 1]];
+            for (auto it = in.rbegin(); it != in.rend(); ++it) {
+                const int v = *it, b = child[2 * v], c = child[2 * v + 1];
+                const double d = (mean[b] - mean[c]) * coef[3 * (size_t)v + 2];
+                adj[b] = coef[3 * (size_t)v] * adj[v] + d;
+                adj[c] = coef[3 * (size_t)v + 1] * adj[v] - d;
+            }
+        };
+        std::vector<int> at(n_nodes, 0);  // place in the post-order
+        for (size_t k = 0; k < post.size(); ++k) at[post[k]] = (int)k;
+        for (int s = 0; s < R; ++s) {
+            // a subtree's nodes end at its root in the post-order
+            const int v = subs[s], nt = tips[v], first = at[v] - (2 * nt - 2);
+            std::vector<int> in, leaf;
+            for (int k = first; k <= at[v]; ++k) (post[k] < m ? leaf : in).push_back(post[k]);
+            mat0.push_back((int64_t)mat.size());
+            for (int k : leaf) mean[k] = 0.0;
+            for (int j = 0; j < nt; ++j) {  // column j of M_s: unit mean at tip j, no adjoint from above
+                mean[leaf[j]] = 1.0;
+                adj[v] = 0.0;
+                up_down(in);
+                for (int k : leaf) mat.push_back(adj[k]);
+                mean[leaf[j]] = 0.0;
+            }
+            adj[v] = 1.0;  // the weights: no means, unit adjoint from above
+            up_down(in);
+            for (int k : leaf) {
+                wgt.push_back(adj[k]);
+                tipv.push_back(k);
+                subv.push_back(s);
+            }
+            tip0.push_back((int)tipv.size());
+        }
+        std::vector<int> top;
+        for (int v : post)
+            if (tips[v] > HK_TREE_SUB) top.push_back(v);
+        for (int v : subs) mean[v] = 0.0;
+        for (int s = 0; s <= R; ++s) {  // columns of Q, then (all means 1) its row sums
+            for (int v : subs) mean[v] = s == R ? 1.0 : 0.0;
+            if (s < R) mean[subs[s]] = 1.0;
+            // the root's mean is needed before its adjoint
+            for (int v : top)
+                mean[v] = coef[3 * (size_t)v] * mean[child[2 * v]] + coef[3 * (size_t)v + 1] * mean[child[2 * v + 1]];
+            adj[root] = mean[root] / rv;
+            up_down(top);
+            for (int r = 0; r < R; ++r) (s < R ? Q[(size_t)s * R + r] : qrow[r]) = adj[subs[r]];
+        }
+    }
+
     hk_tree_free(p);
     hk_tree *t = new hk_tree();
     p->tree = t;
+    t->dense = TreeDense{};
+    t->store = nullptr;
     t->m = m;
     t->n_int = n_nodes - m;
     t->levels = H;
@@ -287,6 +382,45 @@ extern "C" hawkes_status hawkes_plan_set_tree(hawkes_plan p, int64_t n_nodes, co
     TC(hipMemcpy(t->child, child.data(), sizeof(int) * child.size(), hipMemcpyHostToDevice));
     TC(hipMemcpy(t->coef, coef.data(), sizeof(double) * coef.size(), hipMemcpyHostToDevice));
     TC(hipMemcpy(t->pdiag, pdiag.data(), sizeof(double) * m, hipMemcpyHostToDevice));
+    if (R > 0) {
+        // one allocation for the cut tree: 8-byte arrays, then the integers
+        const size_t nd = mat.size() + 2 * (size_t)m + Q.size() + 4 * (size_t)R, ni = 2 * (size_t)m + R + 1;
+        double *d;
+        TC(hipMalloc((void **)&d, sizeof(double) * (nd + R) + sizeof(int) * ni + 64));
+        t->store = d;
+        TreeDense &td = t->dense;
+        td.m = (int)m;
+        td.R = R;
+        const auto put = [&](const void *src, size_t bytes) {
+            void *dst = d;
+            d = (double *)((char *)d + (bytes + 7) / 8 * 8);
+            return src ? hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice) : hipSuccess;
+        };
+        td.mat = d;
+        TC(put(mat.data(), sizeof(double) * mat.size()));
+        td.w = d;
+        TC(put(wgt.data(), sizeof(double) * m));
+        td.Q = d;
+        TC(put(Q.data(), sizeof(double) * Q.size()));
+        td.qrow = d;
+        TC(put(qrow.data(), sizeof(double) * R));
+        td.mat0 = (const int64_t *)d;
+        TC(put(mat0.data(), sizeof(int64_t) * R));
+        td.y = d;
+        TC(put(nullptr, sizeof(double) * m));
+        td.mean = d;
+        TC(put(nullptr, sizeof(double) * R));
+        td.qlow = d;
+        TC(put(nullptr, sizeof(double) * R));
+        td.quad = d;
+        TC(put(nullptr, sizeof(double) * R));
+        td.tip0 = (const int *)d;
+        TC(put(tip0.data(), sizeof(int) * (R + 1)));
+        td.tip = (const int *)d;
+        TC(put(tipv.data(), sizeof(int) * m));
+        td.sub = (const int *)d;
+        TC(put(subv.data(), sizeof(int) * m));
+    }
 #undef TC
     return HAWKES_OK;
 }

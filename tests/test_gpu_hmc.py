@@ -527,3 +527,69 @@ def test_hmc_step_replays_oracle_n23422(gpu):
             else:
                 np.testing.assert_array_equal(zg, z0)
     plan.close()
+
+
+def _tree_shape(name):
+    """(parent, length) of named test trees, tips first, root last."""
+    kind, m = name.split("-")
+    m = int(m)
+    rng = np.random.default_rng(m)
+    if kind == "coalescent":
+        return synth.coalescent_tree(m, seed=m, scale=float(m))
+    parent = np.full(2 * m - 1, -1, dtype=np.int64)
+    if kind == "caterpillar":  # every merger adds one tip to the last node
+        last = 0
+        for k in range(1, m):
+            parent[last] = parent[k] = m + k - 1
+            last = m + k - 1
+    else:  # balanced
+        live, nxt = list(range(m)), m
+        while len(live) > 1:
+            a, b = live.pop(0), live.pop(0)
+            parent[a] = parent[b] = nxt
+            live.append(nxt)
+            nxt += 1
+    return parent, np.where(parent < 0, 0.0, rng.exponential(1.0, 2 * m - 1) + 0.01)
+
+
+@pytest.mark.parametrize("name", ["balanced-64", "coalescent-64", "coalescent-65", "balanced-512", "caterpillar-90",
+                                  "caterpillar-1087", "caterpillar-1088", "coalescent-4200"])
+def test_tree_prior_shapes(gpu, name):
+    """V^{-1} z and z^T V^{-1} z over trees at the edges of the cut (64 tips per
+    subtree; 1,024 subtrees, past which the levels are walked) against the joint
+    precision of all nodes with the internal ones eliminated
+    by a sparse FP64 solve.  FP64 throughout: 1e-10 relative."""
+    import torch
+    from scipy.sparse import coo_matrix
+    from scipy.sparse.linalg import spsolve
+
+    from paper_2103_03348_amd import _lib
+    from paper_2103_03348_amd.hawkes import Plan
+
+    par, ln = (np.ascontiguousarray(v) for v in _tree_shape(name))
+    n = par.shape[0]
+    m = (n + 1) // 2
+    tau0, sigma = 0.9, 0.5
+    w = 1.0 / np.where(par < 0, tau0, ln)
+    v, has = np.arange(n), par >= 0
+    rows = np.concatenate([v, par[has], v[has], par[has]])
+    cols = np.concatenate([v, par[has], par[has], v[has]])
+    vals = np.concatenate([w, w[has], -w[has], -w[has]])
+    Q = coo_matrix((vals, (rows, cols)), shape=(n, n)).tocsc()
+    z = np.random.default_rng(m).standard_normal(m)
+    vz = Q[:m, :m] @ z - Q[:m, m:] @ spsolve(Q[m:, m:], Q[m:, :m] @ z)
+
+    es = synth.small(300, seed=46)
+    plan = Plan.from_numpy(es.t, es.x, es.y, es.t0)
+    _lib.check(_lib.lib().hawkes_plan_set_tree(plan.handle, n, par.ctypes.data_as(ctypes.c_void_p),
+                                               ln.ctypes.data_as(ctypes.c_void_p), tau0), "set_tree")
+    dz = torch.as_tensor(z, device="cuda:0")
+    g = torch.zeros(m, dtype=torch.float64, device="cuda:0")
+    q = torch.zeros(1, dtype=torch.float64, device="cuda:0")
+    for _ in range(2):
+        _lib.check(_lib.lib().hawkes_tree_prior(plan.handle, _lib.ptr(dz), sigma, None, _lib.ptr(g), _lib.ptr(q),
+                                                _lib.stream_handle()), "tree_prior")
+        torch.cuda.synchronize()
+        assert abs(q.item() - z @ vz) <= 1e-10 * (z @ vz)
+        assert np.max(np.abs(g.cpu().numpy() + vz / sigma ** 2)) <= 1e-10 * np.max(np.abs(vz)) / sigma ** 2
+    plan.close()
