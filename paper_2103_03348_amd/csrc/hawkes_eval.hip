@@ -360,6 +360,21 @@ __global__ __launch_bounds__(HK_TILE, 4) void k_row(const double *__restrict__ t
         // chunk breaks the chain
         double ui = 0.0;
         bool have_ui = false;
+        // a chunk's columns are loaded one chunk ahead, after the previous chunk's
+        // sweep: their latency overlaps its column reduction (and, for a piece's
+        // first chunk, the row's own loads), and they hold no registers in a sweep
+        double st = 0.0, sx = 0.0, sy = 0.0;
+        float sv = 0.0f;
+        const auto fetch = [&](int c) {
+            if (tid < HK_WAVE) {
+                const int64_t j = (int64_t)c * HK_WAVE + tid;
+                st = ts[j];
+                sv = theta_v[j];
+                sx = xs[j];
+                sy = ys[j];
+            }
+        };
+        fetch(it.c_end - 1);
         for (int c = it.c_end - 1; c >= it.c_begin; --c) {
             if (have_ui) ui *= tstep[c];
             // under the cutoff a chunk that ends more than dt_cut before the
@@ -374,17 +389,15 @@ __global__ __launch_bounds__(HK_TILE, 4) void k_row(const double *__restrict__ t
             const float ti = (float)((tsi - Tc) * kc.st);  // scaled time
             const bool fact = chunk_precise[c] == 0;
             if (block_live && tid < HK_WAVE) {
-                const int64_t j = (int64_t)c * HK_WAVE + tid;
-                const double tj = ts[j];
                 float2 r;
-                r.x = (float)((tj - Tc) * kc.st);
-                r.y = theta_v[j];  // theta_j, times exp(omega (t_j - T_c)) on a fast chunk
+                r.x = (float)((st - Tc) * kc.st);
+                r.y = sv;  // theta_j, times exp(omega (t_j - T_c)) on a fast chunk
                 rec[tid] = r;
                 rec[tid + HK_WAVE] = r;
-                const double2 pj = make_double2(xs[j] * kc.sbx, ys[j] * kc.sbx);
+                const double2 pj = make_double2(sx * kc.sbx, sy * kc.sbx);
                 rxy[tid] = pj;
                 rxy[tid + HK_WAVE] = pj;
-                rtd[tid] = rtd[tid + HK_WAVE] = tj * kc.st;  // the precise form's FP64 scaled time
+                rtd[tid] = rtd[tid + HK_WAVE] = st * kc.st;  // the precise form's FP64 scaled time
             }
             __syncthreads();
             // the wave's column slots start at zero (the previous chunk's reads of
@@ -422,6 +435,7 @@ __global__ __launch_bounds__(HK_TILE, 4) void k_row(const double *__restrict__ t
                     have_ui = false;
                 }
             }
+            if (c > it.c_begin) fetch(c - 1);
             // after 64 rotation steps lane l holds the accumulators of column (l - 1) mod 64
             const int col = (lane + HK_WAVE - 1) & (HK_WAVE - 1);
 #pragma unroll
@@ -557,19 +571,24 @@ __device__ void fin_totals(const double *__restrict__ blockpart, int nblocks, do
 
 constexpr int HK_FIN_WAVES = 8;
 
-// The first wavefront of a k_fin block: lambda_i, w_i, the per-event terms of
-// the hyperparameter derivatives and the integral, and their block sums.
+// Whether a mode's finalisation forms sum k (0 log lambda; 1-6, 7-12 the
+// hyperparameters' first and second derivatives of it; 13 the integral, 14-17
+// and 18-19 its derivatives).
 template <int MODE>
-__device__ __forceinline__ void fin_events(const double *__restrict__ ts, const double *__restrict__ theta,
-                                           const int *__restrict__ perm, int64_t n, const FinConst &fc,
-                                           const double (*part)[HK_NROW][HK_WAVE],
+__device__ __forceinline__ constexpr bool fin_sum_used(int k) {
+    return k == 0 || k == 13 || (MODE >= HK_MODE_GRAD && (k < 7 || k > 13)) || MODE >= HK_MODE_HESS;
+}
+
+// One wavefront of a k_fin block: lambda_i, w_i and the per-event terms of log
+// lambda's hyperparameter derivatives, to sums[0..12][lane].
+template <int MODE>
+__device__ __forceinline__ void fin_events(int64_t n, const FinConst &fc, const double (*tot)[HK_WAVE],
                                            const double (*exact)[HK_WAVE], bool is_exact, int lane, int64_t i,
                                            double *__restrict__ lam, double *__restrict__ lw,
-                                           double *__restrict__ a_out, double *__restrict__ blockpart,
-                                           int *__restrict__ status) {
-    double s[HK_NSUM];
+                                           double (*sums)[HK_WAVE], int *__restrict__ status) {
+    double s[13];
 #pragma unroll
-    for (int k = 0; k < HK_NSUM; ++k) s[k] = 0.0;
+    for (int k = 0; k < 13; ++k) s[k] = 0.0;
     if (i < n) {
         // the ten sums in natural units: B0, B1 (r^2), B2 (dt^2), B11, B22,
         // X0, X1 (dt), X2 (r^2), X11, X22, from the pair passes' partials or,
@@ -589,11 +608,7 @@ __device__ __forceinline__ void fin_events(const double *__restrict__ ts, const 
         } else {
             double acc[HK_NROW];
 #pragma unroll
-            for (int k = 0; k < HK_NROW; ++k) {
-                double v = part[0][k][lane];
-                for (int q = 1; q < HK_FIN_WAVES; ++q) v += part[q][k][lane];
-                acc[k] = v;
-            }
+            for (int k = 0; k < HK_NROW; ++k) acc[k] = tot[k][lane];
             // moments corrected for the mean exp2 bias and, when the first moments
             // are present, for the rounding of the FP32 ratio rex
             double b0 = acc[0], x0 = acc[5];
@@ -646,7 +661,26 @@ __device__ __forceinline__ void fin_events(const double *__restrict__ ts, const 
                 for (int p = 0; p < 6; ++p) s[7 + p] = d2[p] * inv - s[1 + p] * s[1 + p];
             }
         }
-        // integral term (App. A for the excitation; exact background integral)
+    } else {
+        lam[i] = 1.0;
+        lw[i] = HK_EXP_FLOOR;
+    }
+#pragma unroll
+    for (int k = 0; k < 13; ++k)
+        if (fin_sum_used<MODE>(k)) sums[k][lane] = s[k];
+}
+
+// Another: the integral's per-event terms (App. A for the excitation; exact
+// background integral), to sums[13..19][lane], and a_i.
+template <int MODE>
+__device__ __forceinline__ void fin_integral(const double *__restrict__ ts, const double *__restrict__ theta,
+                                             const int *__restrict__ perm, int64_t n, const FinConst &fc, int lane,
+                                             int64_t i, double *__restrict__ a_out, double (*sums)[HK_WAVE]) {
+    double s[HK_NSUM];
+#pragma unroll
+    for (int k = 13; k < HK_NSUM; ++k) s[k] = 0.0;
+    double ai = 0.0;
+    if (i < n) {
         const double ti = ts[i];
         const double th = theta[perm[i]];
         const double sv = fc.t1 - ti;
@@ -655,7 +689,7 @@ __device__ __forceinline__ void fin_events(const double *__restrict__ ts, const 
         const double e = exp(-fc.omega * sv);
         const double one_m = -expm1(-fc.omega * sv);
         s[13] = fc.mu0 * Cn + fc.theta0 * th * one_m;
-        a_out[i] = fc.theta0 * one_m;
+        ai = fc.theta0 * one_m;
         if (MODE >= HK_MODE_GRAD) {
             const double p1 = std_pdf(u1), p0 = std_pdf(u0);
             s[14] = Cn;
@@ -665,18 +699,12 @@ __device__ __forceinline__ void fin_events(const double *__restrict__ ts, const 
             s[18] = fc.mu0 * (p1 * (2.0 * u1 - u1 * u1 * u1) - p0 * (2.0 * u0 - u0 * u0 * u0)) / (fc.tau_t * fc.tau_t);
             s[19] = -fc.theta0 * th * sv * sv * e;
         }
-    } else {
-        lam[i] = 1.0;
-        lw[i] = HK_EXP_FLOOR;
-        a_out[i] = 0.0;
     }
+    a_out[i] = ai;
 #pragma unroll
-    for (int k = 0; k < HK_NSUM; ++k) {
-        const double v = wave_sum_f64(s[k]);
-        if (lane == k) blockpart[(int64_t)k * gridDim.x + blockIdx.x] = v;
-    }
+    for (int k = 13; k < HK_NSUM; ++k)
+        if (fin_sum_used<MODE>(k)) sums[k][lane] = s[k];
 }
-
 
 // The ten sums of row i straight from the definitions (Sec. 2.1): b_ij over
 // every j != i, theta_j E_ij over the strictly earlier j, each term in FP64
@@ -713,9 +741,13 @@ __device__ void exact_row_sums(const double *__restrict__ ts, const double *__re
 
 // Finalisation, one block per 64-event chunk.  The HK_FIN_WAVES wavefronts
 // first split the partial sums of the chunk's events between them (row pieces
-// and column partials of the later row tiles, round robin; these reads are the
-// kernel's cost, so many are kept in flight), the partials are combined in a
-// fixed order through LDS, and the first wavefront finishes the events.
+// and column partials of the later row tiles, round robin; these reads are most
+// of the kernel's cost on large sets, so many are kept in flight) and combine
+// them in a fixed order through LDS, ten sums between the wavefronts.  One
+// wavefront then forms lambda and its derivatives, another the integral's terms,
+// and the wavefronts reduce the twenty per-event sums between them.  (With one
+// wavefront doing all that follows the partial sums, its 2,000 instructions were
+// most of the kernel on small sets: N = 1,000 8.3 -> 5.2 us, 23,422 17.3 -> 14.6.)
 template <int MODE>
 __global__ __launch_bounds__(HK_FIN_WAVES * HK_WAVE) void k_fin(const double *__restrict__ ts, const double *__restrict__ xs,
                                              const double *__restrict__ ys, const int *__restrict__ g,
@@ -774,17 +806,20 @@ __global__ __launch_bounds__(HK_FIN_WAVES * HK_WAVE) void k_fin(const double *__
         for (int k = 0; k < HK_NROW; ++k) part[wq][k][lane] = acc[k];
     }
     __syncthreads();
+    __shared__ double tot[HK_NROW][HK_WAVE];
+    for (int k = wq; k < HK_NROW; k += HK_FIN_WAVES) {
+        double v = part[0][k][lane];
+#pragma unroll
+        for (int q = 1; q < HK_FIN_WAVES; ++q) v += part[q][k][lane];
+        tot[k][lane] = v;
+    }
+    __syncthreads();
     // rows whose intensity from the partials is below fc.lam_exact (their FP32
     // terms may have lost more than 2^-30 of it) are recomputed here in FP64 by
     // the whole block, one row at a time; every wavefront derives the same mask
     __shared__ double exact[HK_NROW][HK_WAVE];
     __shared__ double red[HK_FIN_WAVES][HK_NROW];
-    double b0 = part[0][0][lane], x0 = part[0][5][lane];
-    for (int q = 1; q < HK_FIN_WAVES; ++q) {
-        b0 += part[q][0][lane];
-        x0 += part[q][5][lane];
-    }
-    const bool low = i < n && fc.c_b * b0 + fc.c_e * x0 < fc.lam_exact;
+    const bool low = i < n && fc.c_b * tot[0][lane] + fc.c_e * tot[5][lane] < fc.lam_exact;
     const uint64_t low_mask = __ballot(low);
     for (uint64_t mk = low_mask; mk != 0; mk &= mk - 1) {
         const int rr = __ffsll((unsigned long long)mk) - 1;
@@ -807,8 +842,14 @@ __global__ __launch_bounds__(HK_FIN_WAVES * HK_WAVE) void k_fin(const double *__
         }
         __syncthreads();
     }
-    if (wq == 0) fin_events<MODE>(ts, theta, perm, n, fc, part, exact, low, lane, i, lam, lw, a_out, blockpart,
-                                  status);
+    __shared__ double sums[HK_NSUM][HK_WAVE];
+    if (wq == 0) fin_events<MODE>(n, fc, tot, exact, low, lane, i, lam, lw, sums, status);
+    else if (wq == 1) fin_integral<MODE>(ts, theta, perm, n, fc, lane, i, a_out, sums);
+    __syncthreads();
+    for (int k = wq; k < HK_NSUM; k += HK_FIN_WAVES) {
+        const double v = fin_sum_used<MODE>(k) ? wave_sum_f64(sums[k][lane]) : 0.0;
+        if (lane == 0) blockpart[(int64_t)k * gridDim.x + blockIdx.x] = v;
+    }
 }
 
 // One block: the partials of every k_fin block -> the scalar results.

@@ -206,6 +206,13 @@ Schedule make_schedule(int T, Lo lo, Hi hi, Wt weight, int64_t slots) {
         }
     }
     if (s.block0.back() != (int)s.items.size()) s.block0.push_back((int)s.items.size());
+    // with fewer sweeps than slots (small sets) the runs are a sweep or two long, and
+    // a block with two pieces takes twice as long as the others: a block per piece
+    // instead (N = 1,000: row pass 31 -> 22 us)
+    if (nb == nch) {
+        s.block0.resize(s.items.size() + 1);
+        for (size_t q = 0; q <= s.items.size(); ++q) s.block0[q] = (int)q;
+    }
     return s;
 }
 

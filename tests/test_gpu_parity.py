@@ -480,3 +480,18 @@ def test_isolated_events_grad_only_matches_oracle(gpu, case):
     assert st == 0
     assert abs(ll - ref["loglik"]) <= 2e-6 * es.n
     assert g_rel < 1e-6
+
+
+@pytest.mark.parametrize("n", [64, 257, 320, 1025, 5000])
+def test_every_output_over_small_schedules(gpu, n):
+    """Sets with fewer sweeps than schedule slots (a block per piece), ending
+    inside a tile and on a chunk's edge: every output against the oracle, with
+    the bounds of the other parity tests."""
+    es = synth.small(n, seed=600 + n, ties=n // 20)
+    ref = oracle.evaluate_es(es)
+    g = run_gpu(es)
+    e = errors(es, g, ref)
+    assert g["status"] == 0
+    assert abs(g["loglik"] - ref["loglik"]) <= 2e-6 * n
+    assert e["lam_rel"] < 2e-6 and e["g_rel"] < 1e-6
+    assert e["h_rel_all"] < 1e-6 and e["h_rel_norm"] < 1e-6
