@@ -24,7 +24,8 @@
 //   k_sub_col      G_k = sum_{t_i > t_k} E_ik w_i, H_k = sum (E_ik w_i)^2, items
 //   k_sub_colfin   Eq. 4 / Eq. 5 on the subset; inside hmc_step also the
 //                  leapfrog's gradient in z, kick and drift
-//   k_hmc_*        momenta (Philox-4x32-10 + Box-Muller), energy, accept
+//   k_sub_energy   parts of the energies; k_hmc_accept the accept decision
+//                  (momenta, Philox-4x32-10 + Box-Muller, in k_sub_theta)
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <string.h>
@@ -75,7 +76,8 @@ struct hk_subset {
     double *z0, *p;      // [m] slot order
     double *off;         // [m] temporal-trend offsets beta t_k, slot order
     double *vz;          // [m] V^{-1} z of the phylogenetic prior, slot order
-    double *scal;        // [16] energies and flags
+    double *scal;        // [2][blocks][4] energies' parts (k_sub_energy), start and end of a trajectory
+    double *quad;        // [1] z^T V^{-1} z of a tree evaluated by its level walk
     // feature grids of the learned preconditioner
     int *grid;
     int64_t grid_cap;
@@ -84,13 +86,15 @@ struct hk_subset {
 namespace {
 
 // The subset passes are split into many one-wavefront items (about this many
-// each, and at most SUB_ITEM_BATCHES 64-wide batches per item, so that the
-// few items that still have work under the underflow cutoff stay short) so
-// that the whole chip takes part; partial sums per item are combined in a
-// fixed order afterwards.  Measured on the N = 23,422 HMC iteration (M = 1,610):
+// each, and at most SUB_ITEM_BATCHES 64-wide batches per item) so that the whole
+// chip takes part; partial sums per item are combined in a fixed order
+// afterwards.  Measured on the N = 23,422 HMC iteration (M = 1,610):
 // column items 4096 -> 8192 (one row chunk per item there) 0.616 -> 0.607 ms,
 // 2048 0.623 ms; row items 4096 0.639 ms, 16384 no change (one batch per item
-// already).
+// already).  The limit on an item's length bounds the last round of wavefronts
+// (and keeps the few items that still have work under the underflow cutoff
+// short): N = 250,000, with / without the cutoff, ms per iteration: 16 batches
+// 6.96 / 24.56, 8 6.08 / 24.03, 4 6.21 / 24.68.
 #ifndef HK_SUB_ROW_ITEMS
 #define HK_SUB_ROW_ITEMS 8192
 #endif
@@ -111,7 +115,7 @@ constexpr int SUB_FIN_BATCH = 8;
 #define HK_SUB_ROWFIN_WAVES 4
 #endif
 constexpr int SUB_ROWFIN_WAVES = HK_SUB_ROWFIN_WAVES;
-constexpr int64_t SUB_ITEM_BATCHES = 16;
+constexpr int64_t SUB_ITEM_BATCHES = 8;
 // unroll of the subset sweeps: 8 measured fastest (114 VGPRs, 4 wavefronts per
 // SIMD); shorter loops fit more wavefronts but lose more instruction-level
 // parallelism than that hides (N = 23,422 HMC iteration, 0.603 ms at 8: 4 ->
@@ -301,6 +305,29 @@ __global__ __launch_bounds__(HK_WAVE) void k_sum_blocks(const double *__restrict
     if (threadIdx.x == 0) out[0] = s + c;
 }
 
+// ---- Philox-4x32-10 (Salmon et al. 2011) ------------------------------------------------
+__device__ __forceinline__ void philox10(uint32_t c[4], uint32_t k0, uint32_t k1) {
+    for (int r = 0; r < 10; ++r) {
+        if (r > 0) {
+            k0 += 0x9E3779B9u;
+            k1 += 0xBB67AE85u;
+        }
+        const uint64_t p0 = (uint64_t)0xD2511F53u * c[0];
+        const uint64_t p1 = (uint64_t)0xCD9E8D57u * c[2];
+        const uint32_t hi0 = (uint32_t)(p0 >> 32), lo0 = (uint32_t)p0;
+        const uint32_t hi1 = (uint32_t)(p1 >> 32), lo1 = (uint32_t)p1;
+        const uint32_t n0 = hi1 ^ c[1] ^ k0, n2 = hi0 ^ c[3] ^ k1;
+        c[0] = n0;
+        c[1] = lo1;
+        c[2] = n2;
+        c[3] = lo0;
+    }
+}
+
+__device__ __forceinline__ double u53(uint32_t a, uint32_t b) {
+    return ((double)(a >> 5) * 67108864.0 + (double)(b >> 6)) * (1.0 / 9007199254740992.0);
+}
+
 // ---- per-evaluation kernels ---------------------------------------------------------------
 // log theta_k = z_k + off_k: off is the temporal-trend term beta f(t_k) of Sec.
 // 2.2 (slot order), or NULL for none.
@@ -308,7 +335,28 @@ __device__ __forceinline__ double zeff(const double *__restrict__ z, const doubl
     return off ? z[k] + off[k] : z[k];
 }
 
-// off_k = beta t_k for the subset events (their times, slot order)
+// The start of a trajectory, in the launch that stages its first evaluation: the
+// offsets off_k = beta t_k of the temporal trend (their times, slot order; off
+// NULL: none), the momenta p_k = sqrt(M_k) N(0,1) (element k uses counter (k, 0,
+// counter_lo, counter_hi)) and z0 <- z.
+struct SubStart {
+    int on;
+    uint64_t seed, counter;
+    const double *mass;
+    double *p, *z0;
+    double beta;
+    double *off;
+};
+
+__device__ __forceinline__ double hmc_momentum(int64_t k, uint64_t seed, uint64_t counter, double mass) {
+    uint32_t c[4] = {(uint32_t)k, 0u, (uint32_t)counter, (uint32_t)(counter >> 32)};
+    philox10(c, (uint32_t)seed, (uint32_t)(seed >> 32));
+    const double u1 = u53(c[0], c[1]), u2 = u53(c[2], c[3]);
+    const double nrm = sqrt(-2.0 * log1p(-u1)) * cos(6.283185307179586 * u2);
+    return sqrt(mass) * nrm;
+}
+
+// off_k = beta t_k alone (evaluations outside a trajectory)
 __global__ void k_sub_offset(const double *__restrict__ ts, const int *__restrict__ pos,
                              const int *__restrict__ slot, int64_t m, double beta, double *__restrict__ off) {
     const int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -325,7 +373,8 @@ __global__ __launch_bounds__(256) void k_sub_theta(
     const int64_t *__restrict__ cidx, int64_t m, const int *__restrict__ pos, const double *__restrict__ ts,
     const double *__restrict__ xs, const double *__restrict__ ys, const PairConst kc, float *__restrict__ tv,
     double2 *__restrict__ sxy, double *__restrict__ sts, int *__restrict__ qwide, double *__restrict__ qstep,
-    double *__restrict__ theta_full, const double *__restrict__ theta_in, double *__restrict__ z_out) {
+    double *__restrict__ theta_full, const double *__restrict__ theta_in, double *__restrict__ z_out,
+    const SubStart st) {
     const int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     const int lane = threadIdx.x & (HK_WAVE - 1);
     const int64_t r0 = r - lane;  // the chunk's first entry
@@ -341,6 +390,16 @@ __global__ __launch_bounds__(256) void k_sub_theta(
         if (theta_in) {
             ze = log(theta_in[cidx[k]]);
             z_out[k] = ze;
+        } else if (st.on) {
+            const double zk = z[k];
+            st.z0[k] = zk;
+            st.p[k] = hmc_momentum(k, st.seed, st.counter, st.mass[k]);
+            ze = zk;
+            if (st.off) {
+                const double o = st.beta * t;
+                st.off[k] = o;
+                ze += o;
+            }
         } else {
             ze = zeff(z, off, k);
         }
@@ -861,142 +920,122 @@ __global__ void k_sub_scatter(const int *__restrict__ slot, int64_t m, const dou
     if (h_out) h_out[k] = hsub[r];
 }
 
-// Deterministic single-block sums over the subset (m is at most a few 1e4).
-// out[0] = sum log lambda (from block partials), out[1] = sum theta_k a_k,
-// out[2] = sum z_k^2 (or, with quad, the sum of its n_quad parts), out[3] = sum
-// p_k^2 / M_k; with loglik, Eq. 1 from them
-constexpr int ENERGY_THREADS = 1024;
-constexpr int ENERGY_BATCH = 4;
+// Sums over the subset in fixed order, one block per ENERGY_THREADS entries
+// (a block also takes its share of the chunks' sums of log lambda and of the
+// phylogenetic prior's parts): out[4 block ..] = sum log lambda (from block
+// partials), sum theta_k a_k, sum z_k^2 (or, with quad, the sum of its n_quad
+// parts), sum p_k^2 / M_k.  Each consumer adds the blocks' parts with
+// energy_sum.  (One block over everything took 4.7 us at 1,610 entries, 43 us at
+// 17,185; this form @@ENERGY@@.)
+constexpr int ENERGY_THREADS = 256;
 __global__ __launch_bounds__(ENERGY_THREADS) void k_sub_energy(const double *__restrict__ loglam_part, int nb,
-                                                    const double *__restrict__ z, const double *__restrict__ off,
-                                                    const double *__restrict__ p,
-                                                    const double *__restrict__ mass, const int *__restrict__ slot,
-                                                    const double *__restrict__ a, int64_t m,
-                                                    const double *__restrict__ quad, int n_quad,
-                                                    double *__restrict__ out, const double *__restrict__ Lam_static,
-                                                    double *__restrict__ loglik) {
-    __shared__ double sh[4][ENERGY_THREADS];
-    const int t = threadIdx.x;
+                                                               const double *__restrict__ z,
+                                                               const double *__restrict__ off,
+                                                               const double *__restrict__ p,
+                                                               const double *__restrict__ mass,
+                                                               const int *__restrict__ slot,
+                                                               const double *__restrict__ a, int64_t m,
+                                                               const double *__restrict__ quad, int n_quad,
+                                                               double *__restrict__ out) {
+    __shared__ double sh[4][ENERGY_THREADS / HK_WAVE];
+    const int t = threadIdx.x, all = gridDim.x * ENERGY_THREADS, first = blockIdx.x * ENERGY_THREADS + t;
     double s[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int b = t; b < nb; b += ENERGY_THREADS) s[0] += loglam_part[b];
-    for (int b = t; b < n_quad; b += ENERGY_THREADS) s[2] += quad[b];
-    // a thread's entries are gathered ENERGY_BATCH at a time (the loads through
-    // the slot issue together), then summed in entry order
-    for (int64_t base = t; base < m; base += (int64_t)ENERGY_BATCH * ENERGY_THREADS) {
-        int k[ENERGY_BATCH];
-        double zk[ENERGY_BATCH], ok[ENERGY_BATCH], pk[ENERGY_BATCH], mk[ENERGY_BATCH], ak[ENERGY_BATCH];
-#pragma unroll
-        for (int e = 0; e < ENERGY_BATCH; ++e) {
-            const int64_t r = base + (int64_t)e * ENERGY_THREADS;
-            k[e] = r < m ? slot[r] : 0;
-            ak[e] = r < m ? a[r] : 0.0;
-        }
-#pragma unroll
-        for (int e = 0; e < ENERGY_BATCH; ++e) {
-            const bool in = base + (int64_t)e * ENERGY_THREADS < m;
-            zk[e] = in ? z[k[e]] : 0.0;
-            ok[e] = in && off ? off[k[e]] : 0.0;
-            pk[e] = in && p ? p[k[e]] : 0.0;
-            mk[e] = in && p ? mass[k[e]] : 1.0;
-        }
-#pragma unroll
-        for (int e = 0; e < ENERGY_BATCH; ++e) {
-            if (base + (int64_t)e * ENERGY_THREADS >= m) break;
-            s[1] += exp(off ? zk[e] + ok[e] : zk[e]) * ak[e];
-            if (!quad) s[2] += zk[e] * zk[e];
-            if (p) s[3] += pk[e] * pk[e] / mk[e];
-        }
+#pragma unroll 4
+    for (int b = first; b < nb; b += all) s[0] += loglam_part[b];
+    for (int b = first; b < n_quad; b += all) s[2] += quad[b];
+    if (first < m) {
+        const int k = slot[first];
+        const double zk = z[k];
+        s[1] = exp(off ? zk + off[k] : zk) * a[first];
+        if (!quad) s[2] = zk * zk;
+        if (p) s[3] = p[k] * p[k] / mass[k];
     }
-    for (int q = 0; q < 4; ++q) sh[q][t] = s[q];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        for (int o = 32; o > 0; o >>= 1) s[q] += __shfl_xor(s[q], o);
+        if ((t & (HK_WAVE - 1)) == 0) sh[q][t / HK_WAVE] = s[q];
+    }
     __syncthreads();
-    for (int h = ENERGY_THREADS / 2; h > 0; h >>= 1) {
-        if (t < h)
-            for (int q = 0; q < 4; ++q) sh[q][t] += sh[q][t + h];
-        __syncthreads();
-    }
-    if (t < 4) out[t] = sh[t][0];
-    if (t == 0 && loglik) loglik[0] = sh[0][0] - Lam_static[0] - sh[1][0];
-}
-
-// ---- Philox-4x32-10 (Salmon et al. 2011) ------------------------------------------------
-__device__ __forceinline__ void philox10(uint32_t c[4], uint32_t k0, uint32_t k1) {
-    for (int r = 0; r < 10; ++r) {
-        if (r > 0) {
-            k0 += 0x9E3779B9u;
-            k1 += 0xBB67AE85u;
-        }
-        const uint64_t p0 = (uint64_t)0xD2511F53u * c[0];
-        const uint64_t p1 = (uint64_t)0xCD9E8D57u * c[2];
-        const uint32_t hi0 = (uint32_t)(p0 >> 32), lo0 = (uint32_t)p0;
-        const uint32_t hi1 = (uint32_t)(p1 >> 32), lo1 = (uint32_t)p1;
-        const uint32_t n0 = hi1 ^ c[1] ^ k0, n2 = hi0 ^ c[3] ^ k1;
-        c[0] = n0;
-        c[1] = lo1;
-        c[2] = n2;
-        c[3] = lo0;
+    if (t < 4) {
+        double v = sh[t][0];
+#pragma unroll
+        for (int w = 1; w < ENERGY_THREADS / HK_WAVE; ++w) v += sh[t][w];
+        out[4 * blockIdx.x + t] = v;
     }
 }
 
-__device__ __forceinline__ double u53(uint32_t a, uint32_t b) {
-    return ((double)(a >> 5) * 67108864.0 + (double)(b >> 6)) * (1.0 / 9007199254740992.0);
+// Sum q of k_sub_energy over its blocks, by one wavefront (every lane gets it).
+__device__ __forceinline__ double energy_sum(const double *__restrict__ parts, int blocks, int q) {
+    double v = 0.0;
+    for (int b = threadIdx.x & (HK_WAVE - 1); b < blocks; b += HK_WAVE) v += parts[4 * b + q];
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    return v;
 }
 
-// p_k = sqrt(M_k) N(0,1): element k uses counter (k, 0, counter_lo, counter_hi);
-// z0 <- z (start of the trajectory)
-__global__ void k_hmc_init(int64_t m, uint64_t seed, uint64_t counter, const double *__restrict__ mass,
-                           const double *__restrict__ z, double *__restrict__ p, double *__restrict__ z0) {
-    const int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (k >= m) return;
-    uint32_t c[4] = {(uint32_t)k, 0u, (uint32_t)counter, (uint32_t)(counter >> 32)};
-    philox10(c, (uint32_t)seed, (uint32_t)(seed >> 32));
-    const double u1 = u53(c[0], c[1]), u2 = u53(c[2], c[3]);
-    const double nrm = sqrt(-2.0 * log1p(-u1)) * cos(6.283185307179586 * u2);
-    p[k] = sqrt(mass[k]) * nrm;
-    z0[k] = z[k];
+__global__ __launch_bounds__(HK_WAVE) void k_sub_loglik(const double *__restrict__ parts, int blocks,
+                                                       const double *__restrict__ Lam_static,
+                                                       double *__restrict__ loglik) {
+    const double ll = energy_sum(parts, blocks, 0) - Lam_static[0] - energy_sum(parts, blocks, 1);
+    if (threadIdx.x == 0) loglik[0] = ll;
 }
 
-// Energies: scal[0..3] start sums, scal[4..7] end sums (k_sub_energy layout).
+// Accept or reject, every block deciding alike from the energies' parts (start,
+// end), and over the blocks: the proposal, z restored after a rejection, and
+// theta_full[idx_k] = exp(z_k + off_k).
 // H = -(sum log lambda - Lam_static - theta0-part) + sum z^2/(2 s^2) + sum p^2/(2M)
-__global__ void k_hmc_accept(const double *__restrict__ scal, const double *__restrict__ Lam_static,
-                             double inv_s2, uint64_t seed, uint64_t counter, int64_t m,
-                             const double *__restrict__ z0, double *__restrict__ z, double *__restrict__ z_prop,
-                             double *__restrict__ out, int *__restrict__ flag) {
+constexpr int ACCEPT_THREADS = 256;
+__global__ __launch_bounds__(ACCEPT_THREADS) void k_hmc_accept(const double *__restrict__ e0,
+                                                               const double *__restrict__ e1, int blocks,
+                                                               const double *__restrict__ Lam_static, double inv_s2,
+                                                               uint64_t seed, uint64_t counter, int64_t m,
+                                                               const double *__restrict__ z0, double *__restrict__ z,
+                                                               double *__restrict__ z_prop,
+                                                               const double *__restrict__ off,
+                                                               const int64_t *__restrict__ cidx,
+                                                               double *__restrict__ theta_full,
+                                                               double *__restrict__ out) {
+    __shared__ double sc[8];
     __shared__ int acc;
+    const int64_t k = blockIdx.x * (int64_t)ACCEPT_THREADS + threadIdx.x;
+    const double zk = k < m ? z[k] : 0.0, zs = k < m ? z0[k] : 0.0, ok = k < m && off ? off[k] : 0.0;
+    const int wq = threadIdx.x / HK_WAVE;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {  // a wavefront: two of the eight sums
+        const int j = 2 * wq + q;
+        const double v = energy_sum(j < 4 ? e0 : e1, blocks, j % 4);
+        if ((threadIdx.x & (HK_WAVE - 1)) == 0) sc[j] = v;
+    }
+    __syncthreads();
     if (threadIdx.x == 0) {
-        const double ll0 = scal[0] - Lam_static[0] - scal[1];
-        const double ll1 = scal[4] - Lam_static[0] - scal[5];
-        const double lp0 = ll0 - 0.5 * scal[2] * inv_s2;
-        const double lp1 = ll1 - 0.5 * scal[6] * inv_s2;
-        const double H0 = -lp0 + 0.5 * scal[3];
-        const double H1 = -lp1 + 0.5 * scal[7];
+        const double ll0 = sc[0] - Lam_static[0] - sc[1];
+        const double ll1 = sc[4] - Lam_static[0] - sc[5];
+        const double lp0 = ll0 - 0.5 * sc[2] * inv_s2;
+        const double lp1 = ll1 - 0.5 * sc[6] * inv_s2;
+        const double H0 = -lp0 + 0.5 * sc[3];
+        const double H1 = -lp1 + 0.5 * sc[7];
         const double dH = H1 - H0;
         uint32_t c[4] = {0u, 1u, (uint32_t)counter, (uint32_t)(counter >> 32)};
         philox10(c, (uint32_t)seed, (uint32_t)(seed >> 32));
         const double u = u53(c[0], c[1]);
         const int a = (isfinite(dH) && log(u) < -dH) ? 1 : 0;
         acc = a;
-        flag[0] = a;
-        out[0] = (double)a;
-        out[1] = dH;
-        out[2] = a ? ll1 : ll0;
-        out[3] = a ? lp1 : lp0;
-        out[4] = isfinite(dH) ? fmin(1.0, exp(-dH)) : 0.0;
-        out[5] = ll1;
-        out[6] = H0;
-        out[7] = H1;
+        if (blockIdx.x == 0) {
+            out[0] = (double)a;
+            out[1] = dH;
+            out[2] = a ? ll1 : ll0;
+            out[3] = a ? lp1 : lp0;
+            out[4] = isfinite(dH) ? fmin(1.0, exp(-dH)) : 0.0;
+            out[5] = ll1;
+            out[6] = H0;
+            out[7] = H1;
+        }
     }
     __syncthreads();
-    for (int64_t k = threadIdx.x; k < m; k += blockDim.x) {
-        if (z_prop) z_prop[k] = z[k];
-        if (!acc) z[k] = z0[k];
-    }
-}
-
-// theta_full[idx_k] = exp(z_k) (after a rejection restores z)
-__global__ void k_sub_theta_full(const double *__restrict__ z, const double *__restrict__ off,
-                                 const int64_t *__restrict__ cidx, int64_t m, double *__restrict__ theta_full) {
-    const int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (k < m) theta_full[cidx[k]] = exp(zeff(z, off, k));
+    if (k >= m) return;
+    if (z_prop) z_prop[k] = zk;
+    const double zf = acc ? zk : zs;
+    if (!acc) z[k] = zs;
+    theta_full[cidx[k]] = exp(off ? zf + ok : zf);
 }
 
 template <class T>
@@ -1012,7 +1051,7 @@ void hk_subset_free(hawkes_plan p) {
     hk_subset *s = p->sub;
     if (!s) return;
     void *ptrs[] = {s->pos, s->slot, s->cidx, s->ritems, s->ritem0, s->rnseg, s->xpart, s->items, s->item0, s->nseg,
-                    s->member, s->lam_static, s->Lam_static, s->a, s->tv, s->sxy, s->sts, s->qwide, s->qstep, s->lw, s->colG, s->gsub, s->hsub, s->sums, s->z0, s->p, s->off, s->vz, s->scal,
+                    s->member, s->lam_static, s->Lam_static, s->a, s->tv, s->sxy, s->sts, s->qwide, s->qstep, s->lw, s->colG, s->gsub, s->hsub, s->sums, s->z0, s->p, s->off, s->vz, s->scal, s->quad,
                     s->grid};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
@@ -1152,7 +1191,8 @@ extern "C" hawkes_status hawkes_plan_set_subset(hawkes_plan p, int64_t m, const 
     SC(dalloc(&s->p, m));
     SC(dalloc(&s->off, m));
     SC(dalloc(&s->vz, m));
-    SC(dalloc(&s->scal, 16));
+    SC(dalloc(&s->scal, 8 * (size_t)nblk(m, ENERGY_THREADS)));
+    SC(dalloc(&s->quad, 1));
 #undef SC
     s->static_valid = false;
     return HAWKES_OK;
@@ -1190,7 +1230,8 @@ enum SubFrom { SUB_FROM_Z, SUB_FROM_THETA, SUB_STAGED };
 // leapfrog update left): (theta,) lambda, w and the block partial sums of log
 // lambda in p->blockpart.
 static void sub_rows(hawkes_plan p, SubFrom from, double *z, const double *off, double *theta, const PairConst &kc,
-                     const FinConst &fc, hipStream_t stream, const TreeDense *tree = nullptr) {
+                     const FinConst &fc, hipStream_t stream, const TreeDense *tree = nullptr,
+                     const SubStart &start = SubStart{}) {
     hk_subset *s = p->sub;
     p->epoch += 1;  // p->lam is overwritten below
     if (from != SUB_STAGED)
@@ -1199,7 +1240,7 @@ static void sub_rows(hawkes_plan p, SubFrom from, double *z, const double *off, 
                            p->xs, p->ys, kc, s->tv, s->sxy, s->sts, s->qwide, s->qstep,
                            from == SUB_FROM_Z ? theta : (double *)nullptr,
                            from == SUB_FROM_THETA ? theta : (double *)nullptr,
-                           from == SUB_FROM_THETA ? z : (double *)nullptr);
+                           from == SUB_FROM_THETA ? z : (double *)nullptr, start);
 #define HK_SUBROWS(T, LOW, TOP, TD)                                                                                 \
     do {                                                                                                            \
         hipLaunchKernelGGL(k_sub_row<T>, dim3(s->n_ritems + (LOW)), dim3(HK_WAVE), 0, stream, p->ts, p->xs, p->ys,    \
@@ -1212,6 +1253,16 @@ static void sub_rows(hawkes_plan p, SubFrom from, double *z, const double *off, 
     if (tree) HK_SUBROWS(true, tree->R, hk_tree_top_blocks(tree->R), *tree);
     else HK_SUBROWS(false, 0, 0, TreeDense{});
 #undef HK_SUBROWS
+}
+
+// Eq. 1 after a row half at z.
+static void sub_loglik(hawkes_plan p, const double *z, const double *off, double *d_loglik, hipStream_t stream) {
+    hk_subset *s = p->sub;
+    const unsigned nb = nblk(s->m, ENERGY_THREADS);
+    hipLaunchKernelGGL(k_sub_energy, dim3(nb), dim3(ENERGY_THREADS), 0, stream, p->blockpart, p->nchunks, z, off,
+                       (const double *)nullptr, (const double *)nullptr, s->slot, s->a, s->m, (const double *)nullptr, 0,
+                       s->scal);
+    hipLaunchKernelGGL(k_sub_loglik, dim3(1), dim3(HK_WAVE), 0, stream, s->scal, (int)nb, s->Lam_static, d_loglik);
 }
 
 // The column half: Eq. 4 (and Eq. 5) on the subset, optionally with the fused
@@ -1293,10 +1344,7 @@ extern "C" hawkes_status hawkes_subset_grad(hawkes_plan p, const hawkes_hyper *h
         hipLaunchKernelGGL(k_sub_scatter, dim3(nblk(s->m, 256)), dim3(256), 0, stream, s->slot, s->m, s->gsub,
                            s->hsub, d_grad_sub, d_negH_sub);
     }
-    if (d_loglik)
-        hipLaunchKernelGGL(k_sub_energy, dim3(1), dim3(ENERGY_THREADS), 0, stream, p->blockpart, p->nchunks, s->z0,
-                           (const double *)nullptr, (const double *)nullptr, (const double *)nullptr, s->slot, s->a,
-                           s->m, (const double *)nullptr, 0, s->scal, s->Lam_static, d_loglik);
+    if (d_loglik) sub_loglik(p, s->z0, nullptr, d_loglik, stream);
     HK_CHECK(hipGetLastError());
     return HAWKES_OK;
 }
@@ -1320,27 +1368,26 @@ extern "C" hawkes_status hmc_step(hawkes_plan p, const hawkes_hyper *hyper, hawk
     const bool tree = a->prior == 1;
     const double *pv = tree ? s->vz : a->d_z;  // prior gradient direction (times 1/sigma^2)
     const double inv_s2 = 1.0 / (a->sigma_z * a->sigma_z);
-    const unsigned gb = nblk(m, 256);
     // temporal trend: log theta_k = z_k + beta t_k
-    const double *off = nullptr;
-    if (a->beta != 0.0) {
-        hipLaunchKernelGGL(k_sub_offset, dim3(gb), dim3(256), 0, stream, p->ts, s->pos, s->slot, m, a->beta, s->off);
-        off = s->off;
-    }
-    hipLaunchKernelGGL(k_hmc_init, dim3(gb), dim3(256), 0, stream, m, a->seed, a->counter, a->d_mass, a->d_z, s->p,
-                       s->z0);
+    const double *off = a->beta != 0.0 ? s->off : nullptr;
     // the phylogenetic prior at an evaluation's z: as extra blocks of its row half,
     // or, where its tree is too large for that, by a launch of its own
     const TreeDense *td = tree ? hk_tree_dense(p) : nullptr;
     const bool walk = tree && !td;
     // start of the trajectory: the energy at z0, then the gradient there and the
     // first half kick and drift (fused into the column finalisation)
-    sub_rows(p, SUB_FROM_Z, a->d_z, off, a->d_theta, kc, fc, stream, td);
+    const SubStart start{1, a->seed, a->counter, a->d_mass, s->p, s->z0, a->beta, a->beta != 0.0 ? s->off : nullptr};
+    sub_rows(p, SUB_FROM_Z, a->d_z, off, a->d_theta, kc, fc, stream, td, start);
     // (under the phylogenetic prior the quadratic form z^T V^{-1} z stands in for sum z^2)
-    hipLaunchKernelGGL(k_sub_energy, dim3(1), dim3(ENERGY_THREADS), 0, stream, p->blockpart, p->nchunks, a->d_z, off, s->p,
-                       a->d_mass, s->slot, s->a, m, td ? td->quad : nullptr, td ? td->R : 0, s->scal, s->Lam_static,
-                       (double *)nullptr);
-    if (walk && (st = hk_tree_launch(p, a->d_z, s->vz, s->scal + 2, stream)) != HAWKES_OK) return st;
+    const unsigned nb = nblk(m, ENERGY_THREADS);
+    double *e0 = s->scal, *e1 = s->scal + 4 * (size_t)nb;
+    const auto energy = [&](double *e) {
+        hipLaunchKernelGGL(k_sub_energy, dim3(nb), dim3(ENERGY_THREADS), 0, stream, p->blockpart, p->nchunks, a->d_z,
+                           off, s->p, a->d_mass, s->slot, s->a, m,
+                           td ? td->quad : walk ? s->quad : (const double *)nullptr, td ? td->R : walk ? 1 : 0, e);
+    };
+    if (walk && (st = hk_tree_launch(p, a->d_z, s->vz, s->quad, stream)) != HAWKES_OK) return st;
+    energy(e0);
     SubUpd upd{s->slot, a->d_z, off, pv, inv_s2, s->p, a->d_mass, 0.5 * a->eps, a->eps, s->tv, s->sts, s->qwide,
                kc.omega};
     sub_cols(p, false, kc, fc, &upd, stream);
@@ -1349,18 +1396,15 @@ extern "C" hawkes_status hmc_step(hawkes_plan p, const hawkes_hyper *hyper, hawk
         // closing half kick after the last one
         const bool last = l == a->L - 1;
         sub_rows(p, SUB_STAGED, a->d_z, off, a->d_theta, kc, fc, stream, td);
-        if (walk && (st = hk_tree_launch(p, a->d_z, s->vz, nullptr, stream)) != HAWKES_OK) return st;
+        if (walk && (st = hk_tree_launch(p, a->d_z, s->vz, s->quad, stream)) != HAWKES_OK) return st;
         upd.a_p = last ? 0.5 * a->eps : a->eps;
         upd.a_z = last ? 0.0 : a->eps;
         sub_cols(p, false, kc, fc, &upd, stream);
     }
-    hipLaunchKernelGGL(k_sub_energy, dim3(1), dim3(ENERGY_THREADS), 0, stream, p->blockpart, p->nchunks, a->d_z, off, s->p,
-                       a->d_mass, s->slot, s->a, m, td ? td->quad : nullptr, td ? td->R : 0, s->scal + 4, s->Lam_static,
-                       (double *)nullptr);
-    if (walk && (st = hk_tree_launch(p, a->d_z, nullptr, s->scal + 6, stream)) != HAWKES_OK) return st;
-    hipLaunchKernelGGL(k_hmc_accept, dim3(1), dim3(256), 0, stream, s->scal, s->Lam_static, inv_s2, a->seed,
-                       a->counter, m, s->z0, a->d_z, a->d_z_proposal, a->d_out, (int *)(s->scal + 8));
-    hipLaunchKernelGGL(k_sub_theta_full, dim3(gb), dim3(256), 0, stream, a->d_z, off, s->cidx, m, a->d_theta);
+    energy(e1);
+    hipLaunchKernelGGL(k_hmc_accept, dim3(nblk(m, ACCEPT_THREADS)), dim3(ACCEPT_THREADS), 0, stream, e0, e1, (int)nb,
+                       s->Lam_static, inv_s2, a->seed, a->counter, m, s->z0, a->d_z, a->d_z_proposal, off, s->cidx,
+                       a->d_theta, a->d_out);
     HK_CHECK(hipGetLastError());
     return HAWKES_OK;
 }
@@ -1390,10 +1434,7 @@ extern "C" hawkes_status hawkes_subset_trend_grad(hawkes_plan p, const hawkes_hy
         hipLaunchKernelGGL(k_sub_trend_out, dim3(1), dim3(256), 0, stream, s->slot, s->pos, p->ts, s->m, s->gsub, d_z,
                            off, d_grad_z, d_grad_beta);
     }
-    if (d_loglik)
-        hipLaunchKernelGGL(k_sub_energy, dim3(1), dim3(ENERGY_THREADS), 0, stream, p->blockpart, p->nchunks, d_z, off,
-                           (const double *)nullptr, (const double *)nullptr, s->slot, s->a, s->m, (const double *)nullptr, 0,
-                           s->scal, s->Lam_static, d_loglik);
+    if (d_loglik) sub_loglik(p, d_z, off, d_loglik, stream);
     HK_CHECK(hipGetLastError());
     return HAWKES_OK;
 }

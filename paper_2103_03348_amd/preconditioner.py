@@ -88,16 +88,31 @@ class LearnedPreconditioner:
         X = X.contiguous()
         T = T.contiguous()
         hist = []
-        # every step's batch rows drawn up front and copied once
-        all_rows = torch.as_tensor(rng.integers(0, n, size=(steps, B)).astype(np.int32), device=self.dev)
+        # The arguments that stay the same are marshalled once.  The batch rows are
+        # drawn block by block beside the GPU's steps, through two pinned buffers in
+        # turn (all drawn and copied before the first step, they were a quarter of
+        # the time: 100 steps of batch 4,096 2,290 -> 2,000 us).
+        step_fn, stream = _lib.lib().hawkes_mlp_train_step, _lib.stream_handle()
+        state = (_lib.ptr(self.params), _lib.ptr(self.adam_m), _lib.ptr(self.adam_v))
+        data = (_lib.ptr(T), B, _lib.ptr(work), _lib.ptr(grad), _lib.ptr(loss), _lib.ptr(err), stream)
+        rate, xp, block = ctypes.c_float(lr), _lib.ptr(X), min(steps, 32)
+        pinned = [torch.empty((block, B), dtype=torch.int32, pin_memory=True) for _ in range(2)]
+        copied = [torch.cuda.Event() for _ in range(2)]
+        rows = torch.empty((steps, B), dtype=torch.int32, device=self.dev)
+        drawn = 0
         for it in range(steps):
-            rows = all_rows[it]
+            if it == drawn:
+                k = min(block, steps - it, max(4, it))
+                buf, ev = pinned[0], copied[0]
+                pinned.reverse()
+                copied.reverse()
+                ev.synchronize()  # the copy out of this buffer, two blocks ago
+                buf.numpy()[:k] = rng.integers(0, n, size=(k, B), dtype=np.int32)
+                rows[it:it + k].copy_(buf[:k], non_blocking=True)
+                ev.record()
+                drawn, p0 = it + k, rows.data_ptr()
             self.step_no += 1
-            _lib.check(_lib.lib().hawkes_mlp_train_step(_lib.ptr(self.params), _lib.ptr(self.adam_m),
-                                                        _lib.ptr(self.adam_v), self.step_no, ctypes.c_float(lr),
-                                                        _lib.ptr(X), n, _lib.ptr(rows), _lib.ptr(T), B,
-                                                        _lib.ptr(work), _lib.ptr(grad), _lib.ptr(loss),
-                                                        _lib.ptr(err), _lib.stream_handle()),
+            _lib.check(step_fn(*state, self.step_no, rate, xp, n, ctypes.c_void_p(p0 + 4 * B * it), *data),
                        "hawkes_mlp_train_step")
             if log_every and (it % log_every == 0 or it == steps - 1):
                 hist.append((it, float(loss.item())))
