@@ -17,10 +17,11 @@
 //   k_sub_offset   temporal-trend offsets beta t_k (Sec. 2.2)
 //   k_sub_theta    theta_k = exp(z_k + beta t_k) into the caller's theta, and the
 //                  subset entries staged in time order for the subset passes
-//   k_sub_row      X_i = sum_{k in M, t_k < t_i} theta_k E_ik (rows = all events),
-//                  one-wavefront items with partial sums
+//   k_sub_items    X_i = sum_{k in M, t_k < t_i} theta_k E_ik (rows = all events),
+//                  one-wavefront items with partial sums; then
 //   k_sub_fin      lambda_i, block sums of log lambda_i, and the column
 //                  pass's row weights log2(c_e / lambda_i)
+//   k_sub_block    both in one launch, on small sets
 //   k_sub_col      G_k = sum_{t_i > t_k} E_ik w_i, H_k = sum (E_ik w_i)^2, items
 //   k_sub_colfin   Eq. 4 / Eq. 5 on the subset; inside hmc_step also the
 //                  leapfrog's gradient in z, kick and drift
@@ -43,7 +44,9 @@ struct hk_subset {
     int *slot;           // [mpad] caller's subset slot k of entry r
     int64_t *cidx;       // [m] caller index of slot k (copy of the caller's idx)
     unsigned char *member;  // [npad] 1 where the sorted event is in the subset
-    // row pass schedule: (row chunk, range of subset entries before its end)
+    int *cnt;            // [nchunks] subset entries before each row chunk's end (a prefix)
+    // row pass schedule of larger sets (n_ritems = 0: a block per row chunk instead):
+    // (row chunk, range of subset entries before its end)
     int n_ritems;
     hk_item *ritems;     // (row chunk, entry begin, entry end, seg)
     int *ritem0, *rnseg; // per row chunk
@@ -66,7 +69,7 @@ struct hk_subset {
     double *sts;         // [mpad] times
     int *qwide;          // [nq] 1 where the 64-entry chunk q spans more than HK_SUB_FACT_SPAN / omega
     double *qstep;       // [nq] exp(-omega (T_{q+1} - T_q)), T_q the time of chunk q's first entry
-    // the subset column pass's row weights, written by k_sub_fin
+    // the subset column pass's row weights, written by the row half
     double *lw;          // [npad] log2(c_e / lambda_i) (HK_EXP_FLOOR on padding)
     double *colG;        // [n_items][2][HK_WAVE]
     double *gsub;        // [mpad] Eq. 4 on the subset, time order
@@ -110,11 +113,18 @@ constexpr int SUB_FIN_WAVES = HK_SUB_FIN_WAVES;
 // partial-sum loads a finalisation wavefront keeps in flight (16 in the
 // column finalisation measured slower: 4.95 -> 5.7 us at N = 23,422)
 constexpr int SUB_FIN_BATCH = 8;
-// wavefronts per row chunk in the subset row finalisation
+// wavefronts per row chunk in the row finalisation of the items
 #ifndef HK_SUB_ROWFIN_WAVES
 #define HK_SUB_ROWFIN_WAVES 4
 #endif
 constexpr int SUB_ROWFIN_WAVES = HK_SUB_ROWFIN_WAVES;
+// block form of the row pass: wavefronts per block (one row chunk), entries per
+// staged unit, and the most one-wavefront items for which it is taken: up to
+// about one per SIMD the items are latency and a second launch (HMC iteration,
+// items / blocks: N = 3,000, 100 items, 368 / 292 us; 8,000, 560 items, 374 / 357;
+// 23,422, 4,850 items, 614 / 635)
+constexpr int SUB_ROW_WAVES = 12, SUB_UNIT = 16;
+constexpr int64_t SUB_BLOCK_ITEMS = 1024;
 constexpr int64_t SUB_ITEM_BATCHES = 8;
 // unroll of the subset sweeps: 8 measured fastest (114 VGPRs, 4 wavefronts per
 // SIMD); shorter loops fit more wavefronts but lose more instruction-level
@@ -437,13 +447,13 @@ __device__ __forceinline__ float sub_exp2_split(double e) {
     return __builtin_amdgcn_ldexpf(fexp2((float)(e - n)), (int)n);
 }
 
-template <bool MASKED, bool FACT>
+template <int N, bool MASKED, bool FACT>
 __device__ __forceinline__ void sub_row_sweep(const double2 *__restrict__ rxy, const float *__restrict__ rv,
                                               const double *__restrict__ rtd, const int *__restrict__ rpos,
                                               double tsi, double xr, double yr, int gr, const PairConst kc,
                                               double &acc) {
 #pragma unroll kSubUnroll
-    for (int s = 0; s < HK_WAVE; ++s) {
+    for (int s = 0; s < N; ++s) {
         const double2 pk = rxy[s];
         const double dx = xr - pk.x, dy = yr - pk.y;
         const double aed = -fma(dx, dx, dy * dy);
@@ -460,7 +470,7 @@ __device__ __forceinline__ void sub_row_sweep(const double2 *__restrict__ rxy, c
 // to the item's slot.  With TREE, the first blocks take the phylogenetic prior's
 // low step at the same z, one subtree each.
 template <bool TREE>
-__global__ __launch_bounds__(HK_WAVE) void k_sub_row(
+__global__ __launch_bounds__(HK_WAVE) void k_sub_items(
     const double *__restrict__ ts, const double *__restrict__ xs, const double *__restrict__ ys, const int *__restrict__ g,
     const int *__restrict__ pos, const float *__restrict__ tv, const double2 *__restrict__ sxy,
     const double *__restrict__ sts, const int *__restrict__ qwide, const double *__restrict__ qstep,
@@ -539,11 +549,11 @@ __global__ __launch_bounds__(HK_WAVE) void k_sub_row(
         // a batch whose entries all precede the chunk's first tie group needs no
         // causality mask (padding entries carry rate 0)
         if (rpos[cend - 1 - c0] < g_first) {
-            if (fact) sub_row_sweep<false, true>(rxy, rv, rtd, rpos, tsi, xr, yr, gr, kc, accb);
-            else sub_row_sweep<false, false>(rxy, rv, rtd, rpos, tsi, xr, yr, gr, kc, accb);
+            if (fact) sub_row_sweep<HK_WAVE, false, true>(rxy, rv, rtd, rpos, tsi, xr, yr, gr, kc, accb);
+            else sub_row_sweep<HK_WAVE, false, false>(rxy, rv, rtd, rpos, tsi, xr, yr, gr, kc, accb);
         } else {
-            if (fact) sub_row_sweep<true, true>(rxy, rv, rtd, rpos, tsi, xr, yr, gr, kc, accb);
-            else sub_row_sweep<true, false>(rxy, rv, rtd, rpos, tsi, xr, yr, gr, kc, accb);
+            if (fact) sub_row_sweep<HK_WAVE, true, true>(rxy, rv, rtd, rpos, tsi, xr, yr, gr, kc, accb);
+            else sub_row_sweep<HK_WAVE, true, false>(rxy, rv, rtd, rpos, tsi, xr, yr, gr, kc, accb);
         }
         if (accb != 0.0) {
             if (fact) {
@@ -561,40 +571,84 @@ __global__ __launch_bounds__(HK_WAVE) void k_sub_row(
     xpart[(int64_t)item * HK_WAVE + lane] = acc;
 }
 
-// One block per 64-row chunk.  Its SUB_ROWFIN_WAVES wavefronts split the
-// chunk's row items (late chunks have the most, one per run of subset sources
-// before them) and combine their partial sums in a fixed order, so that the
-// partial-sum reads are in flight together; wavefront 0 then finalises the
-// rows.  The chunk's sum of log lambda goes to blockpart[chunk], and the
-// subset column pass's weight w_i = c_e / lambda_i to lw as its log2 (FP64).
-//
-// With TREE, the first blocks take the phylogenetic prior's top step at the same z
-// (its low step rode on the row pass).
-template <bool TREE>
-__global__ __launch_bounds__(SUB_ROWFIN_WAVES * HK_WAVE) void k_sub_fin(const double *__restrict__ lam_static,
-                                                 const int *__restrict__ ritem0, const int *__restrict__ rnseg,
-                                                 const double *__restrict__ xpart, const double *__restrict__ ts,
-                                                 const double *__restrict__ xs, const double *__restrict__ ys,
-                                                 const int *__restrict__ g, const int *__restrict__ pos,
-                                                 const float *__restrict__ tv, const double *__restrict__ sts,
-                                                 const int *__restrict__ qwide, int64_t m,
-                                                 int64_t n, int64_t npad, const FinConst fc,
-                                                 double *__restrict__ lam, double *__restrict__ lw,
-                                                 double *__restrict__ blockpart, int *__restrict__ status,
-                                                 const TreeDense tree, double *__restrict__ vz) {
-    const int first = TREE ? hk_tree_top_blocks(tree.R) : 0;
-    if (TREE) {
-        static_assert(SUB_ROWFIN_WAVES * HK_WAVE == HK_TREE_TOP_THREADS, "threads of the prior's blocks");
-        if ((int)blockIdx.x < first) {
-            hk_tree_top(tree, blockIdx.x, vz);
-            return;
+// The end of a row chunk's evaluation, by a block of WAVES wavefronts that all
+// hold the rows' subset excitation x (in units of the FP32 sums) and static part:
+// lambda_i, the chunk's sum of log lambda (blockpart[chunk]) and the column pass's
+// weight w_i = c_e / lambda_i as its log2 (FP64).
+template <int WAVES>
+__device__ __forceinline__ void sub_finish_rows(const double *__restrict__ ts, const double *__restrict__ xs,
+                                                const double *__restrict__ ys, const int *__restrict__ g,
+                                                const int *__restrict__ pos, const float *__restrict__ tv,
+                                                const double *__restrict__ sts, const int *__restrict__ qwide,
+                                                int64_t m, int64_t n, const FinConst &fc, int b, int lane, int wq,
+                                                double lst, double x, double *__restrict__ lam,
+                                                double *__restrict__ lw, double *__restrict__ blockpart,
+                                                int *__restrict__ status) {
+    const int64_t i0 = (int64_t)b * HK_WAVE, i = i0 + lane;
+    // rows whose intensity is below fc.lam_exact (the FP32 terms may have lost
+    // more than 2^-30 of it) take the subset excitation from the definitions
+    // in FP64, the whole block on one row at a time; every wavefront derives
+    // the same mask
+    __shared__ double xred[WAVES];
+    __shared__ double xexact[HK_WAVE];
+    const bool low = i < n && lst + fc.c_e * fc.corr * x < fc.lam_exact;
+    for (uint64_t mk = __ballot(low); mk != 0; mk &= mk - 1) {
+        const int rr = __ffsll((unsigned long long)mk) - 1;
+        const int64_t ir = i0 + rr;
+        const double xi = xs[ir], yi = ys[ir], ti = ts[ir];
+        const int gi = g[ir];
+        const double kh = 0.5 / (fc.h * fc.h);
+        double xs_sum = 0.0;
+        for (int64_t r = threadIdx.x; r < m; r += WAVES * HK_WAVE) {
+            const int pk = pos[r];
+            if (pk >= gi) continue;  // entries are in time order; only earlier events excite
+            const double dx = xi - xs[pk], dy = yi - ys[pk];
+            const double r2 = dx * dx + dy * dy;
+            // tv carries theta_r exp(omega (t_r - T_q)) on a split chunk q
+            const int64_t qr = r / HK_WAVE;
+            const double tq = qwide[qr] ? sts[r] : sts[qr * HK_WAVE];
+            xs_sum += (double)tv[r] * exp(-fc.omega * (ti - tq) - r2 * kh);
         }
+        for (int off = 32; off > 0; off >>= 1) xs_sum += __shfl_xor(xs_sum, off);
+        if (lane == 0) xred[wq] = xs_sum;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double v = xred[0];
+            for (int w = 1; w < WAVES; ++w) v += xred[w];
+            xexact[rr] = v;
+        }
+        __syncthreads();
     }
+    if (wq != 0) return;
+    double v = 0.0;
+    if (i < n) {
+        const double l = low ? lst + fc.c_e * xexact[lane] : lst + fc.c_e * fc.corr * x;
+        lam[i] = l;
+        if (!(l > 0.0)) atomicOr(status, isnan(l) ? HK_ST_NONFINITE : HK_ST_ZERO);
+        v = log(l);
+        lw[i] = l > 0.0 ? fmax(fc.log2_ce - v * 1.4426950408889634, HK_EXP_FLOOR) : HK_EXP_FLOOR;
+    } else {
+        lam[i] = 1.0;
+        lw[i] = HK_EXP_FLOOR;
+    }
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    if (lane == 0) blockpart[b] = v;
+}
+
+// Finalisation of the items, one block per 64-row chunk.  Its SUB_ROWFIN_WAVES
+// wavefronts split the chunk's row items (late chunks have the most, one per run
+// of subset sources before them) and combine their partial sums in a fixed
+// order, so that the partial-sum reads are in flight together.
+__global__ __launch_bounds__(SUB_ROWFIN_WAVES * HK_WAVE) void k_sub_fin(
+    const double *__restrict__ lam_static, const int *__restrict__ ritem0, const int *__restrict__ rnseg,
+    const double *__restrict__ xpart, const double *__restrict__ ts, const double *__restrict__ xs,
+    const double *__restrict__ ys, const int *__restrict__ g, const int *__restrict__ pos, const float *__restrict__ tv,
+    const double *__restrict__ sts, const int *__restrict__ qwide, int64_t m, int64_t n, const FinConst fc,
+    double *__restrict__ lam, double *__restrict__ lw, double *__restrict__ blockpart, int *__restrict__ status) {
     __shared__ double part[SUB_ROWFIN_WAVES][HK_WAVE];
-    const int b = (int)blockIdx.x - first, lane = threadIdx.x & (HK_WAVE - 1);
+    const int b = blockIdx.x, lane = threadIdx.x & (HK_WAVE - 1);
     const int wq = __builtin_amdgcn_readfirstlane(threadIdx.x / HK_WAVE);
-    const int64_t i0 = (int64_t)b * HK_WAVE;  // the chunk's first event
-    const int64_t i = i0 + lane;
+    const int64_t i = (int64_t)b * HK_WAVE + lane;
     // the static part is fetched before the reduction, so that its latency
     // overlaps the partial-sum reads
     double lst = 0.0;
@@ -623,54 +677,142 @@ __global__ __launch_bounds__(SUB_ROWFIN_WAVES * HK_WAVE) void k_sub_fin(const do
     double x = part[0][lane];
 #pragma unroll
     for (int k = 1; k < SUB_ROWFIN_WAVES; ++k) x += part[k][lane];
-    // rows whose intensity is below fc.lam_exact (the FP32 terms may have lost
-    // more than 2^-30 of it) take the subset excitation from the definitions
-    // in FP64, the whole block on one row at a time; every wavefront derives
-    // the same mask
-    __shared__ double xred[SUB_ROWFIN_WAVES];
-    __shared__ double xexact[HK_WAVE];
-    const bool low = i < n && lst + fc.c_e * fc.corr * x < fc.lam_exact;
-    for (uint64_t mk = __ballot(low); mk != 0; mk &= mk - 1) {
-        const int rr = __ffsll((unsigned long long)mk) - 1;
-        const int64_t ir = i0 + rr;
-        const double xi = xs[ir], yi = ys[ir], ti = ts[ir];
-        const int gi = g[ir];
-        const double kh = 0.5 / (fc.h * fc.h);
-        double xs_sum = 0.0;
-        for (int64_t r = threadIdx.x; r < m; r += SUB_ROWFIN_WAVES * HK_WAVE) {
-            const int pk = pos[r];
-            if (pk >= gi) continue;  // entries are in time order; only earlier events excite
-            const double dx = xi - xs[pk], dy = yi - ys[pk];
-            const double r2 = dx * dx + dy * dy;
-            // tv carries theta_r exp(omega (t_r - T_q)) on a split chunk q
-            const int64_t q = r / HK_WAVE;
-            const double tq = qwide[q] ? sts[r] : sts[q * HK_WAVE];
-            xs_sum += (double)tv[r] * exp(-fc.omega * (ti - tq) - r2 * kh);
-        }
-        for (int off = 32; off > 0; off >>= 1) xs_sum += __shfl_xor(xs_sum, off);
-        if (lane == 0) xred[wq] = xs_sum;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double v = xred[0];
-            for (int k = 1; k < SUB_ROWFIN_WAVES; ++k) v += xred[k];
-            xexact[rr] = v;
-        }
-        __syncthreads();
+    sub_finish_rows<SUB_ROWFIN_WAVES>(ts, xs, ys, g, pos, tv, sts, qwide, m, n, fc, b, lane, wq, lst, x, lam, lw,
+                                      blockpart, status);
+}
+
+// orders a wavefront's own LDS writes and reads (its LDS instructions execute in
+// order: only the compiler has to keep them so)
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+struct SubRowLds {  // one wavefront's staged entries
+    double2 xy[SUB_UNIT];
+    double t[SUB_UNIT];
+    float v[SUB_UNIT];
+    int pos[SUB_UNIT];
+};
+
+// Row pass and its finalisation, one block per 64-row chunk.  The entries before
+// the chunk's end (a prefix in time order) are cut into units of SUB_UNIT, and
+// the block's wavefronts take equal runs of units, each staging its own through
+// LDS; a run is walked from late to early, so that the row's split factor
+// exp(-omega (t_i - T_q)) is evaluated at the run's first entry chunk with a
+// causal pair (where it is at most 1) and carried down by the chunks' step
+// factors.  The runs' sums are combined in a fixed order, and the first
+// wavefront finishes the rows: lambda_i, the chunk's sum of log lambda
+// (blockpart[chunk]) and the column pass's weight w_i = c_e / lambda_i as its
+// log2 (FP64).
+//
+// What bounds small sets is latency: a wavefront's pairs are a microsecond or two
+// of issue behind three dependent loads, and the items' two launches took 9.2 us
+// at N = 3,000 (M = 206), this form 6.2.  Where the items fill the chip it loses:
+// blocks of many wavefronts even out worse than single ones (N = 23,422, M =
+// 1,610: 15.0 us against 15.4 in two launches that overlap at their ends).
+//
+// With TREE, the first blocks take the phylogenetic prior's low step at the same z.
+template <bool TREE>
+__global__ __launch_bounds__(SUB_ROW_WAVES * HK_WAVE) void k_sub_block(
+    const double *__restrict__ ts, const double *__restrict__ xs, const double *__restrict__ ys, const int *__restrict__ g,
+    const int *__restrict__ pos, const float *__restrict__ tv, const double2 *__restrict__ sxy,
+    const double *__restrict__ sts, const int *__restrict__ qwide, const double *__restrict__ qstep,
+    const int *__restrict__ cnt, int nch, const double *__restrict__ lam_static, int64_t m, int64_t n,
+    const PairConst kc, const FinConst fc, double *__restrict__ lam, double *__restrict__ lw,
+    double *__restrict__ blockpart, int *__restrict__ status, const TreeDense tree, const double *__restrict__ z) {
+    const int lane = threadIdx.x & (HK_WAVE - 1), wq = __builtin_amdgcn_readfirstlane(threadIdx.x / HK_WAVE);
+    const int low_blocks = TREE ? (tree.R + SUB_ROW_WAVES - 1) / SUB_ROW_WAVES : 0;
+    if (TREE && (int)blockIdx.x < low_blocks) {
+        const int r = (int)blockIdx.x * SUB_ROW_WAVES + wq;
+        if (r < tree.R) hk_tree_low(tree, z, r);
+        return;
     }
-    if (wq != 0) return;
-    double v = 0.0;
-    if (i < n) {
-        const double l = low ? lst + fc.c_e * xexact[lane] : lst + fc.c_e * fc.corr * x;
-        lam[i] = l;
-        if (!(l > 0.0)) atomicOr(status, isnan(l) ? HK_ST_NONFINITE : HK_ST_ZERO);
-        v = log(l);
-        lw[i] = l > 0.0 ? fmax(fc.log2_ce - v * 1.4426950408889634, HK_EXP_FLOOR) : HK_EXP_FLOOR;
-    } else {
-        lam[i] = 1.0;
-        lw[i] = HK_EXP_FLOOR;
+    __shared__ SubRowLds Ls[SUB_ROW_WAVES];
+    __shared__ double part[SUB_ROW_WAVES][HK_WAVE];
+    const int k = (int)blockIdx.x - low_blocks;
+    const int b = nch - 1 - k;  // the chunks of the most entries first
+    const int64_t i0 = (int64_t)b * HK_WAVE;  // the chunk's first event
+    const int64_t i = i0 + lane;
+    const int c_end = cnt[b], units = (c_end + SUB_UNIT - 1) / SUB_UNIT;
+    const int u0 = units * wq / SUB_ROW_WAVES, u1 = units * (wq + 1) / SUB_ROW_WAVES;
+    const double lst = i < n ? lam_static[i] : 0.0;
+    double x = 0.0;  // every term in FP64 (see the row pass: FP32 sums drop small terms)
+    if (u1 > u0) {
+        SubRowLds &L = Ls[wq];  // the wavefront's own
+        // a unit is loaded into registers one unit ahead (the subset arrays are padded
+        // to whole 256-entry tiles: every load is in bounds)
+        double2 nxy = make_double2(0.0, 0.0);
+        float nv = 0.0f;
+        double nt = 0.0;
+        int np = 0;
+        const auto fetch = [&](int u) {
+            if (lane < SUB_UNIT) {
+                const int e = u * SUB_UNIT + lane;
+                nxy = sxy[e];
+                nv = tv[e];
+                nt = sts[e];
+                np = pos[e];
+            }
+        };
+        fetch(u1 - 1);
+        const double tsi = ts[i], xr = xs[i] * kc.sx, yr = ys[i] * kc.sx;
+        const int gr = g[i];
+        const double chunk_tmin = ts[i0];
+        const int g_first = g[i0];  // g is non-decreasing
+        double ui = 0.0, accq = 0.0;
+        bool have_ui = false;
+        int q = (u1 - 1) / (HK_WAVE / SUB_UNIT);
+        bool fact = qwide[q] == 0;
+        const auto fold = [&]() {  // the entry chunk's sum, with the row's split factor
+            if (accq == 0.0) return;
+            if (fact && !have_ui) {
+                ui = exp(-kc.omega * (tsi - sts[(int64_t)q * HK_WAVE]));
+                have_ui = true;
+            }
+            x += fact ? ui * accq : accq;
+            accq = 0.0;
+        };
+        for (int u = u1 - 1; u >= u0; --u) {
+            // under the cutoff a unit whose last entry precedes the chunk's first row
+            // by more than dt_cut_ex, and all the earlier ones, add nothing (entries
+            // are in time order)
+            if (kc.dt_cut_ex < INFINITY && chunk_tmin - sts[min((u + 1) * SUB_UNIT, c_end) - 1] > kc.dt_cut_ex) break;
+            const int qu = u / (HK_WAVE / SUB_UNIT);
+            if (qu != q) {
+                fold();
+                q = qu;
+                if (have_ui) ui *= qstep[q];
+                fact = qwide[q] == 0;
+            }
+            if (lane < SUB_UNIT) {
+                L.xy[lane] = nxy;
+                L.t[lane] = nt;
+                L.v[lane] = nv;
+                L.pos[lane] = np;
+            }
+            if (u > u0) fetch(u - 1);
+            wave_sync();
+            // a unit whose entries all precede the chunk's first tie group needs no
+            // causality mask (entries past the prefix and padding follow every row)
+            if (L.pos[SUB_UNIT - 1] < g_first) {
+                if (fact) sub_row_sweep<SUB_UNIT, false, true>(L.xy, L.v, L.t, L.pos, tsi, xr, yr, gr, kc, accq);
+                else sub_row_sweep<SUB_UNIT, false, false>(L.xy, L.v, L.t, L.pos, tsi, xr, yr, gr, kc, accq);
+            } else {
+                if (fact) sub_row_sweep<SUB_UNIT, true, true>(L.xy, L.v, L.t, L.pos, tsi, xr, yr, gr, kc, accq);
+                else sub_row_sweep<SUB_UNIT, true, false>(L.xy, L.v, L.t, L.pos, tsi, xr, yr, gr, kc, accq);
+            }
+            wave_sync();
+        }
+        fold();
     }
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    if (lane == 0) blockpart[b] = v;
+    part[wq][lane] = x;
+    __syncthreads();
+    x = part[0][lane];
+#pragma unroll
+    for (int w = 1; w < SUB_ROW_WAVES; ++w) x += part[w][lane];
+    sub_finish_rows<SUB_ROW_WAVES>(ts, xs, ys, g, pos, tv, sts, qwide, m, n, fc, b, lane, wq, lst, x, lam, lw, blockpart,
+                                   status);
 }
 
 // Column pass on the subset: lanes own subset entries (time order), rows are
@@ -713,17 +855,24 @@ __device__ __forceinline__ void sub_col_sweep(const SubColRow *__restrict__ rows
 
 // One item: a chunk of 64 subset entries (the lanes) against a range of row
 // chunks after them; the entries' partial sums go to the item's slot.  Times
-// enter relative to the subset chunk's first entry.
+// enter relative to the subset chunk's first entry.  The first `tops` blocks take
+// the phylogenetic prior's top step (its low step rode on the row pass).
 template <bool WITH_H, bool DOT>
 __global__ __launch_bounds__(HK_WAVE) void k_sub_col(const double *__restrict__ ts, const double *__restrict__ xs,
                                                       const double *__restrict__ ys, const double *__restrict__ lw,
                                                       const int *__restrict__ g, const int *__restrict__ pos,
                                                       const double2 *__restrict__ sxy, const double *__restrict__ sts,
                                                       int64_t m, const hk_item *__restrict__ items,
-                                                      const PairConst kc, double *__restrict__ colG) {
+                                                      const PairConst kc, double *__restrict__ colG, int tops,
+                                                      const TreeDense tree, double *__restrict__ vz) {
+    if ((int)blockIdx.x < tops) {
+        hk_tree_top(tree, blockIdx.x, vz);
+        return;
+    }
     __shared__ SubColRow rows[HK_WAVE];
     __shared__ int rg[HK_WAVE];
-    const hk_item it = items[blockIdx.x];
+    const int item = (int)blockIdx.x - tops;
+    const hk_item it = items[item];
     const int lane = threadIdx.x;
     const int64_t q0 = (int64_t)it.tile * HK_WAVE;
     const int64_t r = q0 + lane;
@@ -807,7 +956,7 @@ __global__ __launch_bounds__(HK_WAVE) void k_sub_col(const double *__restrict__ 
         if (WITH_H) Hd += (double)H;
         __syncthreads();
     }
-    double *cg = colG + (int64_t)blockIdx.x * 2 * HK_WAVE;
+    double *cg = colG + (int64_t)item * 2 * HK_WAVE;
     cg[lane] = live ? Gd : 0.0;
     if (WITH_H) cg[HK_WAVE + lane] = live ? Hd : 0.0;
 }
@@ -926,7 +1075,7 @@ __global__ void k_sub_scatter(const int *__restrict__ slot, int64_t m, const dou
 // partials), sum theta_k a_k, sum z_k^2 (or, with quad, the sum of its n_quad
 // parts), sum p_k^2 / M_k.  Each consumer adds the blocks' parts with
 // energy_sum.  (One block over everything took 4.7 us at 1,610 entries, 43 us at
-// 17,185; this form @@ENERGY@@.)
+// 17,185; this form 3.6 and 4.8.)
 constexpr int ENERGY_THREADS = 256;
 __global__ __launch_bounds__(ENERGY_THREADS) void k_sub_energy(const double *__restrict__ loglam_part, int nb,
                                                                const double *__restrict__ z,
@@ -1050,7 +1199,7 @@ inline unsigned nblk(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
 void hk_subset_free(hawkes_plan p) {
     hk_subset *s = p->sub;
     if (!s) return;
-    void *ptrs[] = {s->pos, s->slot, s->cidx, s->ritems, s->ritem0, s->rnseg, s->xpart, s->items, s->item0, s->nseg,
+    void *ptrs[] = {s->pos, s->slot, s->cidx, s->cnt, s->ritems, s->ritem0, s->rnseg, s->xpart, s->items, s->item0, s->nseg,
                     s->member, s->lam_static, s->Lam_static, s->a, s->tv, s->sxy, s->sts, s->qwide, s->qstep, s->lw, s->colG, s->gsub, s->hsub, s->sums, s->z0, s->p, s->off, s->vz, s->scal, s->quad,
                     s->grid};
     for (void *q : ptrs)
@@ -1115,8 +1264,8 @@ extern "C" hawkes_status hawkes_plan_set_subset(hawkes_plan p, int64_t m, const 
     // (the positions are valid: an index out of range or repeated was refused above)
     hipLaunchKernelGGL(k_sub_member, dim3(nblk(m, 256)), dim3(256), 0, stream, s->pos, m, s->member);
     SC(hipGetLastError());
-    // row pass schedule: row chunk b pairs with the subset entries before its end
-    // (cnt_b of them, a prefix in time order), in items of at most BR entries
+    // row chunk b pairs with the subset entries before its end (cnt_b of them, a
+    // prefix in time order)
     const int nch = p->nchunks;
     std::vector<int> cnt(nch);
     {
@@ -1126,14 +1275,19 @@ extern "C" hawkes_status hawkes_plan_set_subset(hawkes_plan p, int64_t m, const 
             cnt[b] = (int)r;
         }
     }
-    int64_t wrow = 0;
-    for (int b = 0; b < nch; ++b) wrow += cnt[b];
+    // row pass schedule: items of at most BR entries, unless there are few (the
+    // block form then needs none)
+    int64_t wrow = 0, batches = 0;
+    for (int b = 0; b < nch; ++b) {
+        wrow += cnt[b];
+        batches += (cnt[b] + HK_WAVE - 1) / HK_WAVE;
+    }
     const int64_t br = std::min<int64_t>(SUB_ITEM_BATCHES, std::max<int64_t>(1, (wrow + SUB_ROW_ITEMS * HK_WAVE - 1) /
                                                                                    (SUB_ROW_ITEMS * HK_WAVE))) *
                        HK_WAVE;
     std::vector<hk_item> ritems;
     std::vector<int> ritem0(nch), rnseg(nch);
-    for (int b = 0; b < nch; ++b) {
+    for (int b = 0; b < nch && batches > SUB_BLOCK_ITEMS; ++b) {
         ritem0[b] = (int)ritems.size();
         int seg = 0;
         for (int64_t e = 0; e < cnt[b]; e += br)
@@ -1158,16 +1312,19 @@ extern "C" hawkes_status hawkes_plan_set_subset(hawkes_plan p, int64_t m, const 
         nseg[q] = seg;
     }
     for (int q = nq_live; q < s->nq; ++q) item0[q] = (int)items.size();
-    s->n_ritems = (int)ritems.size();
     s->n_items = (int)items.size();
-    SC(dalloc(&s->ritems, std::max<size_t>(1, ritems.size())));
-    SC(dalloc(&s->ritem0, nch));
-    SC(dalloc(&s->rnseg, nch));
-    SC(dalloc(&s->xpart, (size_t)std::max(1, s->n_ritems) * HK_WAVE));
-    if (!ritems.empty())
+    SC(dalloc(&s->cnt, nch));
+    SC(hipMemcpy(s->cnt, cnt.data(), sizeof(int) * nch, hipMemcpyHostToDevice));
+    s->n_ritems = (int)ritems.size();
+    if (s->n_ritems > 0) {
+        SC(dalloc(&s->ritems, ritems.size()));
+        SC(dalloc(&s->ritem0, nch));
+        SC(dalloc(&s->rnseg, nch));
+        SC(dalloc(&s->xpart, ritems.size() * HK_WAVE));
         SC(hipMemcpy(s->ritems, ritems.data(), sizeof(hk_item) * ritems.size(), hipMemcpyHostToDevice));
-    SC(hipMemcpy(s->ritem0, ritem0.data(), sizeof(int) * nch, hipMemcpyHostToDevice));
-    SC(hipMemcpy(s->rnseg, rnseg.data(), sizeof(int) * nch, hipMemcpyHostToDevice));
+        SC(hipMemcpy(s->ritem0, ritem0.data(), sizeof(int) * nch, hipMemcpyHostToDevice));
+        SC(hipMemcpy(s->rnseg, rnseg.data(), sizeof(int) * nch, hipMemcpyHostToDevice));
+    }
     SC(dalloc(&s->items, items.size()));
     SC(dalloc(&s->item0, s->nq));
     SC(dalloc(&s->nseg, s->nq));
@@ -1241,18 +1398,25 @@ static void sub_rows(hawkes_plan p, SubFrom from, double *z, const double *off, 
                            from == SUB_FROM_Z ? theta : (double *)nullptr,
                            from == SUB_FROM_THETA ? theta : (double *)nullptr,
                            from == SUB_FROM_THETA ? z : (double *)nullptr, start);
-#define HK_SUBROWS(T, LOW, TOP, TD)                                                                                 \
-    do {                                                                                                            \
-        hipLaunchKernelGGL(k_sub_row<T>, dim3(s->n_ritems + (LOW)), dim3(HK_WAVE), 0, stream, p->ts, p->xs, p->ys,    \
-                           p->g, s->pos, s->tv, s->sxy, s->sts, s->qwide, s->qstep, s->ritems, kc, s->xpart, TD, z);  \
-        hipLaunchKernelGGL(k_sub_fin<T>, dim3(p->nchunks + (TOP)), dim3(SUB_ROWFIN_WAVES * HK_WAVE), 0, stream,       \
-                           s->lam_static, s->ritem0, s->rnseg, s->xpart, p->ts, p->xs, p->ys, p->g, s->pos, s->tv,    \
-                           s->sts, s->qwide, s->m, p->n, p->npad, fc, p->lam, s->lw, p->blockpart, p->status, TD,     \
-                           s->vz);                                                                                  \
-    } while (0)
-    if (tree) HK_SUBROWS(true, tree->R, hk_tree_top_blocks(tree->R), *tree);
-    else HK_SUBROWS(false, 0, 0, TreeDense{});
-#undef HK_SUBROWS
+    if (s->n_ritems > 0) {
+#define HK_SUBITEMS(T, LOW, TD)                                                                                   \
+    hipLaunchKernelGGL(k_sub_items<T>, dim3(s->n_ritems + (LOW)), dim3(HK_WAVE), 0, stream, p->ts, p->xs, p->ys,   \
+                       p->g, s->pos, s->tv, s->sxy, s->sts, s->qwide, s->qstep, s->ritems, kc, s->xpart, TD, z)
+        if (tree) HK_SUBITEMS(true, tree->R, *tree);
+        else HK_SUBITEMS(false, 0, TreeDense{});
+#undef HK_SUBITEMS
+        hipLaunchKernelGGL(k_sub_fin, dim3(p->nchunks), dim3(SUB_ROWFIN_WAVES * HK_WAVE), 0, stream, s->lam_static,
+                           s->ritem0, s->rnseg, s->xpart, p->ts, p->xs, p->ys, p->g, s->pos, s->tv, s->sts, s->qwide,
+                           s->m, p->n, fc, p->lam, s->lw, p->blockpart, p->status);
+        return;
+    }
+#define HK_SUBBLOCK(T, LOW, TD)                                                                                   \
+    hipLaunchKernelGGL(k_sub_block<T>, dim3(p->nchunks + (LOW)), dim3(SUB_ROW_WAVES * HK_WAVE), 0, stream, p->ts,  \
+                       p->xs, p->ys, p->g, s->pos, s->tv, s->sxy, s->sts, s->qwide, s->qstep, s->cnt, p->nchunks,  \
+                       s->lam_static, s->m, p->n, kc, fc, p->lam, s->lw, p->blockpart, p->status, TD, z)
+    if (tree) HK_SUBBLOCK(true, (tree->R + SUB_ROW_WAVES - 1) / SUB_ROW_WAVES, *tree);
+    else HK_SUBBLOCK(false, 0, TreeDense{});
+#undef HK_SUBBLOCK
 }
 
 // Eq. 1 after a row half at z.
@@ -1267,12 +1431,14 @@ static void sub_loglik(hawkes_plan p, const double *z, const double *off, double
 
 // The column half: Eq. 4 (and Eq. 5) on the subset, optionally with the fused
 // leapfrog update.
-static void sub_cols(hawkes_plan p, bool with_h, const PairConst &kc, const FinConst &fc, const SubUpd *upd,
-                     hipStream_t stream) {
+static void sub_col_pass(hawkes_plan p, bool with_h, const PairConst &kc, hipStream_t stream,
+                         const TreeDense *tree = nullptr) {
+    const int tops = tree ? hk_tree_top_blocks(tree->R) : 0;
+    const TreeDense td = tree ? *tree : TreeDense{};
     hk_subset *s = p->sub;
 #define HK_SUBCOL(H, D)                                                                                          \
-    hipLaunchKernelGGL((k_sub_col<H, D>), dim3(s->n_items), dim3(HK_WAVE), 0, stream, p->ts, p->xs, p->ys, s->lw, \
-                       p->g, s->pos, s->sxy, s->sts, s->m, s->items, kc, s->colG)
+    hipLaunchKernelGGL((k_sub_col<H, D>), dim3(s->n_items + tops), dim3(HK_WAVE), 0, stream, p->ts, p->xs, p->ys,   \
+                       s->lw, p->g, s->pos, s->sxy, s->sts, s->m, s->items, kc, s->colG, tops, td, s->vz)
     if (with_h) {
         if (kc.dot) HK_SUBCOL(true, true);
         else HK_SUBCOL(true, false);
@@ -1281,12 +1447,21 @@ static void sub_cols(hawkes_plan p, bool with_h, const PairConst &kc, const FinC
         else HK_SUBCOL(false, false);
     }
 #undef HK_SUBCOL
+}
+
+static void sub_col_fin(hawkes_plan p, bool with_h, const FinConst &fc, const SubUpd *upd, hipStream_t stream) {
+    hk_subset *s = p->sub;
     if (upd)
         hipLaunchKernelGGL(k_sub_colfin<true>, dim3(s->nq), dim3(SUB_FIN_WAVES * HK_WAVE), 0, stream, s->item0,
                            s->nseg, s->colG, s->a, s->m, fc, with_h, s->gsub, s->hsub, *upd);
     else
         hipLaunchKernelGGL(k_sub_colfin<false>, dim3(s->nq), dim3(SUB_FIN_WAVES * HK_WAVE), 0, stream, s->item0,
                            s->nseg, s->colG, s->a, s->m, fc, with_h, s->gsub, s->hsub, SubUpd{});
+}
+
+static void sub_cols(hawkes_plan p, bool with_h, const PairConst &kc, const FinConst &fc, hipStream_t stream) {
+    sub_col_pass(p, with_h, kc, stream);
+    sub_col_fin(p, with_h, fc, nullptr, stream);
 }
 
 // z_k = log theta_{idx_k} - beta t_{idx_k} (slot order)
@@ -1340,7 +1515,7 @@ extern "C" hawkes_status hawkes_subset_grad(hawkes_plan p, const hawkes_hyper *h
     // z = log theta on the subset (the rates are taken from d_theta as given)
     sub_rows(p, SUB_FROM_THETA, s->z0, nullptr, const_cast<double *>(d_theta), kc, fc, stream);
     if (d_grad_sub || d_negH_sub) {
-        sub_cols(p, d_negH_sub != nullptr, kc, fc, nullptr, stream);
+        sub_cols(p, d_negH_sub != nullptr, kc, fc, stream);
         hipLaunchKernelGGL(k_sub_scatter, dim3(nblk(s->m, 256)), dim3(256), 0, stream, s->slot, s->m, s->gsub,
                            s->hsub, d_grad_sub, d_negH_sub);
     }
@@ -1387,10 +1562,13 @@ extern "C" hawkes_status hmc_step(hawkes_plan p, const hawkes_hyper *hyper, hawk
                            td ? td->quad : walk ? s->quad : (const double *)nullptr, td ? td->R : walk ? 1 : 0, e);
     };
     if (walk && (st = hk_tree_launch(p, a->d_z, s->vz, s->quad, stream)) != HAWKES_OK) return st;
-    energy(e0);
     SubUpd upd{s->slot, a->d_z, off, pv, inv_s2, s->p, a->d_mass, 0.5 * a->eps, a->eps, s->tv, s->sts, s->qwide,
                kc.omega};
-    sub_cols(p, false, kc, fc, &upd, stream);
+    // (the energy comes before the first kick and drift, and after the prior's top
+    // step, which rides on the column pass)
+    sub_col_pass(p, false, kc, stream, td);
+    energy(e0);
+    sub_col_fin(p, false, fc, &upd, stream);
     for (int l = 0; l < a->L; ++l) {
         // evaluation at the drifted position, then a full kick and drift, or the
         // closing half kick after the last one
@@ -1399,7 +1577,8 @@ extern "C" hawkes_status hmc_step(hawkes_plan p, const hawkes_hyper *hyper, hawk
         if (walk && (st = hk_tree_launch(p, a->d_z, s->vz, s->quad, stream)) != HAWKES_OK) return st;
         upd.a_p = last ? 0.5 * a->eps : a->eps;
         upd.a_z = last ? 0.0 : a->eps;
-        sub_cols(p, false, kc, fc, &upd, stream);
+        sub_col_pass(p, false, kc, stream, td);
+        sub_col_fin(p, false, fc, &upd, stream);
     }
     energy(e1);
     hipLaunchKernelGGL(k_hmc_accept, dim3(nblk(m, ACCEPT_THREADS)), dim3(ACCEPT_THREADS), 0, stream, e0, e1, (int)nb,
@@ -1430,7 +1609,7 @@ extern "C" hawkes_status hawkes_subset_trend_grad(hawkes_plan p, const hawkes_hy
     sub_rows(p, SUB_FROM_Z, const_cast<double *>(d_z), off, d_theta, kc, fc, stream);
     // the log-likelihood alone (a Metropolis-Hastings proposal) needs no column pass
     if (d_grad_z || d_grad_beta) {
-        sub_cols(p, false, kc, fc, nullptr, stream);
+        sub_cols(p, false, kc, fc, stream);
         hipLaunchKernelGGL(k_sub_trend_out, dim3(1), dim3(256), 0, stream, s->slot, s->pos, p->ts, s->m, s->gsub, d_z,
                            off, d_grad_z, d_grad_beta);
     }
@@ -1472,7 +1651,7 @@ hawkes_status hk_subset_exact(hawkes_plan p, const hawkes_hyper *hy, const doubl
     hawkes_status st = ensure_static(p, hy, d_theta, false, kc, fc, stream);
     if (st != HAWKES_OK) return st;
     sub_rows(p, SUB_FROM_THETA, s->z0, nullptr, const_cast<double *>(d_theta), kc, fc, stream);
-    sub_cols(p, true, kc, fc, nullptr, stream);
+    sub_cols(p, true, kc, fc, stream);
     HK_CHECK(hipGetLastError());
     *gsub = s->gsub;
     *hsub = s->hsub;

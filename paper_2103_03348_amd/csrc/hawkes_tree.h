@@ -20,8 +20,8 @@
 // M_s has zero row sums and Q row sums e_r, so both products are taken over
 // differences, and the quadratic form over their squares (off-diagonals are <= 0:
 // every term is >= 0).  Needing z alone, the two steps ride as extra blocks on
-// the row pass and on its finalisation: N = 23,422, 1,610 tips, HMC iteration
-// under this prior 1,126 us with the level walk, 653 us with these (617 us under
+// the row pass and on the column pass: N = 23,422, 1,610 tips, HMC iteration
+// under this prior 1,117 us with the level walk, 638 us with these (619 us under
 // the independent prior).
 #define HK_TREE_SUB 64           // tips per subtree: one wavefront
 #define HK_TREE_MAX_ROOTS 1024   // more subtrees (a tree of over ~15,000 tips) take the level walk
@@ -42,7 +42,7 @@ struct TreeDense {
     double *quad;         // [R] parts of z^T V^{-1} z (their sum is the form)
 };
 
-constexpr int HK_TREE_TOP_THREADS = 256, HK_TREE_TOP_ROOTS = 16;  // per block of the top step
+constexpr int HK_TREE_TOP_THREADS = 64, HK_TREE_TOP_ROOTS = 4;  // per block of the top step
 constexpr int hk_tree_top_blocks(int R) { return (R + HK_TREE_TOP_ROOTS - 1) / HK_TREE_TOP_ROOTS; }
 
 // Low step of subtree r, by one wavefront.
@@ -74,7 +74,7 @@ __device__ __forceinline__ void hk_tree_low(const TreeDense &t, const double *__
     }
 }
 
-// Top step of 16 subtrees, by a block of HK_TREE_TOP_THREADS.
+// Top step of HK_TREE_TOP_ROOTS subtrees, by a block of HK_TREE_TOP_THREADS.
 __device__ __forceinline__ void hk_tree_top(const TreeDense &t, int block, double *__restrict__ vz) {
     __shared__ double adj[HK_TREE_TOP_ROOTS];
     const int l = threadIdx.x / 16, c = threadIdx.x % 16, r0 = block * HK_TREE_TOP_ROOTS, r = min(r0 + l, t.R - 1);

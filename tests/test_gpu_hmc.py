@@ -593,3 +593,31 @@ def test_tree_prior_shapes(gpu, name):
         assert abs(q.item() - z @ vz) <= 1e-10 * (z @ vz)
         assert np.max(np.abs(g.cpu().numpy() + vz / sigma ** 2)) <= 1e-10 * np.max(np.abs(vz)) / sigma ** 2
     plan.close()
+
+
+@pytest.mark.parametrize("cutoff", [False, True])
+@pytest.mark.parametrize("m,t_end", [(1, 600.0), (17, 7200.0), (400, 7200.0), (1300, 600.0), (2011, 7200.0)])
+def test_subset_row_forms_match_oracle(gpu, m, t_end, cutoff):
+    """The row half of the subset path as blocks (up to 1,024 batches of 64 entries
+    before the row chunks: m <= 400 and some below 1,300 of these 6,000 events)
+    and as one-wavefront items (m = 1,300 and 2,011), dense and sparse in time
+    (split and unsplit batches), without and with the underflow cutoff: Eq. 1, 4
+    and 5 against the oracle, with the bounds above."""
+    import dataclasses
+
+    es = synth.small(6000, seed=60, t_end=t_end, ties=8, all_free=False)
+    sub = np.sort(np.random.default_rng(m).choice(es.n, m, replace=False)).astype(np.int64)
+    es = dataclasses.replace(es, subset=sub, z=np.log(es.theta[sub]))
+    plan, idx = _setup(es)
+    plan.set_cutoff(cutoff)
+    ref = oracle.evaluate_es(es)
+    gi, hi = ref["grad_theta"][sub], ref["negH_theta"][sub]
+    a = es.hyper[3] * (1.0 - np.exp(-es.hyper[4] * (es.t.max() - es.t[sub])))
+    for want_h in (True, False):
+        ll, g, h = _subset_grad(plan, es, es.theta, want_h=want_h)
+        assert plan.status() == 0
+        assert abs(ll - ref["loglik"]) < 2e-6 * es.n
+        assert np.max(np.abs(g - gi) / np.maximum(gi + 2 * a, 1e-300)) < 1e-6
+        if want_h:
+            assert h_rel_all(h, hi) < 1e-6
+    plan.close()
