@@ -111,6 +111,7 @@ struct hawkes_plan_s {
     hk_item *row_items;       // [n_row_items] (device)
     int n_row_blocks;         // blocks of the row pass
     int *row_block0;          // [n_row_blocks + 1] first item of each block (device)
+    bool row_single;          // a block per item: block b takes item b
     int *row_item0;           // [ntiles] first item of each row tile (device)
     int *row_nseg;            // [ntiles] items per row tile (device)
     int64_t *colpart_off;     // [ntiles] offset of tile I's column partials (device)
