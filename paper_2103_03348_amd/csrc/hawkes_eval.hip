@@ -973,6 +973,31 @@ __device__ __forceinline__ void col_sweep(const ColRow *__restrict__ rows, const
     H += H1;
 }
 
+// A row as staged (by one lane of a wavefront that holds the chunk's 64 rows);
+// for Eq. 4 alone, `split` returns whether the chunk splits every exponent exactly.
+template <bool WITH_H, bool DOT>
+__device__ __forceinline__ ColRow stage_col_row(double dt_ref, double ux, double uy, double lwi, const PairConst &kc,
+                                                bool &split) {
+    double cr = lwi + kc.kw_d * dt_ref;
+    ColRow r;
+    if (DOT) {
+        cr -= fma(ux, ux, uy * uy);
+        r.u = make_double2(2.0 * ux, 2.0 * uy);
+    } else {
+        r.u = make_double2(ux, uy);
+    }
+    r.c = fmax(cr, HK_EXP_FLOOR);
+    r.n = 0;
+    split = !WITH_H && __ballot(lwi > HK_LW_SPLIT_MAX) != 0;
+    if (!WITH_H && !split && lwi > HK_EXP_FLOOR) {
+        const double nw = rint(lwi);
+        r.n = (int)nw;
+        r.c -= nw;
+    }
+    if (WITH_H) split = true;
+    return r;
+}
+
 template <bool WITH_H, bool DOT>
 __global__ __launch_bounds__(HK_TILE) void k_col(const double *__restrict__ ts, const double *__restrict__ xs,
                                                   const double *__restrict__ ys, const double *__restrict__ lw,
@@ -1012,23 +1037,8 @@ __global__ __launch_bounds__(HK_TILE) void k_col(const double *__restrict__ ts, 
                 const int64_t i = (int64_t)c * HK_WAVE + tid;
                 const double ux = xs[i] * kc.sx, uy = ys[i] * kc.sx;
                 const double lwi = lw[i];
-                double cr = lwi + kc.kw_d * (ts[i] - t_ref);
-                ColRow r;
-                if (DOT) {
-                    cr -= fma(ux, ux, uy * uy);
-                    r.u = make_double2(2.0 * ux, 2.0 * uy);
-                } else {
-                    r.u = make_double2(ux, uy);
-                }
-                r.c = fmax(cr, HK_EXP_FLOOR);
-                r.n = 0;
-                // the staging wavefront holds the chunk's 64 rows
-                const bool split = !WITH_H && __ballot(lwi > HK_LW_SPLIT_MAX) != 0;
-                if (!WITH_H && !split && lwi > HK_EXP_FLOOR) {
-                    const double nw = rint(lwi);
-                    r.n = (int)nw;
-                    r.c -= nw;
-                }
+                bool split;
+                const ColRow r = stage_col_row<WITH_H, DOT>(ts[i] - t_ref, ux, uy, lwi, kc, split);
                 rows[tid] = r;
                 rg[tid] = g[i];
                 if (tid == 0) chunk_split = split;
@@ -1060,6 +1070,107 @@ __global__ __launch_bounds__(HK_TILE) void k_col(const double *__restrict__ ts, 
         cg[tid] = Gd;
         if (WITH_H) cg[HK_TILE + tid] = Hd;
     }
+}
+
+// Column pass and its finalisation for small sets, one block of COL_BLOCK_WAVES
+// wavefronts per 32 columns: the wavefronts take the later row chunks in turn,
+// each staging its own rows through LDS and giving half its lanes to each of
+// k_col's two streams (so that every chunk's FP32 sum is k_col's), and the first
+// adds their sums in a fixed order and finishes the columns.  With `totals` the last block reduces the scalar
+// results, as in k_colfin.
+//
+// Small sets are bound by the chain of launches and of each launch's own loads;
+// this saves a launch, and half a wavefront per stream halves the longest chain of
+// steps: an evaluation of N = 1,000 events 42.0 us with k_col and k_colfin, 33.1
+// in this form (35.8 with 64 columns per block); 2,000 43.6 / 37.3; 4,000 51.2 /
+// 49.2; 5,003 60.7 / 60.3; 8,000 94.2 / 94.5 (12 or 8 wavefronts: slower).  Hence
+// its limit, COL_BLOCK_CHUNKS.
+#ifndef HK_COL_BLOCK_WAVES
+#define HK_COL_BLOCK_WAVES 16
+#endif
+#ifndef HK_COL_BLOCK_CHUNKS
+#define HK_COL_BLOCK_CHUNKS 80
+#endif
+constexpr int COL_BLOCK_WAVES = HK_COL_BLOCK_WAVES, COL_BLOCK_CHUNKS = HK_COL_BLOCK_CHUNKS;
+constexpr int COL_BLOCK_COLS = HK_WAVE / 2;
+// k_col's two streams of a chunk, one per half of the wavefront (`half` is the lane's)
+template <bool WITH_H, bool SPLIT, bool MASKED, bool DOT>
+__device__ __forceinline__ void col_sweep_halves(const ColRow *__restrict__ rows, const int *__restrict__ rg, int half,
+                                                 int jcol, double xj, double yj, double dj, float &G, float &H) {
+#pragma clang fp contract(off)
+#pragma unroll 4
+    for (int s = 0; s < HK_WAVE; s += 2) {
+        const float e = col_term<SPLIT, MASKED, DOT>(rows, rg, s + half, jcol, xj, yj, dj);
+        G += e;
+        if (WITH_H) H = fmaf(e, e, H);
+    }
+    G += __shfl_xor(G, COL_BLOCK_COLS);
+    if (WITH_H) H += __shfl_xor(H, COL_BLOCK_COLS);
+}
+
+struct ColBlockLds {  // one wavefront's staged rows
+    ColRow rows[HK_WAVE];
+    int g[HK_WAVE];
+};
+
+template <bool WITH_H, bool DOT>
+__global__ __launch_bounds__(COL_BLOCK_WAVES * HK_WAVE) void k_col_block(
+    const double *__restrict__ ts, const double *__restrict__ xs, const double *__restrict__ ys,
+    const double *__restrict__ lw, const int *__restrict__ g, const int *__restrict__ perm, int64_t n, int nchunks,
+    const double *__restrict__ a, const PairConst kc, const FinConst fc, double *__restrict__ grad_theta,
+    double *__restrict__ negH_theta, const double *__restrict__ blockpart, double *__restrict__ loglik,
+    double *__restrict__ grad_hyper, double *__restrict__ negH_hyper, int *__restrict__ status) {
+    __shared__ ColBlockLds Ls[COL_BLOCK_WAVES];
+    __shared__ double part[COL_BLOCK_WAVES][2][HK_WAVE];
+    if ((int)blockIdx.x == 2 * nchunks) {
+        fin_totals(blockpart, nchunks, loglik, grad_hyper, negH_hyper, status, &part[0][0][0]);
+        return;
+    }
+    const int lane = threadIdx.x & (HK_WAVE - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x / HK_WAVE);
+    ColBlockLds &L = Ls[wv];
+    const int first = blockIdx.x * COL_BLOCK_COLS, half = lane / COL_BLOCK_COLS;
+    const int jcol = first + lane % COL_BLOCK_COLS;
+    const double t_ref = ts[first / HK_TILE * HK_TILE];
+    const double tj = ts[jcol], uxj = xs[jcol] * kc.sx, uyj = ys[jcol] * kc.sx;
+    const double t_max = ts[first + COL_BLOCK_COLS - 1];  // the block's latest column
+    double dj = -kc.kw_d * (tj - t_ref);
+    if (DOT) dj -= fma(uxj, uxj, uyj * uyj);
+    if (jcol >= n) dj = HK_EXP_FLOOR;
+    double Gd = 0.0, Hd = 0.0;
+    for (int c = first / HK_WAVE + wv; c < nchunks; c += COL_BLOCK_WAVES) {
+        const int64_t i = (int64_t)c * HK_WAVE + lane;
+        const double ti = ts[i], ux = xs[i] * kc.sx, uy = ys[i] * kc.sx, lwi = lw[i];
+        const int gi = g[i];
+        if (__shfl(ti, 0) - t_max > kc.dt_cut_ex) break;  // and all later rows
+        bool split = true;
+        L.rows[lane] = stage_col_row<WITH_H, DOT>(ti - t_ref, ux, uy, lwi, kc, split);
+        L.g[lane] = gi;
+        hk_wave_sync();
+        if (L.g[HK_WAVE - 1] > first) {
+            float G = 0.0f, H = 0.0f;
+            const bool masked = L.g[0] <= first + COL_BLOCK_COLS - 1;
+            if (masked && split) col_sweep_halves<WITH_H, true, true, DOT>(L.rows, L.g, half, jcol, uxj, uyj, dj, G, H);
+            else if (masked) col_sweep_halves<WITH_H, false, true, DOT>(L.rows, L.g, half, jcol, uxj, uyj, dj, G, H);
+            else if (split) col_sweep_halves<WITH_H, true, false, DOT>(L.rows, L.g, half, jcol, uxj, uyj, dj, G, H);
+            else col_sweep_halves<WITH_H, false, false, DOT>(L.rows, L.g, half, jcol, uxj, uyj, dj, G, H);
+            Gd += (double)G;
+            if (WITH_H) Hd += (double)H;
+        }
+        hk_wave_sync();
+    }
+    part[wv][0][lane] = Gd;
+    part[wv][1][lane] = Hd;
+    __syncthreads();
+    if (wv != 0 || half != 0 || jcol >= n) return;
+    double Gs = part[0][0][lane], Hs = part[0][1][lane];
+#pragma unroll
+    for (int q = 1; q < COL_BLOCK_WAVES; ++q) {
+        Gs += part[q][0][lane];
+        Hs += part[q][1][lane];
+    }
+    const int dst = perm[jcol];
+    if (grad_theta) grad_theta[dst] = Gs * fc.corr - a[jcol];
+    if (negH_theta) negH_theta[dst] = Hs * fc.corr * fc.corr;
 }
 
 // Column finalisation, one block per 64-event chunk: the HK_FIN_WAVES
@@ -1201,6 +1312,15 @@ static void launch_col(hawkes_plan p, const PairConst &kc, const FinConst &fc, d
                        double *d_negH_theta, hipStream_t stream, bool totals = false, double *d_loglik = nullptr,
                        double *d_grad_hyper = nullptr, double *d_negH_hyper = nullptr) {
     hk_prof_mark(p, HK_PROF_COL, true, stream);
+    if (p->nchunks <= COL_BLOCK_CHUNKS) {
+        const auto kern = d_negH_theta ? (kc.dot ? k_col_block<true, true> : k_col_block<true, false>)
+                                       : (kc.dot ? k_col_block<false, true> : k_col_block<false, false>);
+        hipLaunchKernelGGL(kern, dim3(2 * p->nchunks + (totals ? 1 : 0)), dim3(COL_BLOCK_WAVES * HK_WAVE), 0, stream,
+                           p->ts, p->xs, p->ys, p->lw, p->g, p->perm, p->n, p->nchunks, p->a, kc, fc, d_grad_theta,
+                           d_negH_theta, p->blockpart, d_loglik, d_grad_hyper, d_negH_hyper, p->status);
+        hk_prof_mark(p, HK_PROF_COL, false, stream);
+        return;
+    }
 #define HK_COL(H, D)                                                                                        \
     hipLaunchKernelGGL((k_col<H, D>), dim3(p->n_col_blocks), dim3(HK_TILE), 0, stream, p->ts, p->xs, p->ys, p->lw, \
                        p->g, p->n, p->col_items, p->col_block0, p->colG, kc)

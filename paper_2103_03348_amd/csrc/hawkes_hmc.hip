@@ -681,13 +681,6 @@ __global__ __launch_bounds__(SUB_ROWFIN_WAVES * HK_WAVE) void k_sub_fin(
                                       blockpart, status);
 }
 
-// orders a wavefront's own LDS writes and reads (its LDS instructions execute in
-// order: only the compiler has to keep them so)
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 struct SubRowLds {  // one wavefront's staged entries
     double2 xy[SUB_UNIT];
     double t[SUB_UNIT];
@@ -792,7 +785,7 @@ __global__ __launch_bounds__(SUB_ROW_WAVES * HK_WAVE) void k_sub_block(
                 L.pos[lane] = np;
             }
             if (u > u0) fetch(u - 1);
-            wave_sync();
+            hk_wave_sync();
             // a unit whose entries all precede the chunk's first tie group needs no
             // causality mask (entries past the prefix and padding follow every row)
             if (L.pos[SUB_UNIT - 1] < g_first) {
@@ -802,7 +795,7 @@ __global__ __launch_bounds__(SUB_ROW_WAVES * HK_WAVE) void k_sub_block(
                 if (fact) sub_row_sweep<SUB_UNIT, true, true>(L.xy, L.v, L.t, L.pos, tsi, xr, yr, gr, kc, accq);
                 else sub_row_sweep<SUB_UNIT, true, false>(L.xy, L.v, L.t, L.pos, tsi, xr, yr, gr, kc, accq);
             }
-            wave_sync();
+            hk_wave_sync();
         }
         fold();
     }

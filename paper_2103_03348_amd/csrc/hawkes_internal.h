@@ -216,6 +216,13 @@ struct FinConst {
     double lam_exact;
 };
 
+// orders a wavefront's own LDS writes and reads (its LDS instructions execute in
+// order: only the compiler has to keep them so)
+__device__ __forceinline__ void hk_wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 bool hk_hyper_ok(const hawkes_hyper *h);
 // Eq. 4 and Eq. 5 on the subset at the rates d_theta (O(N M) path); device
 // pointers to the results in time order

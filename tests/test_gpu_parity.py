@@ -495,3 +495,64 @@ def test_every_output_over_small_schedules(gpu, n):
     assert abs(g["loglik"] - ref["loglik"]) <= 2e-6 * n
     assert e["lam_rel"] < 2e-6 and e["g_rel"] < 1e-6
     assert e["h_rel_all"] < 1e-6 and e["h_rel_norm"] < 1e-6
+
+
+@pytest.mark.parametrize("n,t_end", [(1, 10.0), (33, 10.0), (1056, 400.0), (1056, 4.0e4), (1056, 4.0e5),
+                                     (5120, 1500.0), (5121, 1500.0), (11264, 3000.0), (11265, 3000.0)])
+def test_small_set_forms_match_oracle(gpu, n, t_end):
+    """The sizes where the small sets' forms begin and end: columns in blocks of
+    32 that finish themselves (up to 80 chunks of 64), rates staged by the row
+    pass (up to 44 tiles of 256), dense in time and sparse (both forms of the row
+    pass), with and without the cutoff, all outputs and Eq. 4 alone; the bounds of
+    the other parity tests."""
+    import torch
+
+    from paper_2103_03348_amd.hawkes import Plan
+
+    es = synth.small(n, seed=900 + n, t_end=t_end, ties=n // 20)
+    ref = oracle.evaluate_es(es)
+    a = es.hyper[3] * (1.0 - np.exp(-es.hyper[4] * (es.t.max() - es.t)))
+    plan = Plan.from_numpy(es.t, es.x, es.y, es.t0)
+    th = torch.as_tensor(es.theta, device="cuda:0")
+    for cutoff in (False, True):
+        plan.set_cutoff(cutoff)
+        for full in (True, False):
+            out = plan.eval(th, es.hyper, loglik=True, grad_theta=True, grad_hyper=full, negH_theta=full,
+                            negH_hyper=full)
+            # events without any intensity (a single event, 98 of the sparsest set):
+            # a log-likelihood of -inf, which is reported
+            ll = float(out["loglik"].item())
+            assert (plan.status() == 0) == np.isfinite(ref["loglik"])
+            if not np.isfinite(ref["loglik"]):
+                assert ll == ref["loglik"]
+                continue
+            assert abs(ll - ref["loglik"]) <= 2e-6 * n
+            lam = plan.lam().cpu().numpy()
+            assert np.all(np.abs(lam - ref["lam"]) <= 2e-6 * ref["lam"])
+            g = out["grad_theta"].cpu().numpy()
+            assert np.max(np.abs(g - ref["grad_theta"]) / np.maximum(ref["grad_theta"] + 2 * a, 1e-300)) < 1e-6
+            if full:
+                h = out["negH_theta"].cpu().numpy()
+                assert np.max(np.abs(h - ref["negH_theta"]) / (ref["negH_theta"] + 1e-30)) < 1e-6
+    plan.close()
+
+
+@pytest.mark.parametrize("bad", [-1.0, np.nan, np.inf])
+def test_bad_rate_is_reported_by_the_staging_row_pass(gpu, bad):
+    """A rate that is negative or not finite sets the status where the row pass
+    stages the rates itself, wherever the event lies."""
+    import torch
+
+    from paper_2103_03348_amd import _lib
+    from paper_2103_03348_amd.hawkes import Plan
+
+    es = synth.small(700, seed=5)
+    plan = Plan.from_numpy(es.t, es.x, es.y, es.t0)
+    for k in (0, 350, 699):
+        theta = es.theta.copy()
+        theta[k] = bad
+        plan.eval(torch.as_tensor(theta, device="cuda:0"), es.hyper, loglik=True)
+        assert plan.status() == _lib.E_INVALID
+    plan.eval(torch.as_tensor(es.theta, device="cuda:0"), es.hyper, loglik=True)
+    assert plan.status() == 0
+    plan.close()
