@@ -335,19 +335,30 @@ __global__ __launch_bounds__(MLP_APPLY_WAVES * HK_WAVE) void k_mlp_apply(const d
 // N = 100,000, 6,874 free events: cells of 3h whose every event was tested for
 // all nine sums, in two passes, took 257 us (bound by L2: 3 GB of candidates)
 // after 123 us of counting sort by global atomics (contended in the clusters);
-// this form 79 us after 27 (sums of 440 and 110 us per
-// prediction with the network).
+// this form 49 us after 23 (sums of 440 and 75 us per prediction with the network).
 struct FeatGrid {
     double gx0, gy0, s;  // origin and cell size
     int nx, ny;
     int nb, per;         // runs of the time-ordered events, events per run
 };
 
+// The discs and windows, formed once on the host (FP64 divisions cost a wavefront
+// some 20 instructions each).
+struct FeatConst {
+    double r0, r1;          // squared radii h^2, (3h)^2
+    double w1, w3, w6;      // 1, 3 and 6 over omega
+    double inv_h2, inv_s;   // 1 / h^2, 1 / cell
+    double R0, R1;          // the radii in cells
+    double omega;
+};
+
 constexpr int kFeatCells = 8192;  // cells of a run's histogram in LDS (32 KB)
 constexpr int kFeatRuns = 64;     // one lane per run in k_features
-constexpr int kFeatGroup = 256;   // cells per block of the offsets kernel
+constexpr int kFeatGroup = HK_WAVE;  // cells per block of the offsets kernel, a lane each
+constexpr int kFeatOffWaves = 4;     // its wavefronts, a quarter of the runs each
 constexpr int kFeatThreads = 1024;
-constexpr int kFeatTests = 4;     // candidates a lane of k_features loads together
+constexpr int kFeatWindows = 2;   // columns whose windows' candidates a lane loads together
+constexpr int kFeatTests = 8;     // candidates a lane of k_features loads together
 constexpr int kFeatBatch = 4;     // events a thread of the sort loads together
 
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return min(max(v, lo), hi); }
@@ -366,7 +377,7 @@ __device__ __forceinline__ int64_t cell_of(const double *__restrict__ xy, int64_
 __global__ __launch_bounds__(kFeatThreads) void k_cell_hist(const double *__restrict__ xy, const int *__restrict__ perm,
                                                            int64_t n, const FeatGrid G, int *__restrict__ off,
                                                            int *__restrict__ gsum) {
-    __shared__ int cnt[kFeatCells];
+    __shared__ __attribute__((aligned(16))) int cnt[kFeatCells];
     const int cells = G.nx * G.ny, b = blockIdx.x;
     for (int c = threadIdx.x; c < kFeatCells; c += kFeatThreads) cnt[c] = 0;
     const int64_t i1 = min(n, (int64_t)(b + 1) * G.per);
@@ -384,53 +395,61 @@ __global__ __launch_bounds__(kFeatThreads) void k_cell_hist(const double *__rest
     }
     __syncthreads();
     for (int c = threadIdx.x; c < cells; c += kFeatThreads) off[(int64_t)b * (cells + 1) + c] = cnt[c];
-    const int l = threadIdx.x % 32, g = threadIdx.x / 32;
+    // a thread's cells, then the threads of a group
+    constexpr int own = kFeatCells / kFeatThreads, thr = kFeatGroup / own;
     int v = 0;
 #pragma unroll
-    for (int k = 0; k < kFeatGroup / 32; ++k) v += cnt[g * kFeatGroup + 32 * k + l];
-    for (int o = 16; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    if (l == 0) gsum[b * (kFeatCells / kFeatGroup) + g] = v;
+    for (int k = 0; k < own; ++k) v += cnt[threadIdx.x * own + k];
+    for (int o = 1; o < thr; o <<= 1) v += __shfl_xor(v, o);
+    if (threadIdx.x % thr == 0) gsum[(threadIdx.x * own + b * kFeatCells) / kFeatGroup] = v;
 }
 
 // Counts to offsets in place: a block has kFeatGroup cells; the events of the
-// groups before it come from the runs' sums.
-__global__ __launch_bounds__(kFeatGroup) void k_cell_off(const int *__restrict__ gsum, int64_t n, const FeatGrid G,
-                                                         int *__restrict__ off) {
-    __shared__ int sh[kFeatGroup];
-    const int cells = G.nx * G.ny, c = blockIdx.x * kFeatGroup + threadIdx.x;
-    constexpr int groups = kFeatCells / kFeatGroup;
+// groups before it come from the runs' sums.  Bound by the latency of its loads:
+// N = 100,000 (6,806 cells, 64 runs) 5.4 us, with 256 cells per block and
+// every run of a cell in one thread 9.8.
+__global__ __launch_bounds__(kFeatOffWaves * HK_WAVE) void k_cell_off(const int *__restrict__ gsum, int64_t n,
+                                                                      const FeatGrid G, int *__restrict__ off) {
+    constexpr int groups = kFeatCells / kFeatGroup, threads = kFeatOffWaves * HK_WAVE;
+    constexpr int per = kFeatRuns / kFeatOffWaves;
+    __shared__ int before[kFeatOffWaves], tot[kFeatOffWaves][HK_WAVE];
+    const int lane = threadIdx.x % HK_WAVE, w = threadIdx.x / HK_WAVE;
+    const int cells = G.nx * G.ny, c = blockIdx.x * kFeatGroup + lane;
+    // the cell's counts of the wavefront's runs, loaded together
+    int cnt[per], sum = 0;
+#pragma unroll
+    for (int k = 0; k < per; ++k) {
+        const int b = w * per + k;
+        cnt[k] = b < G.nb && c < cells ? off[(int64_t)b * (cells + 1) + c] : 0;
+    }
     int v = 0;
-    for (int k = threadIdx.x; k < G.nb * groups; k += kFeatGroup)
-        if (k % groups < (int)blockIdx.x) v += gsum[k];
-    sh[threadIdx.x] = v;
+#pragma unroll 8
+    for (int k = threadIdx.x; k < G.nb * groups; k += threads) v += k % groups < (int)blockIdx.x ? gsum[k] : 0;
+    for (int o = HK_WAVE / 2; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    if (lane == 0) before[w] = v;
+#pragma unroll
+    for (int k = 0; k < per; ++k) sum += cnt[k];
+    tot[w][lane] = sum;
     __syncthreads();
-    for (int h = kFeatGroup / 2; h > 0; h >>= 1) {
-        if (threadIdx.x < h) sh[threadIdx.x] += sh[threadIdx.x + h];
-        __syncthreads();
+    int all = 0, run = 0;
+#pragma unroll
+    for (int q = 0; q < kFeatOffWaves; ++q) {
+        run += before[q] + (q < w ? tot[q][lane] : 0);
+        all += tot[q][lane];
     }
-    const int base = sh[0];
-    __syncthreads();
-    // the cell's counts of every run, loaded together
-    int cnt[kFeatRuns], tot = 0;
-#pragma unroll
-    for (int b = 0; b < kFeatRuns; ++b) cnt[b] = b < G.nb && c < cells ? off[(int64_t)b * (cells + 1) + c] : 0;
-#pragma unroll
-    for (int b = 0; b < kFeatRuns; ++b) tot += cnt[b];
-    sh[threadIdx.x] = tot;
-    __syncthreads();
-    for (int h = 1; h < kFeatGroup; h <<= 1) {
-        const int o = threadIdx.x >= h ? sh[threadIdx.x - h] : 0;
-        __syncthreads();
-        sh[threadIdx.x] += o;
-        __syncthreads();
+    run -= all;
+    for (int o = 1; o < HK_WAVE; o <<= 1) {  // the cells before it in the group
+        const int u = __shfl_up(all, o);
+        if (lane >= o) all += u;
     }
-    int run = base + sh[threadIdx.x] - tot;
+    run += all;
 #pragma unroll
-    for (int b = 0; b < kFeatRuns; ++b) {
+    for (int k = 0; k < per; ++k) {
+        const int b = w * per + k;
         if (b < G.nb && c < cells) off[(int64_t)b * (cells + 1) + c] = run;
-        run += cnt[b];
+        run += cnt[k];
     }
-    if (c == 0) off[cells] = (int)n;  // end of the last cell
+    if (c == 0 && w == 0) off[cells] = (int)n;  // end of the last cell
 }
 
 // Per run: its events to their places (the order inside a cell and run does not
@@ -521,9 +540,17 @@ __global__ void k_cell_scatter(const double *__restrict__ t, const double *__res
 }
 
 // One wavefront per free event; its lanes take the grid rows of the 3h disc
-// side by side (8 or 16 lanes a row), so that the rows' loads are in flight
-// together.  The counts are summed across the wavefront (integers: exact in any
-// order).
+// side by side (8 or 16 lanes a row) to find the rows' ranges and for the time
+// windows, and the whole wavefront goes through one range of candidates after the
+// other for the counts over all times.  The counts are summed across the wavefront
+// (integers: exact in any order).
+//
+// Bound by its instructions, mostly the tests, and by how the wavefronts fill the
+// chip (N = 100,000, 6,874 free events, 6.7 wavefronts per SIMD): candidates side
+// by side, a row per lane group, left most lanes idle behind the longest row (a
+// wavefront 3,580 vector instructions, 79 us); ranges one by one 2,600 and 62 us;
+// constants formed on the host, blocks of one wavefront and seven of them per
+// SIMD, so that all are in flight at once, 49 us (six: 52; eight spill).
 //
 // A cell counts as inside the 3h disc, or as out of reach of a disc, with a
 // margin of 1e-6 cells, far above the rounding of its edges (positions relative
@@ -539,24 +566,19 @@ __global__ void k_cell_scatter(const double *__restrict__ t, const double *__res
 // depend on it: the largest exponent a_max (a maximum is exact) and then
 // sum_e rint(2^36 exp(a_e - a_max)) in 64-bit integers (exact up to 2^27
 // terms), each exponential by the FP32 exp2 (a feature needs no more).
-__global__ __launch_bounds__(256) void k_features(const double *__restrict__ t, const double *__restrict__ xy,
+__global__ __launch_bounds__(HK_WAVE, 7) void k_features(const double *__restrict__ t, const double *__restrict__ xy,
                                                   const int64_t *__restrict__ cidx, const int *__restrict__ pos,
                                                   const int *__restrict__ slot, const int *__restrict__ g,
                                                   const double *__restrict__ ts, const double *__restrict__ z,
-                                                  int64_t m, int64_t n, double t0, double t1, double h, double omega,
+                                                  int64_t m, int64_t n, double t0, double t1, const FeatConst F,
                                                   const FeatGrid G, const int *__restrict__ off,
                                                   const double *__restrict__ ct, const double2 *__restrict__ cxy,
                                                   float *__restrict__ feat) {
 #pragma clang fp contract(off)
-    const int lane = threadIdx.x & (HK_WAVE - 1);
-    const int64_t r = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / HK_WAVE;
-    if (r >= m) return;  // whole wavefronts leave together
-    const int k = slot[r];
+    const int lane = threadIdx.x, r = blockIdx.x, k = slot[r];
     const int64_t e = cidx[k];
     const double xm = xy[2 * e], ym = xy[2 * e + 1], tm = t[e];
-    const double r0 = h * h, h3 = 3.0 * h, r1 = h3 * h3;
-    const double w1 = 1.0 / omega, w3 = 3.0 / omega, w6 = 6.0 / omega;
-    const double inv_h2 = 1.0 / (h * h);
+    const double r0 = F.r0, r1 = F.r1, w1 = F.w1, w3 = F.w3, w6 = F.w6;
     // the runs that hold events of the time windows: the last one that starts
     // before the earliest window, up to the last that starts inside the latest
     int b_lo = 0, b_hi = 0;
@@ -572,8 +594,8 @@ __global__ __launch_bounds__(256) void k_features(const double *__restrict__ t, 
     // (past the last run a cell ends where the next begins)
     const int *__restrict__ w_hi = b_hi + 1 < G.nb ? off + (b_hi + 1) * stride : off + 1;
     // positions in cells relative to the grid's origin
-    const double inv_s = 1.0 / G.s, um = (xm - G.gx0) * inv_s, vm = (ym - G.gy0) * inv_s;
-    const double R0 = h * inv_s, R1 = h3 * inv_s, tol = 1e-6;
+    const double um = (xm - G.gx0) * F.inv_s, vm = (ym - G.gy0) * F.inv_s;
+    const double R0 = F.R0, R1 = F.R1, tol = 1e-6;
     const int y_lo = clampi((int)floor(vm - R1 - tol), 0, G.ny - 1), y_hi = clampi((int)floor(vm + R1 + tol), 0, G.ny - 1);
     // at most 8 rows and columns (6 h over cells of at least h)
     const int lpr = y_hi - y_lo < 4 ? 16 : 8;
@@ -583,6 +605,8 @@ __global__ __launch_bounds__(256) void k_features(const double *__restrict__ t, 
 
     int c[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     int xa = 0, xb = -1;  // the columns the 3h disc reaches in the lane's row
+    // the row's candidates: [la, lb) and [ra, rb) for the 3h disc, [ha, hb) for the h disc
+    int la = 0, lb = 0, ra = 0, rb = 0, ha = 0, hb = 0;
     int wq = 0, wn = 0;   // first event and number of events in the time windows' runs, of column xa + lr
     if (live) {
         // least and largest distance in y to the row's cells
@@ -605,43 +629,49 @@ __global__ __launch_bounds__(256) void k_features(const double *__restrict__ t, 
             qj = off[row + xj + 1];
             if (lr == 0) c[1] += qj - qi;
         }
-        const int left = qi - qa, tests = left + (qb - qj);
-        for (int s = lr; s < tests; s += kFeatTests * lpr) {
-            double2 p[kFeatTests];
-#pragma unroll
-            for (int u = 0; u < kFeatTests; ++u) {
-                const int su = min(s + u * lpr, tests - 1);
-                p[u] = cxy[su < left ? qa + su : qj + (su - left)];
-            }
-#pragma unroll
-            for (int u = 0; u < kFeatTests; ++u) {
-                const double dx = p[u].x - xm, dy = p[u].y - ym;
-                c[1] += dx * dx + dy * dy < r1 && s + u * lpr < tests;
-            }
-        }
+        la = qa;
+        lb = qi;
+        ra = qj;
+        rb = qb;
         // the h disc over all times
         if (dn <= R0 + tol) {
             const double wh = sqrt(fmax(0.0, R0 * R0 - dn * dn)) + tol;
-            const int ha = clampi((int)floor(um - wh), 0, G.nx - 1), hb = clampi((int)floor(um + wh), 0, G.nx - 1);
-            const int q1 = off[row + hb + 1];
-            for (int q = off[row + ha] + lr; q < q1; q += kFeatTests * lpr) {
-                double2 p[kFeatTests];
-#pragma unroll
-                for (int u = 0; u < kFeatTests; ++u) p[u] = cxy[min(q + u * lpr, q1 - 1)];
-#pragma unroll
-                for (int u = 0; u < kFeatTests; ++u) {
-                    const double dx = p[u].x - xm, dy = p[u].y - ym;
-                    c[0] += dx * dx + dy * dy < r0 && q + u * lpr < q1;
-                }
-            }
+            const int x0 = clampi((int)floor(um - wh), 0, G.nx - 1), x1 = clampi((int)floor(um + wh), 0, G.nx - 1);
+            ha = off[row + x0];
+            hb = off[row + x1 + 1];
         }
     }
+    // the candidates of a row, by the whole wavefront: a range's start is uniform, so
+    // that a test is a load, a distance and a bit of a ballot
+    int n0 = 0, n1 = 0;
+    const auto within = [&](int qa, int qb, double lim) {
+        int cnt = 0;
+        for (int q = qa; q < qb; q += kFeatTests * HK_WAVE) {
+            const double2 *__restrict__ p0 = cxy + q;
+            double2 p[kFeatTests];
+#pragma unroll
+            for (int u = 0; u < kFeatTests; ++u)
+                if (u == 0 || q + u * HK_WAVE < qb) p[u] = p0[min(u * HK_WAVE + lane, qb - q - 1)];
+#pragma unroll
+            for (int u = 0; u < kFeatTests; ++u) {
+                if (u != 0 && q + u * HK_WAVE >= qb) break;
+                const double dx = p[u].x - xm, dy = p[u].y - ym;
+                cnt += (int)__popcll(__ballot(dx * dx + dy * dy < lim && u * HK_WAVE + lane < qb - q));
+            }
+        }
+        return cnt;
+    };
+    for (int y = 0; y <= y_hi - y_lo; ++y) {
+        const int l = y * lpr;
+        n1 += within(__builtin_amdgcn_readlane(la, l), __builtin_amdgcn_readlane(lb, l), r1);
+        n1 += within(__builtin_amdgcn_readlane(ra, l), __builtin_amdgcn_readlane(rb, l), r1);
+        n0 += within(__builtin_amdgcn_readlane(ha, l), __builtin_amdgcn_readlane(hb, l), r0);
+    }
     // the time windows: one candidate, and its exponent in feature 8 (-inf: no term)
-    const auto window = [&](int q) {
-        const double2 p = cxy[q];
+    const auto window_at = [&](const double2 p, double tq) {
         const double dx = p.x - xm, dy = p.y - ym;
         const double d2 = dx * dx + dy * dy;
-        const double dt = ct[q] - tm;
+        const double dt = tq - tm;
         const bool prev = dt >= -w1 && dt < 0.0, next = dt > 0.0 && dt <= w1, next3 = dt > 0.0 && dt <= w3;
         if (!(d2 < r1)) return -(double)INFINITY;
         c[6] += prev;
@@ -653,8 +683,9 @@ __global__ __launch_bounds__(256) void k_features(const double *__restrict__ t, 
         }
         if (!(dt > 0.0 && dt <= w6)) return -(double)INFINITY;
         c[2] += 1;
-        return -2.0 * omega * dt - d2 * inv_h2;
+        return -2.0 * F.omega * dt - d2 * F.inv_h2;
     };
+    const auto window = [&](int q) { return window_at(cxy[q], ct[q]); };
     // each column's first lpr candidates are loaded together, one per lane (nearly
     // always all of them); their exponents are kept
     double ae[8], amax = -INFINITY;  // largest exponent of feature 8's terms
@@ -663,14 +694,28 @@ __global__ __launch_bounds__(256) void k_features(const double *__restrict__ t, 
     for (int i = 0; i < 8; ++i) {
         cq[i] = __shfl(wq, lane - lr + i);
         cn[i] = __shfl(wn, lane - lr + i);
-        ae[i] = lr < cn[i] ? window(cq[i] + lr) : -INFINITY;
-        amax = fmax(amax, ae[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < 8; i += kFeatWindows) {
+        double2 p[kFeatWindows];
+        double tq[kFeatWindows];
+#pragma unroll
+        for (int u = 0; u < kFeatWindows; ++u) {
+            const int q = lr < cn[i + u] ? cq[i + u] + lr : 0;
+            p[u] = cxy[q];
+            tq[u] = ct[q];
+        }
+#pragma unroll
+        for (int u = 0; u < kFeatWindows; ++u) {
+            ae[i + u] = lr < cn[i + u] ? window_at(p[u], tq[u]) : -INFINITY;
+            amax = fmax(amax, ae[i + u]);
+        }
     }
 #pragma unroll
     for (int i = 0; i < 8; ++i)
         for (int s = lr + lpr; s < cn[i]; s += lpr) amax = fmax(amax, window(cq[i] + s));
 #pragma unroll
-    for (int a = 0; a < 8; ++a) {
+    for (int a = 1; a < 8; ++a) {
 #pragma unroll
         for (int o = 1; o < HK_WAVE; o <<= 1) c[a] += __shfl_xor(c[a], o);
     }
@@ -691,7 +736,7 @@ __global__ __launch_bounds__(256) void k_features(const double *__restrict__ t, 
                 const double dx = p.x - xm, dy = p.y - ym;
                 const double d2 = dx * dx + dy * dy;
                 const double dt = ct[q] - tm;
-                if (d2 < r1 && dt > 0.0 && dt <= w6) ksum += term(-2.0 * omega * dt - d2 * inv_h2);
+                if (d2 < r1 && dt > 0.0 && dt <= w6) ksum += term(-2.0 * F.omega * dt - d2 * F.inv_h2);
             }
         }
 #pragma unroll
@@ -699,8 +744,8 @@ __global__ __launch_bounds__(256) void k_features(const double *__restrict__ t, 
     }
     // lane a forms feature a (the event itself is inside every disc)
     if (lane >= MLP_IN) return;
-    int cnt = lane < 2 ? c[0] - 1 : c[2];
-    if (lane == 1) cnt = c[1] - 1;
+    int cnt = lane < 2 ? n0 - 1 : c[2];
+    if (lane == 1) cnt = c[1] + n1 - 1;
 #pragma unroll
     for (int a = 3; a < 8; ++a)
         if (lane == a) cnt = c[a];
@@ -909,7 +954,7 @@ extern "C" hawkes_status hawkes_features(hawkes_plan p, const hawkes_hyper *hy, 
     double *ct = (double *)(cxy + n);
     if (lds) {
         hipLaunchKernelGGL(k_cell_hist, dim3(G.nb), dim3(kFeatThreads), 0, stream, d_xy, p->perm, n, G, off, rest);
-        hipLaunchKernelGGL(k_cell_off, dim3(nblk(cells, kFeatGroup)), dim3(kFeatGroup), 0, stream, rest, n, G, off);
+        hipLaunchKernelGGL(k_cell_off, dim3(nblk(cells, kFeatGroup)), dim3(kFeatOffWaves * HK_WAVE), 0, stream, rest, n, G, off);
         hipLaunchKernelGGL(k_cell_place, dim3(G.nb), dim3(kFeatThreads), 0, stream, d_t, d_xy, p->perm, n, G, off, ct,
                            cxy);
     } else {
@@ -925,8 +970,11 @@ extern "C" hawkes_status hawkes_features(hawkes_plan p, const hawkes_hyper *hy, 
     const int64_t *cidx;
     const int *pos, *slot;
     hk_subset_view(p, &m, &cidx, &pos, &slot);
-    hipLaunchKernelGGL(k_features, dim3(nblk(m * HK_WAVE, 256)), dim3(256), 0, stream, d_t, d_xy, cidx, pos, slot,
-                       p->g, p->ts, d_z, m, n, p->t0, p->t1, hy->h, hy->omega, G, off, ct, cxy, d_feat);
+    const double h3 = 3.0 * hy->h, inv_s = 1.0 / G.s;
+    const FeatConst F{hy->h * hy->h,  h3 * h3, 1.0 / hy->omega, 3.0 / hy->omega, 6.0 / hy->omega, 1.0 / (hy->h * hy->h),
+                      inv_s, hy->h * inv_s, h3 * inv_s, hy->omega};
+    hipLaunchKernelGGL(k_features, dim3((unsigned)m), dim3(HK_WAVE), 0, stream, d_t, d_xy, cidx, pos, slot,
+                       p->g, p->ts, d_z, m, n, p->t0, p->t1, F, G, off, ct, cxy, d_feat);
     HK_CHECK(hipGetLastError());
     return HAWKES_OK;
 }
