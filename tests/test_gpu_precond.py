@@ -320,3 +320,35 @@ def test_features_over_cell_sizes_match_oracle(gpu, n, h):
     torch.cuda.synchronize()
     ref = ofeat.features(es.t, es.x, es.y, sub, z[:200], es.hyper, es.t0, gx0, gy0)
     np.testing.assert_allclose(feat.cpu().numpy()[:200], ref, rtol=1e-6, atol=1e-6)
+
+
+@pytest.mark.parametrize("n", [2, 63, 64, 65, 130, 512, 513, 1100])
+def test_features_of_long_ranges_match_oracle(gpu, n):
+    """Every other event in a cell or two on the 3h circle of the free ones (and a
+    few on their h circle): ranges of candidates around a wavefront's 64 and its
+    8 x 64 loads in flight, and time windows that hold most of them.  Counts are
+    integers: their log1p agrees to FP32 rounding."""
+    import torch
+
+    from paper_2103_03348_amd import _lib
+
+    h = 0.3
+    es = synth.small(n, seed=n, t_end=6.0, ties=n // 10, all_free=False)
+    rng = np.random.default_rng(n)
+    r = h * np.where(rng.random(n) < 0.9, 3.0, 1.0) * (1.0 + 0.02 * rng.standard_normal(n))
+    a = 0.1 * rng.standard_normal(n)
+    es.x[:], es.y[:] = 5.0 + r * np.cos(a), 5.0 + r * np.sin(a)
+    free = es.subset[:: max(1, es.subset.shape[0] // 8)]
+    es.x[free], es.y[free] = 5.0, 5.0
+    es.hyper = es.hyper[:5] + (h,)
+    plan = _plan_with_subset(es)
+    z = np.log(es.theta[es.subset])
+    gx0, gy0 = float(es.x.min()) - 1e-9, float(es.y.min()) - 1e-9
+    feat = torch.empty((es.subset.shape[0], 12), dtype=torch.float32, device="cuda:0")
+    hy = _lib.Hyper.of(es.hyper)
+    dt, dxy, dz = _t(es.t), _t(np.stack([es.x, es.y], 1)), _t(z)
+    _lib.check(_lib.lib().hawkes_features(plan.handle, ctypes.byref(hy), _lib.ptr(dt), _lib.ptr(dxy), _lib.ptr(dz),
+                                          gx0, gy0, _lib.ptr(feat), _lib.stream_handle()), "features")
+    torch.cuda.synchronize()
+    ref = ofeat.features(es.t, es.x, es.y, es.subset, z, es.hyper, es.t0, gx0, gy0)
+    np.testing.assert_allclose(feat.cpu().numpy(), ref, rtol=1e-6, atol=1e-6)
