@@ -58,6 +58,7 @@ struct hk_subset {
     int nq;              // subset chunks: mpad / HK_WAVE
     // cached static part
     bool static_valid;
+    bool sum_static;     // the static part's integral term is still in parts (p->blockpart)
     hawkes_hyper static_hyper;
     double *lam_static;  // [npad]
     double *Lam_static;  // [1] integral term of the fixed-rate events + background
@@ -73,7 +74,6 @@ struct hk_subset {
     double *lw;          // [npad] log2(c_e / lambda_i) (HK_EXP_FLOOR on padding)
     double *colG;        // [n_items][2][HK_WAVE]
     double *gsub;        // [mpad] Eq. 4 on the subset, time order
-    double *hsub;        // [mpad] Eq. 5 on the subset, time order
     double *sums;        // [8] loglik pieces of the last evaluation
     // HMC state
     double *z0, *p;      // [m] slot order
@@ -296,9 +296,9 @@ __global__ __launch_bounds__(SUB_STATIC_WAVES * HK_WAVE) void k_sub_static(
     if (lane == 0) blockpart[blockIdx.x] = lam_part;
 }
 
-// One wavefront: the chunks' sums, each lane's share by a Neumaier sum, then a
+// By one wavefront: the chunks' sums, each lane's share by a Neumaier sum, then a
 // butterfly that carries the corrections (fixed order).
-__global__ __launch_bounds__(HK_WAVE) void k_sum_blocks(const double *__restrict__ part, int nb, double *__restrict__ out) {
+__device__ __forceinline__ void sum_blocks(const double *__restrict__ part, int nb, double *__restrict__ out) {
     double s = 0.0, c = 0.0;
     const auto add = [&](double v) {
         const double t = s + v;
@@ -377,14 +377,20 @@ __global__ void k_sub_offset(const double *__restrict__ ts, const int *__restric
 // log theta_k from it into z_out), and the subset entries of this evaluation in
 // time order: pre-scaled coordinates, times, the rate with the split time factor of its
 // 64-entry chunk, the chunk's split flag and step factor.  One wavefront per
-// chunk (the grid covers mpad exactly).
+// chunk (the grid covers mpad exactly).  With nstatic, a block more adds the parts of
+// the static part's integral term that k_sub_static has just left (a launch of
+// its own cost each change of hyperparameters 5.5 us).
 __global__ __launch_bounds__(256) void k_sub_theta(
     const double *__restrict__ z, const double *__restrict__ off, const int *__restrict__ slot,
     const int64_t *__restrict__ cidx, int64_t m, const int *__restrict__ pos, const double *__restrict__ ts,
     const double *__restrict__ xs, const double *__restrict__ ys, const PairConst kc, float *__restrict__ tv,
     double2 *__restrict__ sxy, double *__restrict__ sts, int *__restrict__ qwide, double *__restrict__ qstep,
     double *__restrict__ theta_full, const double *__restrict__ theta_in, double *__restrict__ z_out,
-    const SubStart st) {
+    const SubStart st, const double *__restrict__ static_part, int nstatic, double *__restrict__ Lam_static) {
+    if (nstatic > 0 && blockIdx.x == gridDim.x - 1) {
+        if (threadIdx.x < HK_WAVE) sum_blocks(static_part, nstatic, Lam_static);
+        return;
+    }
     const int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     const int lane = threadIdx.x & (HK_WAVE - 1);
     const int64_t r0 = r - lane;  // the chunk's first entry
@@ -980,7 +986,7 @@ template <bool UPD>
 __global__ __launch_bounds__(SUB_FIN_WAVES * HK_WAVE) void k_sub_colfin(
     const int *__restrict__ item0, const int *__restrict__ nseg, const double *__restrict__ colG,
     const double *__restrict__ a, int64_t m, const FinConst fc, bool with_h, double *__restrict__ gsub,
-    double *__restrict__ hsub, const SubUpd u) {
+    const int64_t *__restrict__ cidx, const SubOut o, const SubUpd u) {
     __shared__ double part[SUB_FIN_WAVES][2][HK_WAVE];
     const int q = blockIdx.x, lane = threadIdx.x & (HK_WAVE - 1);
     const int wq = __builtin_amdgcn_readfirstlane(threadIdx.x / HK_WAVE);
@@ -991,9 +997,16 @@ __global__ __launch_bounds__(SUB_FIN_WAVES * HK_WAVE) void k_sub_colfin(
     // partial-sum reads; each slot belongs to one entry, so no other thread
     // writes them in between
     double ar = 0.0, zk = 0.0, offk = 0.0, pvk = 0.0, pk0 = 0.0, massk = 1.0, dts = 0.0;
+    double th = 0.0, prec = 0.0;
     int k = 0, wide = 1;
     if (fin) {
         ar = a[r];
+        if (!UPD) k = u.slot[r];
+        if (!UPD && o.theta) {
+            th = o.theta[cidx[k]];
+            prec = hk_prior_prec(o.pdiag, k, o.inv_s2);
+            if (o.mass) massk = o.mass[k];
+        }
         if (UPD) {
             k = u.slot[r];
             zk = u.z[k];
@@ -1037,7 +1050,15 @@ __global__ __launch_bounds__(SUB_FIN_WAVES * HK_WAVE) void k_sub_colfin(
     }
     const double g = Gs * fc.corr - ar;
     gsub[r] = g;
-    if (with_h) hsub[r] = Hs * fc.corr * fc.corr;
+    if (!UPD) {
+        const double h = Hs * fc.corr * fc.corr;
+        if (o.g) o.g[k] = g;
+        if (o.h) o.h[k] = h;
+        const double c = th * th * h - th * g;
+        if (o.curv) o.curv[k] = c + prec;
+        if (o.log_h) o.log_h[k] = (float)log(fmax(h, HK_LOGH_FLOOR));
+        if (o.mass) o.mass[k] = (o.count * massk + (fmax(c, 0.0) + prec)) / (o.count + 1.0);
+    }
     if (UPD) {
         const double gz = exp(u.off ? zk + offk : zk) * g - pvk * u.inv_s2;
         const double pk = pk0 + u.a_p * gz;
@@ -1049,17 +1070,6 @@ __global__ __launch_bounds__(SUB_FIN_WAVES * HK_WAVE) void k_sub_colfin(
             u.tv[r] = (float)exp(wide ? ze : ze + u.omega * dts);
         }
     }
-}
-
-// Scatter the subset results to the caller's slot order.
-__global__ void k_sub_scatter(const int *__restrict__ slot, int64_t m, const double *__restrict__ gsub,
-                              const double *__restrict__ hsub, double *__restrict__ g_out,
-                              double *__restrict__ h_out) {
-    const int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (r >= m) return;
-    const int k = slot[r];
-    if (g_out) g_out[k] = gsub[r];
-    if (h_out) h_out[k] = hsub[r];
 }
 
 // Sums over the subset in fixed order, one block per ENERGY_THREADS entries
@@ -1119,6 +1129,40 @@ __global__ __launch_bounds__(HK_WAVE) void k_sub_loglik(const double *__restrict
                                                        double *__restrict__ loglik) {
     const double ll = energy_sum(parts, blocks, 0) - Lam_static[0] - energy_sum(parts, blocks, 1);
     if (threadIdx.x == 0) loglik[0] = ll;
+}
+
+// The log-likelihood alone for up to LOGLIK_ONE_MAX entries: one block adds
+// everything, 5.5 us for 1,610 entries, 9.9 for 6,874, 18.2 for 16,000; k_sub_energy
+// and k_sub_loglik, a chain of loads each, take some 10.5 and a launch more at any of
+// these sizes.
+constexpr int LOGLIK_ONE_THREADS = 1024;
+constexpr int64_t LOGLIK_ONE_MAX = 8192;
+__global__ __launch_bounds__(LOGLIK_ONE_THREADS) void k_sub_loglik_one(
+    const double *__restrict__ loglam_part, int nb, const double *__restrict__ z, const double *__restrict__ off,
+    const int *__restrict__ slot, const double *__restrict__ a, int64_t m, const double *__restrict__ Lam_static,
+    double *__restrict__ loglik) {
+    __shared__ double sh[2][LOGLIK_ONE_THREADS / HK_WAVE];
+    const int lane = threadIdx.x & (HK_WAVE - 1), w = threadIdx.x / HK_WAVE;
+    double s = 0.0, v = 0.0;
+#pragma unroll 4
+    for (int b = threadIdx.x; b < nb; b += LOGLIK_ONE_THREADS) s += loglam_part[b];
+#pragma unroll 2
+    for (int64_t r = threadIdx.x; r < m; r += LOGLIK_ONE_THREADS) v += exp(zeff(z, off, slot[r])) * a[r];
+    for (int o = 32; o > 0; o >>= 1) {
+        s += __shfl_xor(s, o);
+        v += __shfl_xor(v, o);
+    }
+    if (lane == 0) {
+        sh[0][w] = s;
+        sh[1][w] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int k = 1; k < LOGLIK_ONE_THREADS / HK_WAVE; ++k) {
+        s += sh[0][k];
+        v += sh[1][k];
+    }
+    loglik[0] = s - Lam_static[0] - v;
 }
 
 // Accept or reject, every block deciding alike from the energies' parts (start,
@@ -1193,7 +1237,7 @@ void hk_subset_free(hawkes_plan p) {
     hk_subset *s = p->sub;
     if (!s) return;
     void *ptrs[] = {s->pos, s->slot, s->cidx, s->cnt, s->ritems, s->ritem0, s->rnseg, s->xpart, s->items, s->item0, s->nseg,
-                    s->member, s->lam_static, s->Lam_static, s->a, s->tv, s->sxy, s->sts, s->qwide, s->qstep, s->lw, s->colG, s->gsub, s->hsub, s->sums, s->z0, s->p, s->off, s->vz, s->scal, s->quad,
+                    s->member, s->lam_static, s->Lam_static, s->a, s->tv, s->sxy, s->sts, s->qwide, s->qstep, s->lw, s->colG, s->gsub, s->sums, s->z0, s->p, s->off, s->vz, s->scal, s->quad,
                     s->grid};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
@@ -1335,7 +1379,6 @@ extern "C" hawkes_status hawkes_plan_set_subset(hawkes_plan p, int64_t m, const 
     SC(dalloc(&s->lw, p->npad));
     SC(dalloc(&s->colG, (size_t)s->n_items * 2 * HK_WAVE));
     SC(dalloc(&s->gsub, s->mpad));
-    SC(dalloc(&s->hsub, s->mpad));
     SC(dalloc(&s->sums, 8));
     SC(dalloc(&s->z0, m));
     SC(dalloc(&s->p, m));
@@ -1344,7 +1387,7 @@ extern "C" hawkes_status hawkes_plan_set_subset(hawkes_plan p, int64_t m, const 
     SC(dalloc(&s->scal, 8 * (size_t)nblk(m, ENERGY_THREADS)));
     SC(dalloc(&s->quad, 1));
 #undef SC
-    s->static_valid = false;
+    s->static_valid = s->sum_static = false;
     return HAWKES_OK;
 }
 
@@ -1356,7 +1399,8 @@ bool same_hyper(const hawkes_hyper &a, const hawkes_hyper &b) {
 }
 
 // Static part for (hyper, fixed rates) -- recomputed when the hyperparameters
-// change or the caller asks.
+// change or the caller asks.  Its integral term's parts are added by the row half
+// that follows (sub_rows).
 hawkes_status ensure_static(hawkes_plan p, const hawkes_hyper *hy, const double *d_theta, bool force,
                             const PairConst &kc, const FinConst &fc, hipStream_t stream) {
     hk_subset *s = p->sub;
@@ -1365,10 +1409,10 @@ hawkes_status ensure_static(hawkes_plan p, const hawkes_hyper *hy, const double 
     hipLaunchKernelGGL(k_sub_static, dim3(p->nchunks), dim3(SUB_STATIC_WAVES * HK_WAVE), 0, stream, p->ts, p->xs,
                        p->ys, p->g, d_theta, p->perm, p->theta_s, p->n, p->ntiles, p->row_item0, p->row_nseg,
                        p->rowpart, p->colpart, fc, s->pos, s->m, s->mpad, s->a, s->lam_static, p->blockpart);
-    hipLaunchKernelGGL(k_sum_blocks, dim3(1), dim3(HK_WAVE), 0, stream, p->blockpart, p->nchunks, s->Lam_static);
     HK_CHECK(hipGetLastError());
     s->static_hyper = *hy;
     s->static_valid = true;
+    s->sum_static = true;
     return HAWKES_OK;
 }
 
@@ -1384,13 +1428,17 @@ static void sub_rows(hawkes_plan p, SubFrom from, double *z, const double *off, 
                      const SubStart &start = SubStart{}) {
     hk_subset *s = p->sub;
     p->epoch += 1;  // p->lam is overwritten below
-    if (from != SUB_STAGED)
-        hipLaunchKernelGGL(k_sub_theta, dim3((unsigned)(s->mpad / 256)), dim3(256), 0, stream,
+    if (from != SUB_STAGED) {
+        const int nstatic = s->sum_static ? p->nchunks : 0;
+        s->sum_static = false;
+        hipLaunchKernelGGL(k_sub_theta, dim3((unsigned)(s->mpad / 256) + (nstatic > 0)), dim3(256), 0, stream,
                            from == SUB_FROM_Z ? z : (double *)nullptr, off, s->slot, s->cidx, s->m, s->pos, p->ts,
                            p->xs, p->ys, kc, s->tv, s->sxy, s->sts, s->qwide, s->qstep,
                            from == SUB_FROM_Z ? theta : (double *)nullptr,
                            from == SUB_FROM_THETA ? theta : (double *)nullptr,
-                           from == SUB_FROM_THETA ? z : (double *)nullptr, start);
+                           from == SUB_FROM_THETA ? z : (double *)nullptr, start, p->blockpart, nstatic,
+                           s->Lam_static);
+    }
     if (s->n_ritems > 0) {
 #define HK_SUBITEMS(T, LOW, TD)                                                                                   \
     hipLaunchKernelGGL(k_sub_items<T>, dim3(s->n_ritems + (LOW)), dim3(HK_WAVE), 0, stream, p->ts, p->xs, p->ys,   \
@@ -1415,6 +1463,11 @@ static void sub_rows(hawkes_plan p, SubFrom from, double *z, const double *off, 
 // Eq. 1 after a row half at z.
 static void sub_loglik(hawkes_plan p, const double *z, const double *off, double *d_loglik, hipStream_t stream) {
     hk_subset *s = p->sub;
+    if (s->m <= LOGLIK_ONE_MAX) {
+        hipLaunchKernelGGL(k_sub_loglik_one, dim3(1), dim3(LOGLIK_ONE_THREADS), 0, stream, p->blockpart, p->nchunks, z,
+                           off, s->slot, s->a, s->m, s->Lam_static, d_loglik);
+        return;
+    }
     const unsigned nb = nblk(s->m, ENERGY_THREADS);
     hipLaunchKernelGGL(k_sub_energy, dim3(nb), dim3(ENERGY_THREADS), 0, stream, p->blockpart, p->nchunks, z, off,
                        (const double *)nullptr, (const double *)nullptr, s->slot, s->a, s->m, (const double *)nullptr, 0,
@@ -1442,19 +1495,20 @@ static void sub_col_pass(hawkes_plan p, bool with_h, const PairConst &kc, hipStr
 #undef HK_SUBCOL
 }
 
-static void sub_col_fin(hawkes_plan p, bool with_h, const FinConst &fc, const SubUpd *upd, hipStream_t stream) {
+static void sub_col_fin(hawkes_plan p, bool with_h, const FinConst &fc, const SubUpd *upd, const SubOut &out,
+                        hipStream_t stream) {
     hk_subset *s = p->sub;
-    if (upd)
-        hipLaunchKernelGGL(k_sub_colfin<true>, dim3(s->nq), dim3(SUB_FIN_WAVES * HK_WAVE), 0, stream, s->item0,
-                           s->nseg, s->colG, s->a, s->m, fc, with_h, s->gsub, s->hsub, *upd);
-    else
-        hipLaunchKernelGGL(k_sub_colfin<false>, dim3(s->nq), dim3(SUB_FIN_WAVES * HK_WAVE), 0, stream, s->item0,
-                           s->nseg, s->colG, s->a, s->m, fc, with_h, s->gsub, s->hsub, SubUpd{});
+    SubUpd u{};
+    u.slot = s->slot;
+    hipLaunchKernelGGL((upd ? k_sub_colfin<true> : k_sub_colfin<false>), dim3(s->nq), dim3(SUB_FIN_WAVES * HK_WAVE), 0,
+                       stream, s->item0, s->nseg, s->colG, s->a, s->m, fc, with_h, s->gsub, s->cidx, out,
+                       upd ? *upd : u);
 }
 
-static void sub_cols(hawkes_plan p, bool with_h, const PairConst &kc, const FinConst &fc, hipStream_t stream) {
+static void sub_cols(hawkes_plan p, bool with_h, const PairConst &kc, const FinConst &fc, const SubOut &out,
+                     hipStream_t stream) {
     sub_col_pass(p, with_h, kc, stream);
-    sub_col_fin(p, with_h, fc, nullptr, stream);
+    sub_col_fin(p, with_h, fc, nullptr, out, stream);
 }
 
 // z_k = log theta_{idx_k} - beta t_{idx_k} (slot order)
@@ -1508,9 +1562,10 @@ extern "C" hawkes_status hawkes_subset_grad(hawkes_plan p, const hawkes_hyper *h
     // z = log theta on the subset (the rates are taken from d_theta as given)
     sub_rows(p, SUB_FROM_THETA, s->z0, nullptr, const_cast<double *>(d_theta), kc, fc, stream);
     if (d_grad_sub || d_negH_sub) {
-        sub_cols(p, d_negH_sub != nullptr, kc, fc, stream);
-        hipLaunchKernelGGL(k_sub_scatter, dim3(nblk(s->m, 256)), dim3(256), 0, stream, s->slot, s->m, s->gsub,
-                           s->hsub, d_grad_sub, d_negH_sub);
+        SubOut out{};
+        out.g = d_grad_sub;
+        out.h = d_negH_sub;
+        sub_cols(p, d_negH_sub != nullptr, kc, fc, out, stream);
     }
     if (d_loglik) sub_loglik(p, s->z0, nullptr, d_loglik, stream);
     HK_CHECK(hipGetLastError());
@@ -1561,7 +1616,7 @@ extern "C" hawkes_status hmc_step(hawkes_plan p, const hawkes_hyper *hyper, hawk
     // step, which rides on the column pass)
     sub_col_pass(p, false, kc, stream, td);
     energy(e0);
-    sub_col_fin(p, false, fc, &upd, stream);
+    sub_col_fin(p, false, fc, &upd, SubOut{}, stream);
     for (int l = 0; l < a->L; ++l) {
         // evaluation at the drifted position, then a full kick and drift, or the
         // closing half kick after the last one
@@ -1571,7 +1626,7 @@ extern "C" hawkes_status hmc_step(hawkes_plan p, const hawkes_hyper *hyper, hawk
         upd.a_p = last ? 0.5 * a->eps : a->eps;
         upd.a_z = last ? 0.0 : a->eps;
         sub_col_pass(p, false, kc, stream, td);
-        sub_col_fin(p, false, fc, &upd, stream);
+        sub_col_fin(p, false, fc, &upd, SubOut{}, stream);
     }
     energy(e1);
     hipLaunchKernelGGL(k_hmc_accept, dim3(nblk(m, ACCEPT_THREADS)), dim3(ACCEPT_THREADS), 0, stream, e0, e1, (int)nb,
@@ -1602,7 +1657,7 @@ extern "C" hawkes_status hawkes_subset_trend_grad(hawkes_plan p, const hawkes_hy
     sub_rows(p, SUB_FROM_Z, const_cast<double *>(d_z), off, d_theta, kc, fc, stream);
     // the log-likelihood alone (a Metropolis-Hastings proposal) needs no column pass
     if (d_grad_z || d_grad_beta) {
-        sub_cols(p, false, kc, fc, stream);
+        sub_cols(p, false, kc, fc, SubOut{}, stream);
         hipLaunchKernelGGL(k_sub_trend_out, dim3(1), dim3(256), 0, stream, s->slot, s->pos, p->ts, s->m, s->gsub, d_z,
                            off, d_grad_z, d_grad_beta);
     }
@@ -1635,7 +1690,7 @@ hawkes_status hk_subset_grid(hawkes_plan p, int64_t cells, hipStream_t stream) {
 int *hk_subset_grid_ptr(hawkes_plan p) { return p->sub->grid; }
 
 hawkes_status hk_subset_exact(hawkes_plan p, const hawkes_hyper *hy, const double *d_theta, hipStream_t stream,
-                              const double **gsub, const double **hsub) {
+                              const SubOut &out) {
     hk_subset *s = p->sub;
     p->last_stream = stream;
     PairConst kc;
@@ -1644,10 +1699,8 @@ hawkes_status hk_subset_exact(hawkes_plan p, const hawkes_hyper *hy, const doubl
     hawkes_status st = ensure_static(p, hy, d_theta, false, kc, fc, stream);
     if (st != HAWKES_OK) return st;
     sub_rows(p, SUB_FROM_THETA, s->z0, nullptr, const_cast<double *>(d_theta), kc, fc, stream);
-    sub_cols(p, true, kc, fc, stream);
+    sub_cols(p, true, kc, fc, out, stream);
     HK_CHECK(hipGetLastError());
-    *gsub = s->gsub;
-    *hsub = s->hsub;
     return HAWKES_OK;
 }
 

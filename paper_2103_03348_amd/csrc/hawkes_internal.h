@@ -224,10 +224,32 @@ __device__ __forceinline__ void hk_wave_sync() {
 }
 
 bool hk_hyper_ok(const hawkes_hyper *h);
-// Eq. 4 and Eq. 5 on the subset at the rates d_theta (O(N M) path); device
-// pointers to the results in time order
+// Where the column finalisation of a subset evaluation leaves its results, slot
+// order, each NULL or zero where not wanted: Eq. 4 and Eq. 5 themselves, and what
+// the preconditioner forms from them at the rates theta (caller order).  In z
+// (theta_k = exp(z_k + beta t_k), so d theta_k / d z_k = theta_k) the
+// log-posterior's curvature on the diagonal is
+//   c_k = theta_k^2 H_k - theta_k g_k + P_kk
+// with g, H Eq. 4 and Eq. 5 on the subset and P the prior's precision
+// diagonal: 1/sigma^2 (iid prior, pdiag NULL) or (V^{-1})_kk / sigma^2 (Eq. 2).
+struct SubOut {
+    double *g, *h;
+    const double *theta;
+    const double *pdiag;
+    double inv_s2;
+    double *curv;        // c_k
+    float *log_h;        // log max(H_k, HK_LOGH_FLOOR), the learned preconditioner's target
+    double *mass;        // mass <- (count mass + max(theta^2 H - theta g, 0) + P_kk) / (count + 1)
+    double count;
+};
+
+__device__ __forceinline__ double hk_prior_prec(const double *__restrict__ pdiag, int k, double inv_s2) {
+    return pdiag ? pdiag[k] * inv_s2 : inv_s2;
+}
+
+// Eq. 4 and Eq. 5 on the subset at the rates d_theta (O(N M) path) to `out`
 hawkes_status hk_subset_exact(hawkes_plan p, const hawkes_hyper *hy, const double *d_theta, hipStream_t stream,
-                              const double **gsub, const double **hsub);
+                              const SubOut &out);
 void hk_make_consts(const hawkes_plan p, const hawkes_hyper *hy, PairConst *kc, FinConst *fc);
 // Log-likelihood-only row pass (no moments) at the rates d_theta with the
 // excitation of the sorted events that `member` marks left out; leaves the sorted

@@ -621,3 +621,23 @@ def test_subset_row_forms_match_oracle(gpu, m, t_end, cutoff):
         if want_h:
             assert h_rel_all(h, hi) < 1e-6
     plan.close()
+
+
+@pytest.mark.parametrize("m", [8192, 8193])
+def test_subset_loglik_forms_match_oracle(gpu, m):
+    """The log-likelihood of a large subset by one block (up to 8,192 entries) and
+    by a block per 256 of them, and the static part's integral term, summed beside
+    the staging, after a change of hyperparameters."""
+    import dataclasses
+
+    es = synth.small(8400, seed=84, t_end=900.0, all_free=False)
+    sub = np.sort(np.random.default_rng(m).choice(es.n, m, replace=False)).astype(np.int64)
+    es = dataclasses.replace(es, subset=sub, z=np.log(es.theta[sub]))
+    plan, idx = _setup(es)
+    for hyper in (es.hyper, tuple(1.1 * v for v in es.hyper)):
+        es = dataclasses.replace(es, hyper=hyper)
+        ref = oracle.evaluate_es(es, want=("loglik",))["loglik"]
+        ll, _, _ = _subset_grad(plan, es, es.theta, want_h=False)
+        assert plan.status() == 0
+        assert abs(ll - ref) < 2e-6 * es.n
+    plan.close()
