@@ -1173,15 +1173,18 @@ __global__ __launch_bounds__(COL_BLOCK_WAVES * HK_WAVE) void k_col_block(
     if (negH_theta) negH_theta[dst] = Hs * fc.corr * fc.corr;
 }
 
-// Column finalisation, one block per 64-event chunk: the HK_FIN_WAVES
-// wavefronts split the column pieces round robin (reads in flight), then the
-// first combines them in a fixed order.
+// Column finalisation, one block per 64-event chunk: its wavefronts split the
+// column pieces round robin (reads in flight), then the first combines them in a
+// fixed order.  Bound by the latency of the reads: with sixteen wavefronts an
+// evaluation of N = 8,000 events takes 91.7 us, with eight 93.9 (23,422: 359.5 /
+// 361.5).
+constexpr int HK_COLFIN_WAVES = 16;
 //
 // With `totals` set, one block more (the last) reduces the row finalisation's
 // block partials to the scalar results instead (the work of k_fin2, whose
 // inputs are complete once the column pass runs): one launch fewer per
 // evaluation.
-__global__ __launch_bounds__(HK_FIN_WAVES * HK_WAVE) void k_colfin(const int *__restrict__ perm, int64_t n,
+__global__ __launch_bounds__(HK_COLFIN_WAVES * HK_WAVE) void k_colfin(const int *__restrict__ perm, int64_t n,
                                                 const int *__restrict__ col_item0, const int *__restrict__ col_nseg,
                                                 const double *__restrict__ colG, const double *__restrict__ a,
                                                 const FinConst fc, double *__restrict__ grad_theta,
@@ -1189,7 +1192,7 @@ __global__ __launch_bounds__(HK_FIN_WAVES * HK_WAVE) void k_colfin(const int *__
                                                 const double *__restrict__ blockpart, int nfin,
                                                 double *__restrict__ loglik, double *__restrict__ grad_hyper,
                                                 double *__restrict__ negH_hyper, int *__restrict__ status) {
-    __shared__ double part[HK_FIN_WAVES][2][HK_WAVE];
+    __shared__ double part[HK_COLFIN_WAVES][2][HK_WAVE];
     if (totals && blockIdx.x == gridDim.x - 1) {
         __shared__ double tot[HK_NSUM];
         fin_totals(blockpart, nfin, loglik, grad_hyper, negH_hyper, status, tot);
@@ -1201,7 +1204,7 @@ __global__ __launch_bounds__(HK_FIN_WAVES * HK_WAVE) void k_colfin(const int *__
     const int it0 = col_item0[J], ns = col_nseg[J];
     double G = 0.0, H = 0.0;
     #pragma unroll 2
-    for (int sg = wv; sg < ns; sg += HK_FIN_WAVES) {
+    for (int sg = wv; sg < ns; sg += HK_COLFIN_WAVES) {
         const double *cg = colG + (int64_t)(it0 + sg) * 2 * HK_TILE + r;
         G += cg[0];
         if (negH_theta) H += cg[HK_TILE];
@@ -1211,7 +1214,7 @@ __global__ __launch_bounds__(HK_FIN_WAVES * HK_WAVE) void k_colfin(const int *__
     __syncthreads();
     if (wv != 0 || j >= n) return;
     double Gs = part[0][0][lane], Hs = part[0][1][lane];
-    for (int q = 1; q < HK_FIN_WAVES; ++q) {
+    for (int q = 1; q < HK_COLFIN_WAVES; ++q) {
         Gs += part[q][0][lane];
         Hs += part[q][1][lane];
     }
@@ -1333,7 +1336,7 @@ static void launch_col(hawkes_plan p, const PairConst &kc, const FinConst &fc, d
     }
 #undef HK_COL
     hk_prof_mark(p, HK_PROF_COL, false, stream);
-    hipLaunchKernelGGL(k_colfin, dim3(p->nchunks + (totals ? 1 : 0)), dim3(HK_FIN_WAVES * HK_WAVE), 0, stream,
+    hipLaunchKernelGGL(k_colfin, dim3(p->nchunks + (totals ? 1 : 0)), dim3(HK_COLFIN_WAVES * HK_WAVE), 0, stream,
                        p->perm, p->n, p->col_item0, p->col_nseg, p->colG, p->a, fc, d_grad_theta, d_negH_theta,
                        totals ? 1 : 0, p->blockpart, p->nchunks, d_loglik, d_grad_hyper, d_negH_hyper, p->status);
 }
@@ -1420,9 +1423,15 @@ void hk_launch_row_loglik(hawkes_plan p, const PairConst &kc, const double *d_th
 // wavefronts fill a CU of gfx950 at the register footprints of k_row and k_col;
 // two rounds of equal-weight blocks measured faster than one (the hardware
 // dispatcher then evens out the blocks' run-time differences), while more
-// rounds cost more partial-sum traffic than they gain.
+// rounds cost more partial-sum traffic than they gain.  The column pass, whose
+// pieces are shorter in time, takes half as many again (evaluation of N = 23,422
+// events, 16 / 20 / 24 / 32 / 48 blocks: 362.3 / 361.6 / 361.0 / 363.1 / 366.5 us;
+// gradient of 60,000: 1,650 / 1,647 / 1,638 / 1,638 / 1,633).
 #ifndef HK_BLOCKS_PER_CU
 #define HK_BLOCKS_PER_CU 16
+#endif
+#ifndef HK_COL_BLOCKS_PER_CU
+#define HK_COL_BLOCKS_PER_CU 24
 #endif
 
 // From 65,536 (padded) events on, 20 row-pass and 32 column-pass blocks per CU:
@@ -1438,7 +1447,7 @@ int64_t hk_pass_slots(int device, int pass, int64_t npad) {
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus < 1)
         cus = 256;
     if (npad >= HK_LARGE_NPAD) return (int64_t)cus * (pass == 1 ? 32 : 20);
-    return (int64_t)cus * HK_BLOCKS_PER_CU;
+    return (int64_t)cus * (pass == 1 ? HK_COL_BLOCKS_PER_CU : HK_BLOCKS_PER_CU);
 }
 
 extern "C" hawkes_status hawkes_loglik(hawkes_plan p, const hawkes_hyper *hyper, const double *d_theta,
