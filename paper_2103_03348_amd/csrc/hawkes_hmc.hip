@@ -55,6 +55,7 @@ struct hk_subset {
     int n_items;
     hk_item *items;      // (subset chunk, row chunk begin, end, seg)
     int *item0, *nseg;   // per subset chunk
+    int max_nseg;        // largest of them
     int nq;              // subset chunks: mpad / HK_WAVE
     // cached static part
     bool static_valid;
@@ -93,8 +94,9 @@ namespace {
 // chip takes part; partial sums per item are combined in a fixed order
 // afterwards.  Measured on the N = 23,422 HMC iteration (M = 1,610):
 // column items 4096 -> 8192 (one row chunk per item there) 0.616 -> 0.607 ms,
-// 2048 0.623 ms; row items 4096 0.639 ms, 16384 no change (one batch per item
-// already).  The limit on an item's length bounds the last round of wavefronts
+// 2048 0.623 ms (and 16384 at N = 40,000, M = 4,000, where that is one per item:
+// 1.391 -> 1.370 ms, 32768 1.396); row items 4096 0.639 ms, 16384 no change (one
+// batch per item already).  The limit on an item's length bounds the last round of wavefronts
 // (and keeps the few items that still have work under the underflow cutoff
 // short): N = 250,000, with / without the cutoff, ms per iteration: 16 batches
 // 6.96 / 24.56, 8 6.08 / 24.03, 4 6.21 / 24.68.
@@ -102,7 +104,7 @@ namespace {
 #define HK_SUB_ROW_ITEMS 8192
 #endif
 #ifndef HK_SUB_COL_ITEMS
-#define HK_SUB_COL_ITEMS 8192
+#define HK_SUB_COL_ITEMS 16384
 #endif
 constexpr int64_t SUB_ROW_ITEMS = HK_SUB_ROW_ITEMS;
 constexpr int64_t SUB_COL_ITEMS = HK_SUB_COL_ITEMS;
@@ -110,6 +112,12 @@ constexpr int64_t SUB_COL_ITEMS = HK_SUB_COL_ITEMS;
 #define HK_SUB_FIN_WAVES 16
 #endif
 constexpr int SUB_FIN_WAVES = HK_SUB_FIN_WAVES;
+// the column finalisation takes 16 entries per block where some entry has more
+// items than this, a whole chunk of 64 elsewhere
+#ifndef HK_SUB_FIN_SPLIT
+#define HK_SUB_FIN_SPLIT 64
+#endif
+constexpr int SUB_FIN_SPLIT = HK_SUB_FIN_SPLIT;
 // partial-sum loads a finalisation wavefront keeps in flight (16 in the
 // column finalisation measured slower: 4.95 -> 5.7 us at N = 23,422)
 constexpr int SUB_FIN_BATCH = 8;
@@ -979,19 +987,25 @@ struct SubUpd {
     double omega;
 };
 
-// Per 64-entry subset chunk: the SUB_FIN_WAVES wavefronts split the chunk's
-// items round robin, then the first combines them in a fixed order (and, with
-// UPD, applies the leapfrog update to its entries).
-template <bool UPD>
+// Per E subset entries (16 or 64): the lanes of the SUB_FIN_WAVES wavefronts
+// split the items of the entries' chunk round robin, then the first wavefront combines
+// them in a fixed order (and, with UPD, applies the leapfrog update to its entries).
+// Bound by latency and by what one CU reads (an early chunk has an item for each
+// later row chunk, 512 bytes each): with E = 64 a HMC iteration of N = 23,422 (up to
+// 366 items) took 615 us, with 32 596, with 16 580, with 8 585; at N = 3,000 (47)
+// 295 with 64 and 301 with 16.
+template <bool UPD, int E>
 __global__ __launch_bounds__(SUB_FIN_WAVES * HK_WAVE) void k_sub_colfin(
     const int *__restrict__ item0, const int *__restrict__ nseg, const double *__restrict__ colG,
     const double *__restrict__ a, int64_t m, const FinConst fc, bool with_h, double *__restrict__ gsub,
     const int64_t *__restrict__ cidx, const SubOut o, const SubUpd u) {
-    __shared__ double part[SUB_FIN_WAVES][2][HK_WAVE];
-    const int q = blockIdx.x, lane = threadIdx.x & (HK_WAVE - 1);
+    constexpr int STEP = SUB_FIN_WAVES * (HK_WAVE / E);
+    __shared__ double part[SUB_FIN_WAVES][2][E];
+    const int lane = threadIdx.x & (HK_WAVE - 1), e = lane % E;
     const int wq = __builtin_amdgcn_readfirstlane(threadIdx.x / HK_WAVE);
-    const int64_t r = (int64_t)q * HK_WAVE + lane;
-    const bool fin = wq == 0 && r < m;
+    const int64_t r = (int64_t)blockIdx.x * E + e;
+    const int q = (int)((int64_t)blockIdx.x * E / HK_WAVE);
+    const bool fin = wq == 0 && lane < E && r < m;
     // the operands of the finalisation and of the update are fetched before the
     // reduction, so that their latency (a gather through the slot) overlaps the
     // partial-sum reads; each slot belongs to one entry, so no other thread
@@ -1024,23 +1038,30 @@ __global__ __launch_bounds__(SUB_FIN_WAVES * HK_WAVE) void k_sub_colfin(
     const int ns = nseg[q], i0 = item0[q];
     // batches of SUB_FIN_BATCH loads issue together (absent ones read as zero,
     // which adds exactly); the adds keep the items' order
-    for (int base = wq; base < ns; base += SUB_FIN_BATCH * SUB_FIN_WAVES) {
+    for (int base = wq * (HK_WAVE / E) + lane / E; base < ns; base += SUB_FIN_BATCH * STEP) {
         double vg[SUB_FIN_BATCH], vh[SUB_FIN_BATCH];
 #pragma unroll
-        for (int e = 0; e < SUB_FIN_BATCH; ++e) {
-            const int sg = base + e * SUB_FIN_WAVES;
-            const double *cg = colG + (int64_t)(i0 + sg) * 2 * HK_WAVE + lane;
-            vg[e] = sg < ns ? cg[0] : 0.0;
-            vh[e] = with_h && sg < ns ? cg[HK_WAVE] : 0.0;
+        for (int k = 0; k < SUB_FIN_BATCH; ++k) {
+            const int sg = base + k * STEP;
+            const double *cg = colG + (int64_t)(i0 + sg) * 2 * HK_WAVE + r % HK_WAVE;
+            vg[k] = sg < ns ? cg[0] : 0.0;
+            vh[k] = with_h && sg < ns ? cg[HK_WAVE] : 0.0;
         }
 #pragma unroll
-        for (int e = 0; e < SUB_FIN_BATCH; ++e) {
-            G += vg[e];
-            H += vh[e];
+        for (int k = 0; k < SUB_FIN_BATCH; ++k) {
+            G += vg[k];
+            H += vh[k];
         }
     }
-    part[wq][0][lane] = G;
-    part[wq][1][lane] = H;
+#pragma unroll
+    for (int o = E; o < HK_WAVE; o <<= 1) {
+        G += __shfl_xor(G, o);
+        H += __shfl_xor(H, o);
+    }
+    if (lane < E) {
+        part[wq][0][e] = G;
+        part[wq][1][e] = H;
+    }
     __syncthreads();
     if (!fin) return;
     double Gs = part[0][0][lane], Hs = part[0][1][lane];
@@ -1349,6 +1370,7 @@ extern "C" hawkes_status hawkes_plan_set_subset(hawkes_plan p, int64_t m, const 
         nseg[q] = seg;
     }
     for (int q = nq_live; q < s->nq; ++q) item0[q] = (int)items.size();
+    s->max_nseg = *std::max_element(nseg.begin(), nseg.end());
     s->n_items = (int)items.size();
     SC(dalloc(&s->cnt, nch));
     SC(hipMemcpy(s->cnt, cnt.data(), sizeof(int) * nch, hipMemcpyHostToDevice));
@@ -1500,7 +1522,10 @@ static void sub_col_fin(hawkes_plan p, bool with_h, const FinConst &fc, const Su
     hk_subset *s = p->sub;
     SubUpd u{};
     u.slot = s->slot;
-    hipLaunchKernelGGL((upd ? k_sub_colfin<true> : k_sub_colfin<false>), dim3(s->nq), dim3(SUB_FIN_WAVES * HK_WAVE), 0,
+    const bool split = s->max_nseg > SUB_FIN_SPLIT;
+    const auto kern = split ? (upd ? k_sub_colfin<true, 16> : k_sub_colfin<false, 16>)
+                            : (upd ? k_sub_colfin<true, HK_WAVE> : k_sub_colfin<false, HK_WAVE>);
+    hipLaunchKernelGGL(kern, dim3(nblk(s->m, split ? 16 : HK_WAVE)), dim3(SUB_FIN_WAVES * HK_WAVE), 0,
                        stream, s->item0, s->nseg, s->colG, s->a, s->m, fc, with_h, s->gsub, s->cidx, out,
                        upd ? *upd : u);
 }

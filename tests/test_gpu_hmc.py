@@ -641,3 +641,26 @@ def test_subset_loglik_forms_match_oracle(gpu, m):
         assert plan.status() == 0
         assert abs(ll - ref) < 2e-6 * es.n
     plan.close()
+
+
+@pytest.mark.parametrize("n,m", [(4096, 1), (4096, 130), (4097, 1), (4097, 15), (4097, 17), (4097, 130), (9000, 300)])
+def test_subset_column_finalisation_forms_match_oracle(gpu, n, m):
+    """Up to 64 items per entry the column finalisation takes 64 entries per block,
+    beyond (4,097 events and more: 65 row chunks) 16: Eq. 4 and 5 against the oracle
+    around both widths, with the bounds above."""
+    import dataclasses
+
+    es = synth.small(n, seed=n + m, t_end=900.0, ties=8, all_free=False)
+    sub = np.sort(np.random.default_rng(m).choice(es.n // 8, m, replace=False)).astype(np.int64)  # early events
+    es = dataclasses.replace(es, subset=sub, z=np.log(es.theta[sub]))
+    plan, idx = _setup(es)
+    ref = oracle.evaluate_es(es)
+    gi, hi = ref["grad_theta"][sub], ref["negH_theta"][sub]
+    a = es.hyper[3] * (1.0 - np.exp(-es.hyper[4] * (es.t.max() - es.t[sub])))
+    for want_h in (True, False):
+        ll, g, h = _subset_grad(plan, es, es.theta, want_h=want_h)
+        assert plan.status() == 0
+        assert np.max(np.abs(g - gi) / np.maximum(gi + 2 * a, 1e-300)) < 1e-6
+        if want_h:
+            assert h_rel_all(h, hi) < 1e-6
+    plan.close()
