@@ -211,23 +211,32 @@ __device__ __forceinline__ float exp2_split(double e) {
 // time constant biased the log-likelihood-only pass's lambda by about 1e-9.)
 
 // One pair's terms into the accumulators (b: background term, te: theta_j E_ij,
-// ar, ae: spatial exponents of the two kernels in log2 units, dt = t_i - t_j).
-template <int MODE>
+// ar, ae: spatial exponents of the two kernels in log2 units, dt = t_i - t_j),
+// those of the groups SUMS (what only the others need is dropped by the compiler).
+enum { ROW_B0 = 1, ROW_B1 = 2, ROW_B2 = 4, ROW_X = 8, ROW_ALL = 15 };
+// the group of a row slot and of a column slot
+constexpr int row_slot_group(int a) { return a == 0 ? ROW_B0 : a < 3 ? ROW_B1 : a < 5 ? ROW_B2 : ROW_X; }
+
+template <int MODE, int SUMS>
 __device__ __forceinline__ void row_accumulate(float b, float te, float ar, float ae, float dt, float dt2,
                                                float (&blk)[HK_NROW], float (&C)[HK_NCOL], double &B0d,
                                                double &X0c, double *__restrict__ acc0) {
 #pragma clang fp contract(off)
-    const double bd = (double)b;
-    B0d += bd;
-    // the column's FP64 sum: an LDS add into this step's slot (no return value)
-    __hip_atomic_fetch_add(acc0, bd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-    if (MODE >= HK_MODE_GRAD) {
+    if (SUMS & ROW_B0) {
+        const double bd = (double)b;
+        B0d += bd;
+        // the column's FP64 sum: an LDS add into this step's slot (no return value)
+        __hip_atomic_fetch_add(acc0, bd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    }
+    if (MODE >= HK_MODE_GRAD && (SUMS & (ROW_B1 | ROW_B2))) {
         const float p1 = b * ar, p2 = b * dt2;
-        blk[1] += p1;
-        blk[2] += p2;
-        C[1] = rot_next(C[1]) + p1;
-        C[2] = rot_next(C[2]) + p2;
-        if (MODE >= HK_MODE_HESS) {
+        if (SUMS & ROW_B1) {
+            blk[1] += p1;
+            blk[2] += p2;
+            C[1] = rot_next(C[1]) + p1;
+            C[2] = rot_next(C[2]) + p2;
+        }
+        if (MODE >= HK_MODE_HESS && (SUMS & ROW_B2)) {
             const float p11 = p1 * ar, p22 = p2 * dt2;
             blk[3] += p11;
             blk[4] += p22;
@@ -235,6 +244,7 @@ __device__ __forceinline__ void row_accumulate(float b, float te, float ar, floa
             C[4] = rot_next(C[4]) + p22;
         }
     }
+    if (!(SUMS & ROW_X)) return;
     X0c += (double)te;
     if (MODE >= HK_MODE_GRAD) {
         blk[6] = fmaf(te, dt, blk[6]);
@@ -247,7 +257,7 @@ __device__ __forceinline__ void row_accumulate(float b, float te, float ar, floa
     }
 }
 
-template <int MODE, bool MASK_BG, bool MASK_EX, bool FAST>
+template <int MODE, int SUMS, bool MASK_BG, bool MASK_EX, bool FAST>
 __device__ __forceinline__ void row_sweep(const float2 *__restrict__ rec, const double2 *__restrict__ rxy,
                                           const double *__restrict__ rtd,
                                           double tsi, int lane, float ti, double xr, double yr,
@@ -291,11 +301,11 @@ __device__ __forceinline__ void row_sweep(const float2 *__restrict__ rec, const 
             if (MASK_BG && !(j < irow)) b = 0.0f;
             if (!(j < gr)) E = 0.0f;
         }
-        row_accumulate<MODE>(b, E * r.y, ar, ae, dt, dt2, blk, C, B0d, X0c, acc0 + lane + s);
+        row_accumulate<MODE, SUMS>(b, E * r.y, ar, ae, dt, dt2, blk, C, B0d, X0c, acc0 + lane + s);
     }
 }
 
-template <int MODE, bool FAST>
+template <int MODE, int SUMS, bool FAST>
 __device__ __forceinline__ void row_sweep_masked(const float2 *__restrict__ rec, const double2 *__restrict__ rxy,
                                                  const double *__restrict__ rtd,
                                                  double tsi, int lane, float ti, double xr, double yr,
@@ -304,11 +314,11 @@ __device__ __forceinline__ void row_sweep_masked(const float2 *__restrict__ rec,
                                                  float (&C)[HK_NCOL], double &B0d, double &X0c, double *__restrict__ acc0) {
     const int cbase = c * HK_WAVE;
     if (c == wave_chunk)
-        row_sweep<MODE, true, true, FAST>(rec, rxy, rtd, tsi, lane, ti, xr, yr, irow, gr, cbase, kc, blk, C, B0d, X0c, acc0);
+        row_sweep<MODE, SUMS, true, true, FAST>(rec, rxy, rtd, tsi, lane, ti, xr, yr, irow, gr, cbase, kc, blk, C, B0d, X0c, acc0);
     else if (cbase + HK_WAVE - 1 >= wave_gmin)
-        row_sweep<MODE, false, true, FAST>(rec, rxy, rtd, tsi, lane, ti, xr, yr, irow, gr, cbase, kc, blk, C, B0d, X0c, acc0);
+        row_sweep<MODE, SUMS, false, true, FAST>(rec, rxy, rtd, tsi, lane, ti, xr, yr, irow, gr, cbase, kc, blk, C, B0d, X0c, acc0);
     else
-        row_sweep<MODE, false, false, FAST>(rec, rxy, rtd, tsi, lane, ti, xr, yr, irow, gr, cbase, kc, blk, C, B0d, X0c, acc0);
+        row_sweep<MODE, SUMS, false, false, FAST>(rec, rxy, rtd, tsi, lane, ti, xr, yr, irow, gr, cbase, kc, blk, C, B0d, X0c, acc0);
 }
 
 //
@@ -318,7 +328,18 @@ __device__ __forceinline__ void row_sweep_masked(const float2 *__restrict__ rec,
 // sets is the chain of launches, and the exponential per staged event costs less
 // than the launch (evaluation of N = 1,000 events 44.7 -> 42.0 us, of 5,003 sparse
 // in time 65.2 -> 60.7), while long pieces would pay it once per piece and chunk.
-template <int MODE, bool SELF>
+//
+// With SPLIT (few pieces, so that most SIMDs would have no wavefront) row_parts
+// blocks take a piece, each its own groups of sums: a wavefront alone on its SIMD
+// issues an instruction every eight cycles or so, and 64 steps of all the sums are
+// the longest chain of such an evaluation.  N = 1,000 events 33.1 -> 27.3 us, 300
+// 27.9 -> 23.7, gradient of 1,000 30.2 -> 26.3, log-likelihood 23.5 -> 20.0; the
+// exponents are formed once per part, so it ends where the blocks would no longer
+// be resident together (ROW_SPLIT_BLOCKS: N = 3,000 43.4 -> 40.6, but 4,000 49.3 ->
+// 53.3; four parts gain nothing more).
+constexpr int row_parts(int mode) { return mode == HK_MODE_HESS ? 3 : 2; }
+
+template <int MODE, bool SELF, bool SPLIT>
 __global__ __launch_bounds__(HK_TILE, 4) void k_row(const double *__restrict__ ts, const double *__restrict__ xs,
                                                   const double *__restrict__ ys, const float *__restrict__ theta_v,
                                                   const int *__restrict__ chunk_precise, const double *__restrict__ tstep,
@@ -350,9 +371,12 @@ __global__ __launch_bounds__(HK_TILE, 4) void k_row(const double *__restrict__ t
     // bounds below live in scalar registers and select the sweep variant with
     // scalar branches
     const int tid = threadIdx.x, lane = tid & (HK_WAVE - 1), wv = __builtin_amdgcn_readfirstlane(tid / HK_WAVE);
-    const int q_end = SELF ? blockIdx.x + 1 : block0[blockIdx.x + 1];
+    constexpr int PARTS = SPLIT ? row_parts(MODE) : 1, FIRST = MODE >= HK_MODE_GRAD ? ROW_B0 | ROW_B1 : ROW_B0;
+    const int piece = (int)blockIdx.x / PARTS, part = (int)blockIdx.x % PARTS;
+    const int sums = !SPLIT ? ROW_ALL : part == 0 ? FIRST : part == PARTS - 1 ? ROW_X : ROW_B2;
+    const int q_end = SELF ? piece + 1 : block0[piece + 1];
 
-    for (int q = SELF ? blockIdx.x : block0[blockIdx.x]; q < q_end; ++q) {
+    for (int q = SELF ? piece : block0[piece]; q < q_end; ++q) {
         const hk_item it = items[q];
         const int I = it.tile;
         const int64_t row0 = (int64_t)I * HK_TILE;
@@ -442,12 +466,23 @@ __global__ __launch_bounds__(HK_TILE, 4) void k_row(const double *__restrict__ t
             // the wave's earliest row contributes only terms below 2^-160
             const bool live = block_live && c <= wave_chunk && !(wave_tmin - Tlast > kc.dt_cut);
             if (live) {
-                if (fact)
-                    row_sweep_masked<MODE, true>(rec, rxy, rtd, tsi_s, lane, ti, xr, yr, irow, gr, c, wave_chunk, wave_gmin,
-                                                 kc, blk, C, B0d, X0c, colacc0[wv]);
-                else
-                    row_sweep_masked<MODE, false>(rec, rxy, rtd, tsi_s, lane, ti, xr, yr, irow, gr, c, wave_chunk, wave_gmin,
-                                                  kc, blk, C, B0d, X0c, colacc0[wv]);
+#define HK_ROW_SWEEP(S)                                                                                              \
+    if (fact)                                                                                                     \
+        row_sweep_masked<MODE, S, true>(rec, rxy, rtd, tsi_s, lane, ti, xr, yr, irow, gr, c, wave_chunk, wave_gmin, kc, \
+                                        blk, C, B0d, X0c, colacc0[wv]);                                            \
+    else                                                                                                          \
+        row_sweep_masked<MODE, S, false>(rec, rxy, rtd, tsi_s, lane, ti, xr, yr, irow, gr, c, wave_chunk, wave_gmin, kc, \
+                                         blk, C, B0d, X0c, colacc0[wv])
+                if (!SPLIT) {
+                    HK_ROW_SWEEP(ROW_ALL);
+                } else if (part == 0) {
+                    HK_ROW_SWEEP(FIRST);
+                } else if (part == PARTS - 1) {
+                    HK_ROW_SWEEP(ROW_X);
+                } else {
+                    HK_ROW_SWEEP(ROW_B2);
+                }
+#undef HK_ROW_SWEEP
                 // the row's time factor (t_i >= T_c here, so it is at most 1)
                 if (fact) {
                     if (!have_ui) {
@@ -473,6 +508,7 @@ __global__ __launch_bounds__(HK_TILE, 4) void k_row(const double *__restrict__ t
             // 2^-24 each) and summed in FP64 by the finalisation
             for (int e = tid; e < NC * HK_WAVE; e += HK_TILE) {
                 const int a = e / HK_WAVE, cc = e % HK_WAVE;
+                if (SPLIT && !(sums & row_slot_group(a))) continue;
                 float v;
                 if (a == 0) {
                     double c0 = 0.0;
@@ -492,13 +528,13 @@ __global__ __launch_bounds__(HK_TILE, 4) void k_row(const double *__restrict__ t
             }
         }
         float *__restrict__ rp = rowpart + (int64_t)q * HK_NROW * HK_TILE;
-        rp[tid] = (float)B0d;
-        rp[5 * HK_TILE + tid] = (float)X0d;
+        if (sums & ROW_B0) rp[tid] = (float)B0d;
+        if (sums & ROW_X) rp[5 * HK_TILE + tid] = (float)X0d;
 #pragma unroll
         for (int a = 0; a < HK_NROW; ++a) {
             const bool used = (MODE >= HK_MODE_GRAD && (a == 1 || a == 2 || a == 6 || a == 7)) ||
                               (MODE >= HK_MODE_HESS && a != 0 && a != 5);
-            if (used) rp[a * HK_TILE + tid] = (float)mom[a];
+            if (used && (sums & row_slot_group(a))) rp[a * HK_TILE + tid] = (float)mom[a];
         }
     }
 }
@@ -1302,10 +1338,14 @@ static void launch_tfac(hawkes_plan p, const PairConst &kc, const double *d_thet
 #define HK_ROW_ARGS(p)                                                                                           \
     p->ts, p->xs, p->ys, p->theta_v, p->chunk_precise, p->tstep, p->g, p->row_items, p->row_block0, p->colpart_off, \
         p->rowpart, p->colpart
+constexpr int ROW_SPLIT_BLOCKS = 1024;  // four per CU of an MI355X
 template <int MODE>
 static void launch_row(hawkes_plan p, const PairConst &kc, const double *d_theta, hipStream_t stream) {
-    hipLaunchKernelGGL((p->row_single ? k_row<MODE, true> : k_row<MODE, false>), dim3(p->n_row_blocks), dim3(HK_TILE),
-                       0, stream, HK_ROW_ARGS(p), kc, d_theta, p->perm, p->n, p->status);
+    const bool split = p->row_single && p->n_row_blocks * row_parts(MODE) <= ROW_SPLIT_BLOCKS;
+    hipLaunchKernelGGL((split           ? k_row<MODE, true, true>
+                        : p->row_single ? k_row<MODE, true, false>
+                                        : k_row<MODE, false, false>),
+                       dim3(p->n_row_blocks * (split ? row_parts(MODE) : 1)), dim3(HK_TILE), 0, stream, HK_ROW_ARGS(p), kc, d_theta, p->perm, p->n, p->status);
 }
 
 // Column pass and its finalisation on the plan's current w, a (Eq. 4, Eq. 5).
@@ -1415,7 +1455,7 @@ extern "C" hawkes_status hawkes_eval(hawkes_plan p, const hawkes_hyper *hyper, c
 void hk_launch_row_loglik(hawkes_plan p, const PairConst &kc, const double *d_theta, const unsigned char *member,
                           hipStream_t stream) {
     launch_tfac(p, kc, d_theta, member, stream);
-    hipLaunchKernelGGL((k_row<HK_MODE_LOGLIK, false>), dim3(p->n_row_blocks), dim3(HK_TILE), 0, stream, HK_ROW_ARGS(p),
+    hipLaunchKernelGGL((k_row<HK_MODE_LOGLIK, false, false>), dim3(p->n_row_blocks), dim3(HK_TILE), 0, stream, HK_ROW_ARGS(p),
                        kc, nullptr, nullptr, p->n, p->status);
 }
 

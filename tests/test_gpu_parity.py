@@ -556,3 +556,49 @@ def test_bad_rate_is_reported_by_the_staging_row_pass(gpu, bad):
     plan.eval(torch.as_tensor(es.theta, device="cuda:0"), es.hyper, loglik=True)
     assert plan.status() == 0
     plan.close()
+
+
+@pytest.mark.parametrize("n", [200, 3072, 3073, 3840, 3841])
+@pytest.mark.parametrize("t_end", [900.0, 6.0e4])
+def test_split_row_pass_matches_oracle(gpu, n, t_end):
+    """The sizes where the row pass no longer gives each group of sums its own
+    blocks (3,072 events with the Hessian, 3,840 without), dense and sparse in time:
+    the outputs of each combination against the oracle, lambda and the
+    log-likelihood with the bounds of the other parity tests.  A hyperparameter
+    derivative is a sum over events of ratios of pair sums to lambda: a chunk's
+    moment is 64 FP32 additions (4e-6 relative at most) and lambda is good to 2e-6,
+    so its bound is 8e-6 of the sum of its terms' magnitudes without cancellation."""
+    import torch
+
+    from paper_2103_03348_amd.hawkes import Plan
+
+    es = synth.small(n, seed=n, t_end=t_end, ties=n // 20)
+    ref = oracle.evaluate_es(es)
+    mu0, tx, tt, th0, om, hb = [float(v) for v in es.hyper]
+    cb, ce = oracle.constants(es.hyper)
+    B0, B1, B2, B11, B22, X0, X1, X2, X11, X22 = oracle.row_sums(es.t, es.x, es.y, es.theta, es.hyper).T
+    lam_r = np.maximum(cb * B0 + ce * X0, 1e-300)
+    d1 = np.array([cb * B0 / mu0, cb * (2 * B0 / tx + B1 / tx ** 3), cb * (B0 / tt + B2 / tt ** 3), ce * X0 / th0,
+                   ce * (X0 / om + X1), ce * (2 * X0 / hb + X2 / hb ** 3)]) / lam_r
+    d2 = np.array([0.0 * B0, cb * (6 * B0 / tx ** 2 + 7 * B1 / tx ** 4 + B11 / tx ** 6),
+                   cb * (2 * B0 / tt ** 2 + 5 * B2 / tt ** 4 + B22 / tt ** 6), 0.0 * X0, ce * (X11 + 2 * X1 / om),
+                   ce * (6 * X0 / hb ** 2 + 7 * X2 / hb ** 4 + X22 / hb ** 6)]) / lam_r
+    mag = d1.sum(1), (d2 + 2 * d1 ** 2).sum(1)
+    plan = Plan.from_numpy(es.t, es.x, es.y, es.t0)
+    th = torch.as_tensor(es.theta, device="cuda:0")
+    for grad, hess in ((True, True), (True, False), (False, False)):
+        out = plan.eval(th, es.hyper, loglik=True, grad_hyper=grad, negH_hyper=hess)
+        # (200 events over 60,000: some without any intensity, -inf and reported)
+        ll = float(out["loglik"].item())
+        assert (plan.status() == 0) == np.isfinite(ref["loglik"])
+        if not np.isfinite(ref["loglik"]):
+            assert ll == ref["loglik"]
+            continue
+        assert abs(ll - ref["loglik"]) <= 2e-6 * n
+        lam = plan.lam().cpu().numpy()
+        assert np.all(np.abs(lam - ref["lam"]) <= 2e-6 * ref["lam"])
+        if grad:
+            assert np.all(np.abs(out["grad_hyper"].cpu().numpy() - ref["grad_hyper"]) <= 8e-6 * mag[0])
+        if hess:
+            assert np.all(np.abs(out["negH_hyper"].cpu().numpy() - ref["negH_hyper"]) <= 8e-6 * mag[1])
+    plan.close()
