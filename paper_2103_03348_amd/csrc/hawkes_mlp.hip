@@ -460,7 +460,15 @@ __global__ __launch_bounds__(kFeatThreads) void k_cell_place(const double *__res
                                                             double2 *__restrict__ cxy) {
     __shared__ int next[kFeatCells];
     const int cells = G.nx * G.ny, b = blockIdx.x;
-    for (int c = threadIdx.x; c < cells; c += kFeatThreads) next[c] = off[(int64_t)b * (cells + 1) + c];
+    constexpr int own = kFeatCells / kFeatThreads;
+    int first[own];  // loaded together
+#pragma unroll
+    for (int k = 0; k < own; ++k) {
+        const int c = threadIdx.x + k * kFeatThreads;
+        first[k] = c < cells ? off[(int64_t)b * (cells + 1) + c] : 0;
+    }
+#pragma unroll
+    for (int k = 0; k < own; ++k) next[threadIdx.x + k * kFeatThreads] = first[k];
     const int64_t i1 = min(n, (int64_t)(b + 1) * G.per);
     for (int64_t i0 = (int64_t)b * G.per; i0 < i1; i0 += kFeatBatch * kFeatThreads) {
         double x[kFeatBatch], y[kFeatBatch], tt[kFeatBatch];
