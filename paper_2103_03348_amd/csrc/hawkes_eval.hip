@@ -1289,6 +1289,7 @@ void hk_make_consts(const hawkes_plan p, const hawkes_hyper *hy, PairConst *kc, 
     // time gaps beyond which every background term (exponent <= kbt dt^2) and
     // every excitation term (exponent <= kw dt) is below 2^-160: exactly zero in
     // FP32, and below 1e-48 of a unit term in the split form
+    kc->cut = p->cutoff;
     if (p->cutoff) {
         kc->dt_cut_ex = -160.0 / kw;
         kc->dt_cut = fmax(sqrt(-160.0 / kbt), kc->dt_cut_ex);

@@ -511,6 +511,7 @@ __global__ __launch_bounds__(HK_WAVE) void k_sub_items(
     // more than dt_cut_ex ends the item (entries are in time order, and the
     // batches are walked from late to early), and an item without any leaves
     // before its loads: N = 250,000, HMC iteration with the cutoff 7.6 -> 6.8 ms
+    // (asking first whether there is a cutoff here costs it 0.5%)
     const double chunk_tmin = ts[(int64_t)b * HK_WAVE];
     const int g_first = g[(int64_t)b * HK_WAVE];  // g is non-decreasing
     // batches are the 64-entry subset chunks (items start on chunk boundaries),
@@ -546,7 +547,7 @@ __global__ __launch_bounds__(HK_WAVE) void k_sub_items(
             nt = sts[rn];
             np = pos[rn];
         }
-        if (chunk_tmin - sts[cend - 1] > kc.dt_cut_ex) break;  // and all earlier batches
+        if (kc.cut && chunk_tmin - sts[cend - 1] > kc.dt_cut_ex) break;  // (and all earlier batches)
         const bool fact = qwide[q] == 0;
         {
             // entries past the item's range carry rate 0 and a time of -inf: the
@@ -784,7 +785,7 @@ __global__ __launch_bounds__(SUB_ROW_WAVES * HK_WAVE) void k_sub_block(
             // under the cutoff a unit whose last entry precedes the chunk's first row
             // by more than dt_cut_ex, and all the earlier ones, add nothing (entries
             // are in time order)
-            if (kc.dt_cut_ex < INFINITY && chunk_tmin - sts[min((u + 1) * SUB_UNIT, c_end) - 1] > kc.dt_cut_ex) break;
+            if (kc.cut && chunk_tmin - sts[min((u + 1) * SUB_UNIT, c_end) - 1] > kc.dt_cut_ex) break;
             const int qu = u / (HK_WAVE / SUB_UNIT);
             if (qu != q) {
                 fold();
@@ -918,8 +919,9 @@ __global__ __launch_bounds__(HK_WAVE) void k_sub_col(const double *__restrict__ 
             nt = ts[i];
             ng = g[i];
         }
-        const double Tc = ts[(int64_t)c * HK_WAVE];
-        if (Tc - q_tmax > kc.dt_cut_ex) break;  // cutoff: all later rows too far
+        // cutoff: all later rows too far (without it the time is not waited for: HMC
+        // iteration of N = 3,000 events 295 -> 289 us, 23,422 582 -> 578)
+        if (kc.cut && ts[(int64_t)c * HK_WAVE] - q_tmax > kc.dt_cut_ex) break;
         bool split = WITH_H;
         {
             const double ux = px * kc.sx, uy = py * kc.sx;
