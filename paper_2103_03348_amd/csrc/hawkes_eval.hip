@@ -4,7 +4,7 @@
 // Kernels, in launch order:
 //   k_tfac     theta to sorted order (FP32), validity check, staged rates of
 //              the split excitation time factor, the per-chunk split flags and
-//              step factors
+//              step factors (small sets: part of k_row)
 //   k_row      row pass over causal tile pairs: for each row i the background
 //              moments over j < i and the excitation moments over t_j < t_i;
 //              the background is symmetric, so each pair also adds its
@@ -16,7 +16,8 @@
 //              (App. A), hyperparameter terms; fixed-order block reduction
 //   k_fin2     one block: block partials -> loglik, grad/negH of hyperparameters
 //   k_col      column pass: G_j = sum_{t_i > t_j} E_ij w_i, H_j = sum (E_ij w_i)^2
-//   k_colfin   G_j, H_j -> Eq. 4 / Eq. 5 in the caller's order
+//   k_colfin   G_j, H_j -> Eq. 4 / Eq. 5 in the caller's order, and k_fin2's work
+//   k_col_block  k_col and k_colfin in one launch, on small sets
 #include <hip/hip_runtime.h>
 #include <math.h>
 
@@ -1121,13 +1122,7 @@ __global__ __launch_bounds__(HK_TILE) void k_col(const double *__restrict__ ts, 
 // in this form (35.8 with 64 columns per block); 2,000 43.6 / 37.3; 4,000 51.2 /
 // 49.2; 5,003 60.7 / 60.3; 8,000 94.2 / 94.5 (12 or 8 wavefronts: slower).  Hence
 // its limit, COL_BLOCK_CHUNKS.
-#ifndef HK_COL_BLOCK_WAVES
-#define HK_COL_BLOCK_WAVES 16
-#endif
-#ifndef HK_COL_BLOCK_CHUNKS
-#define HK_COL_BLOCK_CHUNKS 80
-#endif
-constexpr int COL_BLOCK_WAVES = HK_COL_BLOCK_WAVES, COL_BLOCK_CHUNKS = HK_COL_BLOCK_CHUNKS;
+constexpr int COL_BLOCK_WAVES = 16, COL_BLOCK_CHUNKS = 80;
 constexpr int COL_BLOCK_COLS = HK_WAVE / 2;
 // k_col's two streams of a chunk, one per half of the wavefront (`half` is the lane's)
 template <bool WITH_H, bool SPLIT, bool MASKED, bool DOT>

@@ -12,8 +12,8 @@
 // (Eq. 4 and Eq. 5 restricted to the subset), i.e. O(N M) as the paper notes.
 //
 // Kernels:
-//   k_sub_static   partial sums of the static row pass -> lambda_static_i
-//   k_sum_blocks   its integral term
+//   k_sub_static   partial sums of the static row pass -> lambda_static_i (its
+//                  integral term's parts are added by a block of k_sub_theta)
 //   k_sub_offset   temporal-trend offsets beta t_k (Sec. 2.2)
 //   k_sub_theta    theta_k = exp(z_k + beta t_k) into the caller's theta, and the
 //                  subset entries staged in time order for the subset passes
@@ -23,8 +23,10 @@
 //                  pass's row weights log2(c_e / lambda_i)
 //   k_sub_block    both in one launch, on small sets
 //   k_sub_col      G_k = sum_{t_i > t_k} E_ik w_i, H_k = sum (E_ik w_i)^2, items
-//   k_sub_colfin   Eq. 4 / Eq. 5 on the subset; inside hmc_step also the
+//   k_sub_colfin   Eq. 4 / Eq. 5 on the subset and what is formed from them: the
+//                  caller's gradient, curvature or mass, and inside hmc_step the
 //                  leapfrog's gradient in z, kick and drift
+//   k_sub_loglik_one, or k_sub_energy and k_sub_loglik: the log-likelihood
 //   k_sub_energy   parts of the energies; k_hmc_accept the accept decision
 //                  (momenta, Philox-4x32-10 + Box-Muller, in k_sub_theta)
 #include <hip/hip_runtime.h>
@@ -75,7 +77,6 @@ struct hk_subset {
     double *lw;          // [npad] log2(c_e / lambda_i) (HK_EXP_FLOOR on padding)
     double *colG;        // [n_items][2][HK_WAVE]
     double *gsub;        // [mpad] Eq. 4 on the subset, time order
-    double *sums;        // [8] loglik pieces of the last evaluation
     // HMC state
     double *z0, *p;      // [m] slot order
     double *off;         // [m] temporal-trend offsets beta t_k, slot order
@@ -114,10 +115,7 @@ constexpr int64_t SUB_COL_ITEMS = HK_SUB_COL_ITEMS;
 constexpr int SUB_FIN_WAVES = HK_SUB_FIN_WAVES;
 // the column finalisation takes 16 entries per block where some entry has more
 // items than this, a whole chunk of 64 elsewhere
-#ifndef HK_SUB_FIN_SPLIT
-#define HK_SUB_FIN_SPLIT 64
-#endif
-constexpr int SUB_FIN_SPLIT = HK_SUB_FIN_SPLIT;
+constexpr int SUB_FIN_SPLIT = 64;
 // partial-sum loads a finalisation wavefront keeps in flight (16 in the
 // column finalisation measured slower: 4.95 -> 5.7 us at N = 23,422)
 constexpr int SUB_FIN_BATCH = 8;
@@ -1260,7 +1258,7 @@ void hk_subset_free(hawkes_plan p) {
     hk_subset *s = p->sub;
     if (!s) return;
     void *ptrs[] = {s->pos, s->slot, s->cidx, s->cnt, s->ritems, s->ritem0, s->rnseg, s->xpart, s->items, s->item0, s->nseg,
-                    s->member, s->lam_static, s->Lam_static, s->a, s->tv, s->sxy, s->sts, s->qwide, s->qstep, s->lw, s->colG, s->gsub, s->sums, s->z0, s->p, s->off, s->vz, s->scal, s->quad,
+                    s->member, s->lam_static, s->Lam_static, s->a, s->tv, s->sxy, s->sts, s->qwide, s->qstep, s->lw, s->colG, s->gsub, s->z0, s->p, s->off, s->vz, s->scal, s->quad,
                     s->grid};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
@@ -1403,7 +1401,6 @@ extern "C" hawkes_status hawkes_plan_set_subset(hawkes_plan p, int64_t m, const 
     SC(dalloc(&s->lw, p->npad));
     SC(dalloc(&s->colG, (size_t)s->n_items * 2 * HK_WAVE));
     SC(dalloc(&s->gsub, s->mpad));
-    SC(dalloc(&s->sums, 8));
     SC(dalloc(&s->z0, m));
     SC(dalloc(&s->p, m));
     SC(dalloc(&s->off, m));
