@@ -50,16 +50,16 @@ PEAK_FP32_NONPACKED_TFLOPS = 256 * 4 * 16 * 2 * 2.4e9 / 1e12
 # Counters of one k_row launch at N = 23,422 (summary and commands in
 # profiles/k_row_k_col_N23422_counters.md): HBM traffic from rocprofv3
 # FETCH_SIZE and WRITE_SIZE scaled by a device-to-device copy of known size,
-# 8.1 MB read + 64.7 MB written; v_exp_f32 executed per pair from
+# 7.6 MB read + 64.7 MB written; v_exp_f32 executed per pair from
 # SQ_INSTS_VALU_TRANS_F32 (2.03: the masked diagonal sweeps evaluate some
 # terms they discard).  They hold only for the kernel sources they were
 # measured on, so they are reported only while these hashes match.
-K_ROW_TRAFFIC_BYTES = (3940.0 * 2.0 + 63220.0 * 1.0) * 1024
+K_ROW_TRAFFIC_BYTES = (3723.3 * 2.0 + 63220.0 * 1.0) * 1024
 K_ROW_TRANS_PER_PAIR = 2.03
 K_ROW_TRAFFIC_SOURCES = {
-    "paper_2103_03348_amd/csrc/hawkes_eval.hip": "425b29766d8095d0a2564f271e40d13609efb7df5084193006b800e26415fbaf",
-    "paper_2103_03348_amd/csrc/hawkes_internal.h": "910715bce962a5bb9a5c39602d46ace8db597a04f81cbf7eacf85f6dbaed05ae",
-    "paper_2103_03348_amd/csrc/hawkes_plan.hip": "532f6f45e995359bf91f9a2fcd59ef0f3dff5c7a241397c5ec254ce85f9d6177",
+    "paper_2103_03348_amd/csrc/hawkes_eval.hip": "87870b463b5502c83f111777bd28e35eb7b88c65747ed306c87b1c227ed820a5",
+    "paper_2103_03348_amd/csrc/hawkes_internal.h": "4da215d5e667617e3f7cfd448f99a86006741c7284a14d7bd6dbd2d0d377d204",
+    "paper_2103_03348_amd/csrc/hawkes_plan.hip": "fdb68ef8105251d0e0b2d1c7c5ee433743f537b8fe4c74d0bf6f3a7e5574c44f",
 }
 
 
