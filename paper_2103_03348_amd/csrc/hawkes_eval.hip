@@ -164,6 +164,15 @@ __device__ __forceinline__ float exp2_split(double e) {
     return __builtin_amdgcn_ldexpf(fexp2((float)(e - n)), (int)n);
 }
 
+// The same for any finite exponent up to 128: the hardware's conversion saturates, so
+// an exponent below int32's range (a distant pair, a padding row) still ends as 0.
+__device__ __forceinline__ float exp2_split_any(double e) {
+    const double n = rint(e);
+    int ni;
+    asm("v_cvt_i32_f64 %0, %1" : "=v"(ni) : "v"(n));
+    return __builtin_amdgcn_ldexpf(fexp2((float)(e - n)), ni);
+}
+
 // ------------------------------------------------------------------------------------
 // The row pass sweeps a 64-column chunk in one of two forms, chosen per chunk.
 //
@@ -179,8 +188,11 @@ __device__ __forceinline__ float exp2_split(double e) {
 //
 // Precise form (every other chunk: sparse data).  dt is the FP64 difference of
 // the times, both exponents are formed whole in FP64 and exponentiated by
-// exp2_split, so a term's error does not grow with the size of its exponent or
-// with the time span of the chunk.  It costs about a third more per pair and is
+// exp2_split_any, so a term's error does not grow with the size of its exponent or
+// with the time span of the chunk.  (Holding the exponents at a floor first, as
+// exp2_split needs, is two of its 54 instructions per pair: N = 1,000 27.35 us per
+// evaluation against 27.05, 8,000 91.9 / 90.4, gradient of 10,000 103.7 / 101.0.  With
+// FLOOR it does: for constants with which an exponent could overflow FP64.)  It costs about a third more per pair and is
 // taken only where the data is too sparse in time for the fast form.
 //
 // In both forms one sweep is 64 steps, each lane pairing its row with column
@@ -258,7 +270,7 @@ __device__ __forceinline__ void row_accumulate(float b, float te, float ar, floa
     }
 }
 
-template <int MODE, int SUMS, bool MASK_BG, bool MASK_EX, bool FAST>
+template <int MODE, int SUMS, bool FLOOR, bool MASK_BG, bool MASK_EX, bool FAST>
 __device__ __forceinline__ void row_sweep(const float2 *__restrict__ rec, const double2 *__restrict__ rxy,
                                           const double *__restrict__ rtd,
                                           double tsi, int lane, float ti, double xr, double yr,
@@ -286,12 +298,14 @@ __device__ __forceinline__ void row_sweep(const float2 *__restrict__ rec, const 
             const double dtd = tsi - rtd[lane + s];
             const double ard = -fma(dx, dx, dy * dy);
             const double aed = ard * rex_d;
-            b = exp2_split(fmax(fma(-dtd, dtd, ard), HK_EXP_FLOOR));
+            const double eb = fma(-dtd, dtd, ard);
+            b = FLOOR ? exp2_split(fmax(eb, HK_EXP_FLOOR)) : exp2_split_any(eb);
             // a masked sweep also meets later columns (dt < 0, masked below): their
             // exponent is held at 2^128 so that its integer part stays in range
-            double ee = fmax(fma(dtd, kc.kw_s, aed), HK_EXP_FLOOR);
+            double ee = fma(dtd, kc.kw_s, aed);
+            if (FLOOR) ee = fmax(ee, HK_EXP_FLOOR);
             if (MASK_BG || MASK_EX) ee = fmin(ee, 128.0);
-            E = exp2_split(ee);
+            E = FLOOR ? exp2_split(ee) : exp2_split_any(ee);
             ar = (float)ard;
             ae = (float)aed;
             dt = (float)dtd;
@@ -306,7 +320,7 @@ __device__ __forceinline__ void row_sweep(const float2 *__restrict__ rec, const 
     }
 }
 
-template <int MODE, int SUMS, bool FAST>
+template <int MODE, int SUMS, bool FLOOR, bool FAST>
 __device__ __forceinline__ void row_sweep_masked(const float2 *__restrict__ rec, const double2 *__restrict__ rxy,
                                                  const double *__restrict__ rtd,
                                                  double tsi, int lane, float ti, double xr, double yr,
@@ -315,11 +329,11 @@ __device__ __forceinline__ void row_sweep_masked(const float2 *__restrict__ rec,
                                                  float (&C)[HK_NCOL], double &B0d, double &X0c, double *__restrict__ acc0) {
     const int cbase = c * HK_WAVE;
     if (c == wave_chunk)
-        row_sweep<MODE, SUMS, true, true, FAST>(rec, rxy, rtd, tsi, lane, ti, xr, yr, irow, gr, cbase, kc, blk, C, B0d, X0c, acc0);
+        row_sweep<MODE, SUMS, FLOOR, true, true, FAST>(rec, rxy, rtd, tsi, lane, ti, xr, yr, irow, gr, cbase, kc, blk, C, B0d, X0c, acc0);
     else if (cbase + HK_WAVE - 1 >= wave_gmin)
-        row_sweep<MODE, SUMS, false, true, FAST>(rec, rxy, rtd, tsi, lane, ti, xr, yr, irow, gr, cbase, kc, blk, C, B0d, X0c, acc0);
+        row_sweep<MODE, SUMS, FLOOR, false, true, FAST>(rec, rxy, rtd, tsi, lane, ti, xr, yr, irow, gr, cbase, kc, blk, C, B0d, X0c, acc0);
     else
-        row_sweep<MODE, SUMS, false, false, FAST>(rec, rxy, rtd, tsi, lane, ti, xr, yr, irow, gr, cbase, kc, blk, C, B0d, X0c, acc0);
+        row_sweep<MODE, SUMS, FLOOR, false, false, FAST>(rec, rxy, rtd, tsi, lane, ti, xr, yr, irow, gr, cbase, kc, blk, C, B0d, X0c, acc0);
 }
 
 //
@@ -340,7 +354,7 @@ __device__ __forceinline__ void row_sweep_masked(const float2 *__restrict__ rec,
 // 53.3; four parts gain nothing more).
 constexpr int row_parts(int mode) { return mode == HK_MODE_HESS ? 3 : 2; }
 
-template <int MODE, bool SELF, bool SPLIT>
+template <int MODE, bool SELF, bool SPLIT, bool FLOOR = false>
 __global__ __launch_bounds__(HK_TILE, 4) void k_row(const double *__restrict__ ts, const double *__restrict__ xs,
                                                   const double *__restrict__ ys, const float *__restrict__ theta_v,
                                                   const int *__restrict__ chunk_precise, const double *__restrict__ tstep,
@@ -469,10 +483,10 @@ __global__ __launch_bounds__(HK_TILE, 4) void k_row(const double *__restrict__ t
             if (live) {
 #define HK_ROW_SWEEP(S)                                                                                              \
     if (fact)                                                                                                     \
-        row_sweep_masked<MODE, S, true>(rec, rxy, rtd, tsi_s, lane, ti, xr, yr, irow, gr, c, wave_chunk, wave_gmin, kc, \
+        row_sweep_masked<MODE, S, FLOOR, true>(rec, rxy, rtd, tsi_s, lane, ti, xr, yr, irow, gr, c, wave_chunk, wave_gmin, kc, \
                                         blk, C, B0d, X0c, colacc0[wv]);                                            \
     else                                                                                                          \
-        row_sweep_masked<MODE, S, false>(rec, rxy, rtd, tsi_s, lane, ti, xr, yr, irow, gr, c, wave_chunk, wave_gmin, kc, \
+        row_sweep_masked<MODE, S, FLOOR, false>(rec, rxy, rtd, tsi_s, lane, ti, xr, yr, irow, gr, c, wave_chunk, wave_gmin, kc, \
                                          blk, C, B0d, X0c, colacc0[wv])
                 if (!SPLIT) {
                     HK_ROW_SWEEP(ROW_ALL);
@@ -1300,6 +1314,12 @@ void hk_make_consts(const hawkes_plan p, const hawkes_hyper *hy, PairConst *kc, 
         const double umax = half * kc->sx;
         kc->dot = 2.0 * umax * umax <= HK_DOT_MAX2;
     }
+    {
+        // the row pass's exponents stay finite: times (padding's included) and
+        // coordinates far inside FP64's range after scaling
+        const double dt = p->t1 - p->t0 + HK_PAD_DT, side = fmax(p->xmax - p->xmin, p->ymax - p->ymin) * kc->sbx;
+        kc->floor = !(dt * kc->st <= 1e150 && -kw * dt <= 1e300 && side <= 1e150 && side * side * (kex / kbx) <= 1e300);
+    }
     kc->rex = (float)(kex / kbx);
     kc->rex_x = kex / kbx;
     kc->span_max = fmin(HK_FACT_SPAN / hy->omega, HK_COMPACT_TAU * hy->tau_t);
@@ -1337,6 +1357,11 @@ static void launch_tfac(hawkes_plan p, const PairConst &kc, const double *d_thet
 constexpr int ROW_SPLIT_BLOCKS = 1024;  // four per CU of an MI355X
 template <int MODE>
 static void launch_row(hawkes_plan p, const PairConst &kc, const double *d_theta, hipStream_t stream) {
+    if (kc.floor) {
+        hipLaunchKernelGGL((k_row<MODE, false, false, true>), dim3(p->n_row_blocks), dim3(HK_TILE), 0, stream,
+                           HK_ROW_ARGS(p), kc, d_theta, p->perm, p->n, p->status);
+        return;
+    }
     const bool split = p->row_single && p->n_row_blocks * row_parts(MODE) <= ROW_SPLIT_BLOCKS;
     hipLaunchKernelGGL((split           ? k_row<MODE, true, true>
                         : p->row_single ? k_row<MODE, true, false>
@@ -1418,7 +1443,7 @@ extern "C" hawkes_status hawkes_eval(hawkes_plan p, const hawkes_hyper *hyper, c
     const int64_t npad = p->npad;
 
     hk_prof_mark(p, HK_PROF_EVAL, true, stream);
-    if (!p->row_single) launch_tfac(p, kc, d_theta, nullptr, stream);
+    if (!p->row_single || kc.floor) launch_tfac(p, kc, d_theta, nullptr, stream);
     hk_prof_mark(p, HK_PROF_ROW, true, stream);
 #define HK_FIN(M)                                                                                              \
     hipLaunchKernelGGL(k_fin<M>, dim3(p->nchunks), dim3(HK_FIN_WAVES * HK_WAVE), 0, stream, p->ts, p->xs, p->ys, \
@@ -1451,8 +1476,9 @@ extern "C" hawkes_status hawkes_eval(hawkes_plan p, const hawkes_hyper *hyper, c
 void hk_launch_row_loglik(hawkes_plan p, const PairConst &kc, const double *d_theta, const unsigned char *member,
                           hipStream_t stream) {
     launch_tfac(p, kc, d_theta, member, stream);
-    hipLaunchKernelGGL((k_row<HK_MODE_LOGLIK, false, false>), dim3(p->n_row_blocks), dim3(HK_TILE), 0, stream, HK_ROW_ARGS(p),
-                       kc, nullptr, nullptr, p->n, p->status);
+    hipLaunchKernelGGL((kc.floor ? k_row<HK_MODE_LOGLIK, false, false, true> : k_row<HK_MODE_LOGLIK, false, false>),
+                       dim3(p->n_row_blocks), dim3(HK_TILE), 0, stream, HK_ROW_ARGS(p), kc, nullptr, nullptr, p->n,
+                       p->status);
 }
 
 // Blocks per compute unit in the pair-pass schedules.  Eight blocks of four

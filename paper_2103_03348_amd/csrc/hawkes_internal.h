@@ -188,6 +188,7 @@ struct PairConst {
     double sbx;    // sqrt(-kbx): the same for the background exponent a_b
     double dt_cut;     // row pass: time gap past which both terms are below 2^-160 (INFINITY: no cutoff)
     double dt_cut_ex;  // column pass: the same for the excitation term alone
+    int floor;         // row pass: an exponent could overflow FP64 without its floor
     int cut;           // the cutoff is on (the subset passes then read the times it is decided by)
     int dot;           // column passes: expand the spatial exponent (HK_DOT_MAX2 holds for the plan)
 };

@@ -602,3 +602,26 @@ def test_split_row_pass_matches_oracle(gpu, n, t_end):
         if hess:
             assert np.all(np.abs(out["negH_hyper"].cpu().numpy() - ref["negH_hyper"]) <= 8e-6 * mag[1])
     plan.close()
+
+
+@pytest.mark.parametrize("tau_t", [1e-150, 5.0])
+def test_intensity_with_a_vanishing_time_scale(gpu, tau_t):
+    """A background time scale so small that a pair's scaled time difference squared
+    overflows FP64 (the row pass then holds its exponents at a floor): without a
+    background the intensities are the excitation's alone, as in the oracle; and the
+    same set with an ordinary scale."""
+    import torch
+
+    from paper_2103_03348_amd.hawkes import Plan
+
+    es = synth.small(400, seed=44, t_end=40.0)
+    es.hyper = (es.hyper[0] if tau_t > 1.0 else 0.0, es.hyper[1], tau_t, *es.hyper[3:])
+    es.x[:], es.y[:] = 0.1 * es.x, 0.1 * es.y
+    cb, ce = oracle.constants(es.hyper)
+    S = oracle.row_sums(es.t, es.x, es.y, es.theta, es.hyper)
+    ref = cb * S[:, 0] + ce * S[:, 5]
+    plan = Plan.from_numpy(es.t, es.x, es.y, es.t0)
+    plan.eval(torch.as_tensor(es.theta, device="cuda:0"), es.hyper, loglik=True)
+    lam = plan.lam().cpu().numpy()
+    assert np.all(np.abs(lam - ref) <= 2e-6 * ref)
+    plan.close()
