@@ -1314,16 +1314,20 @@ void hk_make_consts(const hawkes_plan p, const hawkes_hyper *hy, PairConst *kc, 
         const double umax = half * kc->sx;
         kc->dot = 2.0 * umax * umax <= HK_DOT_MAX2;
     }
-    {
-        // the row pass's exponents stay finite: times (padding's included) and
-        // coordinates far inside FP64's range after scaling
-        const double dt = p->t1 - p->t0 + HK_PAD_DT, side = fmax(p->xmax - p->xmin, p->ymax - p->ymin) * kc->sbx;
-        kc->floor = !(dt * kc->st <= 1e150 && -kw * dt <= 1e300 && side <= 1e150 && side * side * (kex / kbx) <= 1e300);
-    }
     kc->rex = (float)(kex / kbx);
     kc->rex_x = kex / kbx;
     kc->span_max = fmin(HK_FACT_SPAN / hy->omega, HK_COMPACT_TAU * hy->tau_t);
     kc->rex_lo = (float)(kex / kbx - (double)kc->rex);
+    {
+        // the row pass's exponents are finite: times (padding's included) and
+        // coordinates far inside FP64's range, scaled by the constants as the kernel
+        // holds them (kw_s is infinite where tau_t^2 overflows, rex, an FP32 number,
+        // where tau_x exceeds h by more than 1.8e19); a NaN fails its comparison
+        const double dt = (p->t1 - p->t0 + HK_PAD_DT) * kc->st;
+        const double side = fmax(p->xmax - p->xmin, p->ymax - p->ymin) * kc->sbx;
+        const double rex = fmax((double)kc->rex, kc->rex_x);
+        kc->floor = !(dt <= 1e150 && dt * -kc->kw_s <= 1e300 && side <= 1e150 && side * side * rex <= 1e300);
+    }
     fc->Kt = -1.0 / kbt;
     fc->inv_st = 1.0 / kc->st;
     fc->rho_ex = ((double)kc->rex - kex / kbx) / (double)kc->rex;
