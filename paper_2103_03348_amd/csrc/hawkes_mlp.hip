@@ -919,14 +919,19 @@ extern "C" hawkes_status hawkes_features(hawkes_plan p, const hawkes_hyper *hy, 
     const bool lds = fits(hy->h, kFeatCells) || fits(2.0 * hy->h, kFeatCells) || fits(3.0 * hy->h, kFeatCells);
     const int64_t n = p->n, cells = (int64_t)G.nx * G.ny;
     // runs of at least 256 events
-    G.nb = lds ? (int)std::min<int64_t>(kFeatRuns, (n + 255) / 256) : 1;
+    const int64_t runs = std::min<int64_t>(kFeatRuns, (n + 255) / 256);
+    G.nb = lds ? (int)runs : 1;
     G.per = (int)((n + G.nb - 1) / G.nb);
     // int workspace: offsets [nb][cells + 1], then the runs' group sums, or one
     // run's counts and fill marks; then (16-byte aligned) the events' coordinates
     // and times in cell order [3 n]
     const int64_t offs = G.nb * (cells + 1);
     const int64_t ints = (offs + (lds ? (int64_t)G.nb * (kFeatCells / kFeatGroup) : 2 * cells) + 3) / 4 * 4;
-    hawkes_status st = hk_subset_grid(p, ints + 6 * n, stream);
+    // the number of cells jumps where the cell width goes from one multiple of h to
+    // another, so there is always room for the LDS sort's largest grid: the workspace
+    // then grows only as h falls (a larger one may follow under capture)
+    const int64_t room = (runs * (kFeatCells + 1 + kFeatCells / kFeatGroup) + 3) / 4 * 4;
+    hawkes_status st = hk_subset_grid(p, std::max(ints, room) + 6 * n, stream);
     if (st != HAWKES_OK) return st;
     int *off = hk_subset_grid_ptr(p), *rest = off + offs;
     double2 *cxy = (double2 *)(off + ints);

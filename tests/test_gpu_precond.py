@@ -352,3 +352,45 @@ def test_features_of_long_ranges_match_oracle(gpu, n):
     torch.cuda.synchronize()
     ref = ofeat.features(es.t, es.x, es.y, es.subset, z, es.hyper, es.t0, gx0, gy0)
     np.testing.assert_allclose(feat.cpu().numpy(), ref, rtol=1e-6, atol=1e-6)
+
+
+@pytest.mark.parametrize("n,h0,hs", [(3000, 0.3, (0.35, 0.6, 2.0)), (17000, 0.05, (0.16, 0.35))])
+def test_features_capture_at_larger_bandwidths(gpu, n, h0, hs):
+    """After a first call, calls at any larger bandwidth fit its workspace (the cell
+    width, and with it the grid, jumps between h, 2h and 3h and between the two
+    sorts), so they can be captured; every replay gives the eager result."""
+    import torch
+
+    from paper_2103_03348_amd import _lib
+
+    es = synth.small(n, seed=n, t_end=0.05 * n, all_free=False)
+    rng = np.random.default_rng(n)
+    es.x[:], es.y[:] = rng.uniform(0.0, 30.0, n), rng.uniform(0.0, 30.0, n)
+    plan = _plan_with_subset(es)
+    gx0, gy0 = float(es.x.min()) - 1e-9, float(es.y.min()) - 1e-9
+    feat = torch.empty((es.subset.shape[0], 12), dtype=torch.float32, device="cuda:0")
+    dt, dxy, dz = _t(es.t), _t(np.stack([es.x, es.y], 1)), _t(np.log(es.theta[es.subset]))
+
+    def call(h):
+        hy = _lib.Hyper.of(es.hyper[:5] + (h,))
+        _lib.check(_lib.lib().hawkes_features(plan.handle, ctypes.byref(hy), _lib.ptr(dt), _lib.ptr(dxy),
+                                              _lib.ptr(dz), gx0, gy0, _lib.ptr(feat), _lib.stream_handle()), "features")
+
+    call(h0)
+    torch.cuda.synchronize()
+    graphs = []
+    for h in hs:
+        graphs.append(torch.cuda.CUDAGraph())
+        with torch.cuda.graph(graphs[-1]):
+            call(h)
+    for h, g in zip(hs, graphs):
+        call(h)
+        eager = feat.clone()
+        for _ in range(3):
+            feat.zero_()
+            g.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(feat, eager)
+            call(h0)
+    torch.cuda.synchronize()
+    del graphs
