@@ -359,6 +359,12 @@ constexpr int kFeatOffWaves = 4;     // its wavefronts, a quarter of the runs ea
 constexpr int kFeatThreads = 1024;
 constexpr int kFeatWindows = 2;   // columns whose windows' candidates a lane loads together
 constexpr int kFeatTests = 8;     // candidates a lane of k_features loads together
+// candidates of one cell's windows above which the whole wavefront takes them: where a
+// few crowded cells hold most of a free event's windows, the other lane groups waited
+// for the one that had them (N = 100,000, 400 free events, h = 4, omega = 0.001 / 0.5
+// with 6,874 of h = 1, us: lane groups alone 4,993 / 171, 512 999 / 171, 128 1,000 / 170,
+// 32 992 / 162; 6,874 of h = 0.3, omega = 0.01, lists of some 40: 118, 115, 116, 121)
+constexpr int kFeatLong = 32;
 constexpr int kFeatBatch = 4;     // events a thread of the sort loads together
 
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return min(max(v, lo), hi); }
@@ -719,9 +725,22 @@ __global__ __launch_bounds__(HK_WAVE, 7) void k_features(const double *__restric
             amax = fmax(amax, ae[i + u]);
         }
     }
+    // the others: a short list by the lane group, a long one (windows of many runs over
+    // a crowded cell) by the whole wavefront
+    const uint64_t longs = __ballot(wn > kFeatLong);
+    const auto others = [&](const auto &take) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-        for (int s = lr + lpr; s < cn[i]; s += lpr) amax = fmax(amax, window(cq[i] + s));
+        for (int i = 0; i < 8; ++i)
+            if (cn[i] <= kFeatLong)
+                for (int s = lr + lpr; s < cn[i]; s += lpr) take(cq[i] + s);
+        for (uint64_t mk = longs; mk != 0; mk &= mk - 1) {
+            const int l = __ffsll((unsigned long long)mk) - 1;
+            const int q0 = __builtin_amdgcn_readlane(wq, l), n = __builtin_amdgcn_readlane(wn, l);
+#pragma unroll 4
+            for (int s = lpr + lane; s < n; s += HK_WAVE) take(q0 + s);
+        }
+    };
+    others([&](int q) { amax = fmax(amax, window(q)); });
 #pragma unroll
     for (int a = 1; a < 8; ++a) {
 #pragma unroll
@@ -736,17 +755,15 @@ __global__ __launch_bounds__(HK_WAVE, 7) void k_features(const double *__restric
             return llrint((double)exp2f((float)((a - amax) * 1.4426950408889634)) * 68719476736.0);
         };
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
+        for (int i = 0; i < 8; ++i)
             if (ae[i] > -INFINITY) ksum += term(ae[i]);
-            for (int s = lr + lpr; s < cn[i]; s += lpr) {
-                const int q = cq[i] + s;
-                const double2 p = cxy[q];
-                const double dx = p.x - xm, dy = p.y - ym;
-                const double d2 = dx * dx + dy * dy;
-                const double dt = ct[q] - tm;
-                if (d2 < r1 && dt > 0.0 && dt <= w6) ksum += term(-2.0 * F.omega * dt - d2 * F.inv_h2);
-            }
-        }
+        others([&](int q) {
+            const double2 p = cxy[q];
+            const double dx = p.x - xm, dy = p.y - ym;
+            const double d2 = dx * dx + dy * dy;
+            const double dt = ct[q] - tm;
+            if (d2 < r1 && dt > 0.0 && dt <= w6) ksum += term(-2.0 * F.omega * dt - d2 * F.inv_h2);
+        });
 #pragma unroll
         for (int o = 1; o < HK_WAVE; o <<= 1) ksum += __shfl_xor(ksum, o);
     }

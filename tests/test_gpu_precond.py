@@ -394,3 +394,32 @@ def test_features_capture_at_larger_bandwidths(gpu, n, h0, hs):
             call(h0)
     torch.cuda.synchronize()
     del graphs
+
+
+@pytest.mark.parametrize("n", [16, 32, 33, 40, 41, 96, 97, 161, 3000])
+@pytest.mark.parametrize("spread", [1e-3, 1.5])
+def test_features_of_long_windows_match_oracle(gpu, n, spread):
+    """Time windows over every run of the events, with all events in one cell or
+    over a few: lists of candidates around the 32 from which the whole wavefront
+    takes a cell's, its first 8 or 16 and its 64 lanes.  Counts are integers: their
+    log1p agrees to FP32 rounding, and feature 8 to the FP32 exponential's."""
+    import torch
+
+    from paper_2103_03348_amd import _lib
+
+    h, omega = 0.7, 1e-3
+    es = synth.small(n, seed=n, t_end=0.5 * n, ties=n // 10, all_free=False)
+    rng = np.random.default_rng(n)
+    es.x[:], es.y[:] = spread * rng.uniform(0.0, 1.0, n), spread * rng.uniform(0.0, 1.0, n)
+    es.hyper = es.hyper[:4] + (omega, h)
+    plan = _plan_with_subset(es)
+    z = np.log(es.theta[es.subset])
+    gx0, gy0 = float(es.x.min()) - 1e-9, float(es.y.min()) - 1e-9
+    feat = torch.empty((es.subset.shape[0], 12), dtype=torch.float32, device="cuda:0")
+    hy = _lib.Hyper.of(es.hyper)
+    dt, dxy, dz = _t(es.t), _t(np.stack([es.x, es.y], 1)), _t(z)
+    _lib.check(_lib.lib().hawkes_features(plan.handle, ctypes.byref(hy), _lib.ptr(dt), _lib.ptr(dxy), _lib.ptr(dz),
+                                          gx0, gy0, _lib.ptr(feat), _lib.stream_handle()), "features")
+    torch.cuda.synchronize()
+    ref = ofeat.features(es.t, es.x, es.y, es.subset, z, es.hyper, es.t0, gx0, gy0)
+    np.testing.assert_allclose(feat.cpu().numpy(), ref, rtol=1e-6, atol=1e-6)
