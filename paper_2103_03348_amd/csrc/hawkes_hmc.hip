@@ -125,12 +125,19 @@ constexpr int SUB_FIN_BATCH = 8;
 #endif
 constexpr int SUB_ROWFIN_WAVES = HK_SUB_ROWFIN_WAVES;
 // block form of the row pass: wavefronts per block (one row chunk), entries per
-// staged unit, and the most one-wavefront items for which it is taken: up to
-// about one per SIMD the items are latency and a second launch (HMC iteration,
-// items / blocks: N = 3,000, 100 items, 368 / 292 us; 8,000, 560 items, 374 / 357;
-// 23,422, 4,850 items, 614 / 635)
+// staged unit, and the most one-wavefront items, entries and chunks for which it is
+// taken.  Up to about one item per SIMD the items are latency and a second launch
+// (HMC iteration of 20 steps, items / blocks: N = 3,000, 100 items, 368 / 292 us;
+// 8,000, 560 items, 374 / 357; 23,422, 4,850 items, 614 / 635).  A block's longest
+// wavefront walks an entry in 12, an item's 64 of them at once: with more than three
+// units each it is the longer chain (10 steps, M = 512 / 768 / 1,024 of 5,000
+// events: items 190 / 193 / 194, blocks 179 / 196 / 219).  And the blocks of chunks
+// without an entry cost as much as others (M = 16 of the last events of 65,000 /
+// 100,000 / 150,000 / 250,000: items 202 / 205 / 210 / 218, blocks 165 / 185 / 211 /
+// 260; 512 of them are resident at once).
 constexpr int SUB_ROW_WAVES = 12, SUB_UNIT = 16;
 constexpr int64_t SUB_BLOCK_ITEMS = 1024;
+constexpr int64_t SUB_BLOCK_ENTRIES = 3 * SUB_ROW_WAVES * SUB_UNIT, SUB_BLOCK_CHUNKS = 2048;
 constexpr int64_t SUB_ITEM_BATCHES = 8;
 // unroll of the subset sweeps: 8 measured fastest (114 VGPRs, 4 wavefronts per
 // SIMD); shorter loops fit more wavefronts but lose more instruction-level
@@ -1333,8 +1340,7 @@ extern "C" hawkes_status hawkes_plan_set_subset(hawkes_plan p, int64_t m, const 
             cnt[b] = (int)r;
         }
     }
-    // row pass schedule: items of at most BR entries, unless there are few (the
-    // block form then needs none)
+    // row pass schedule: items of at most BR entries (the block form needs none)
     int64_t wrow = 0, batches = 0;
     for (int b = 0; b < nch; ++b) {
         wrow += cnt[b];
@@ -1345,7 +1351,8 @@ extern "C" hawkes_status hawkes_plan_set_subset(hawkes_plan p, int64_t m, const 
                        HK_WAVE;
     std::vector<hk_item> ritems;
     std::vector<int> ritem0(nch), rnseg(nch);
-    for (int b = 0; b < nch && batches > SUB_BLOCK_ITEMS; ++b) {
+    const bool blocks = batches <= SUB_BLOCK_ITEMS && m <= SUB_BLOCK_ENTRIES && nch <= SUB_BLOCK_CHUNKS;
+    for (int b = 0; b < nch && !blocks; ++b) {
         ritem0[b] = (int)ritems.size();
         int seg = 0;
         for (int64_t e = 0; e < cnt[b]; e += br)

@@ -664,3 +664,51 @@ def test_subset_column_finalisation_forms_match_oracle(gpu, n, m):
         if want_h:
             assert h_rel_all(h, hi) < 1e-6
     plan.close()
+
+
+@pytest.mark.parametrize("m", [576, 577])
+def test_subset_row_forms_by_entries_match_oracle(gpu, m):
+    """Either side of the number of entries up to which a row chunk is one block's,
+    with the bounds above."""
+    import dataclasses
+
+    es = synth.small(1300, seed=61, t_end=60.0, ties=8, all_free=False)
+    sub = np.sort(np.random.default_rng(m).choice(es.n, m, replace=False)).astype(np.int64)
+    es = dataclasses.replace(es, subset=sub, z=np.log(es.theta[sub]))
+    plan, idx = _setup(es)
+    ref = oracle.evaluate_es(es)
+    gi, hi = ref["grad_theta"][sub], ref["negH_theta"][sub]
+    a = es.hyper[3] * (1.0 - np.exp(-es.hyper[4] * (es.t.max() - es.t[sub])))
+    ll, g, h = _subset_grad(plan, es, es.theta, want_h=True)
+    assert plan.status() == 0
+    assert abs(ll - ref["loglik"]) < 2e-6 * es.n
+    assert np.max(np.abs(g - gi) / np.maximum(gi + 2 * a, 1e-300)) < 1e-6
+    assert h_rel_all(h, hi) < 1e-6
+    plan.close()
+
+
+@pytest.mark.parametrize("n", [131072, 131073])
+def test_subset_row_forms_by_chunks_match_full_evaluation(gpu, n):
+    """A few free events late in a large set, either side of the number of row
+    chunks up to which each is a block's: against the full evaluation, itself
+    within the same bounds of the oracle (hence twice them)."""
+    import dataclasses
+
+    import torch
+
+    es = synth.small(n, seed=62, t_end=2600.0, all_free=False)
+    late = np.argsort(es.t)[-n // 100:]
+    sub = np.sort(np.random.default_rng(n).choice(late, 20, replace=False)).astype(np.int64)
+    es = dataclasses.replace(es, subset=sub, z=np.log(es.theta[sub]))
+    plan, idx = _setup(es)
+    out = plan.eval(torch.as_tensor(es.theta, device="cuda:0"), es.hyper, loglik=True, grad_theta=True,
+                    negH_theta=True)
+    gi, hi = out["grad_theta"].cpu().numpy()[sub], out["negH_theta"].cpu().numpy()[sub]
+    ref = float(out["loglik"].item())
+    a = es.hyper[3] * (1.0 - np.exp(-es.hyper[4] * (es.t.max() - es.t[sub])))
+    ll, g, h = _subset_grad(plan, es, es.theta, want_h=True)
+    assert plan.status() == 0
+    assert abs(ll - ref) < 2e-9 * abs(ref)
+    assert np.max(np.abs(g - gi) / np.maximum(gi + 2 * a, 1e-300)) < 2e-6
+    assert h_rel_all(h, hi) < 2e-6
+    plan.close()
