@@ -7,7 +7,7 @@
 // tree level by level is a chain of some 30 dependent levels up and down (25 us
 // for 1,610 tips in one block, the prior's whole cost).  Instead the tree is cut
 // into its R maximal subtrees of at most HK_TREE_SUB tips, and the recursions are
-// carried out once, on the host, on unit vectors, which leaves two dense and
+// carried out once, in closed form, on unit vectors, which leaves two dense and
 // parallel steps per evaluation:
 //
 //   low   per subtree s (one wavefront): y = M_s z_s, the subtree's part of
@@ -27,7 +27,7 @@
 #define HK_TREE_MAX_ROOTS 1024   // more subtrees (a tree of over ~15,000 tips) take the level walk
 
 struct TreeDense {
-    int m, R;             // tips, subtrees (R = 0: none)
+    int R;                // subtrees (0: none)
     const int *tip0;      // [R + 1] first tip of each subtree, in subtree order
     const int *tip;       // [m] subset slot of each tip
     const int *sub;       // [m] its subtree

@@ -33,8 +33,11 @@
 // between levels.
 #include <hip/hip_runtime.h>
 #include <math.h>
+#include <string.h>
 
 #include <algorithm>
+#include <new>
+#include <utility>
 #include <vector>
 
 #include "hawkes_internal.h"
@@ -42,10 +45,9 @@
 
 struct hk_tree {
     int64_t m;           // tips (= subset size)
-    int64_t n_int;       // internal nodes (m - 1)
     int levels;          // height levels of internal nodes
     double logdet;       // log |V|
-    // device arrays
+    // device arrays, all in `store`
     int *order;          // [n_int] internal nodes, grouped by level (increasing height)
     int *level0;         // [levels + 1] first entry of each level in order[]
     int *child;          // [2 (2m - 1)] children of each node (internal only)
@@ -54,9 +56,8 @@ struct hk_tree {
     double *dd;          // [2m - 1] d_a per internal node
     int root;
     double root_inv;     // 1 / (v_root + tau0)
-    int *level0_h;       // host copy of level0 (launch loop bounds)
     double *pdiag;       // [m] diagonal of V^{-1}, tip (slot) order (device)
-    TreeDense dense;     // the cut tree (R = 0: none); its arrays are in `store`
+    TreeDense dense;     // the cut tree (R = 0: none)
     void *store;
 };
 
@@ -128,6 +129,60 @@ __global__ __launch_bounds__(HK_TREE_TOP_THREADS) void k_tree_top(const TreeDens
     hk_tree_top(t, blockIdx.x, vz);
 }
 
+// One inner node of a piece of the cut (a subtree, or the top with the subtrees'
+// roots for leaves): what the entries of the leaves that meet in it need.
+struct TreeStep {
+    double x, alpha_b, alpha_c;
+    int b0, b1, c0, c1;  // the leaves below its children b and c, within the piece
+};
+
+// M_s of each subtree and Q (the last block), the recursions on unit vectors in
+// closed form.  Let a node a have children b and c, and kappa_a be the adjoint of a for
+// a unit mean of a and zero ones beside it: 0 at a subtree's root, 1 / (v_root + tau0)
+// at the tree's.  Then kappa_b = alpha_b^2 kappa_a + 1/s_a, and the adjoint of b for a
+// unit mean of c is x_a = alpha_b alpha_c kappa_a - 1/s_a, so that the entry of two leaves
+// that meet in a is w x_a w', with w a leaf's weight in the mean of its child of a: the
+// product of the alphas between.  (The steps read differences: the diagonals are left
+// 0.)  A block takes its piece node by node, children first.
+//
+// Once per tree.  Formed on the host, column by column of the recursions, this was
+// most of hawkes_plan_set_tree: a balanced tree of 20,000 tips 5.2 ms, a single lineage
+// of 1,087 tips (1,023 steps at the top) 12.6 ms; now 1.1 and 0.96.
+constexpr int TREE_CUT_THREADS = 256;
+__global__ __launch_bounds__(TREE_CUT_THREADS) void k_tree_cut(const TreeStep *__restrict__ steps,
+                                                               const int *__restrict__ step0, int R,
+                                                               const int *__restrict__ tip0,
+                                                               const int64_t *__restrict__ mat0, double root_inv,
+                                                               double *__restrict__ mat, double *__restrict__ wgt,
+                                                               double *__restrict__ Q, double *__restrict__ qrow) {
+    __shared__ double w[HK_TREE_MAX_ROOTS];  // (more than HK_TREE_SUB)
+    const int s = blockIdx.x, tid = threadIdx.x;
+    const bool top = s == R;
+    const int n = top ? R : tip0[s + 1] - tip0[s];
+    double *__restrict__ out = top ? Q : mat + mat0[s];
+    for (int k = tid; k < n; k += TREE_CUT_THREADS) {
+        w[k] = 1.0;
+        out[(int64_t)k * n + k] = 0.0;
+    }
+    __syncthreads();
+    for (int e = step0[s]; e < step0[s + 1]; ++e) {
+        const TreeStep a = steps[e];
+        const int nb = a.b1 - a.b0, nc = a.c1 - a.c0;
+        for (int k = tid; k < nb * nc; k += TREE_CUT_THREADS) {
+            const int i = a.b0 + k / nc, j = a.c0 + k % nc;
+            out[(int64_t)i * n + j] = out[(int64_t)j * n + i] = w[i] * a.x * w[j];
+        }
+        __syncthreads();
+        for (int k = tid; k < nb; k += TREE_CUT_THREADS) w[a.b0 + k] *= a.alpha_b;
+        for (int k = tid; k < nc; k += TREE_CUT_THREADS) w[a.c0 + k] *= a.alpha_c;
+        __syncthreads();
+    }
+    for (int k = tid; k < n; k += TREE_CUT_THREADS) {
+        if (top) qrow[k] = w[k] * root_inv;
+        else wgt[tip0[s] + k] = w[k];
+    }
+}
+
 // z^T V^{-1} z from the subtrees' parts, by one wavefront in a fixed order
 __global__ __launch_bounds__(HK_WAVE) void k_tree_quad(const TreeDense t, double *__restrict__ quad) {
     double q = 0.0;
@@ -146,20 +201,12 @@ __global__ void k_tree_logp(const double *__restrict__ quad, const double *__res
     if (k < m && grad) grad[k] = -vz[k] / sigma2;
 }
 
-template <class T>
-hipError_t dalloc(T **p, size_t count) {
-    return hipMalloc((void **)p, count * sizeof(T) + 16);
-}
-
 }  // namespace
 
 void hk_tree_free(hawkes_plan p) {
     hk_tree *t = p->tree;
     if (!t) return;
-    void *ptrs[] = {t->order, t->level0, t->child, t->coef, t->mv, t->dd, t->pdiag, t->store};
-    for (void *q : ptrs)
-        if (q) (void)hipFree(q);
-    delete[] t->level0_h;
+    if (t->store) (void)hipFree(t->store);
     delete t;
     p->tree = nullptr;
 }
@@ -186,8 +233,8 @@ hawkes_status hk_tree_launch(hawkes_plan p, const double *d_z, double *d_vz, dou
     return HAWKES_OK;
 }
 
-extern "C" hawkes_status hawkes_plan_set_tree(hawkes_plan p, int64_t n_nodes, const int64_t *parent,
-                                              const double *length, double tau0) {
+static hawkes_status set_tree(hawkes_plan p, int64_t n_nodes, const int64_t *parent, const double *length,
+                              double tau0) {
     if (!p || !parent || !length || n_nodes < 1 || n_nodes % 2 == 0 || !(tau0 > 0.0) || !isfinite(tau0))
         return HAWKES_E_INVALID;
     const int64_t m = (n_nodes + 1) / 2;
@@ -275,6 +322,7 @@ extern "C" hawkes_status hawkes_plan_set_tree(hawkes_plan p, int64_t n_nodes, co
         }
     }
     const int H = m > 1 ? height[root] : 0;
+    const size_t M = (size_t)m;
     std::vector<int> level0(H + 1, 0), order;
     for (int64_t v = m; v < n_nodes; ++v) level0[height[v]]++;  // heights 1..H
     // level l holds height l + 1
@@ -286,143 +334,149 @@ extern "C" hawkes_status hawkes_plan_set_tree(hawkes_plan p, int64_t n_nodes, co
     std::vector<int> fill(start.begin(), start.end());
     for (int64_t v = m; v < n_nodes; ++v) order[fill[height[v] - 1]++] = (int)v;
 
-    // the cut: maximal subtrees of at most HK_TREE_SUB tips, in post-order
-    std::vector<int> tips(n_nodes, 0), subs, tip0(1, 0), tipv, subv;
-    for (int v : post) tips[v] = v < m ? 1 : tips[child[2 * v]] + tips[child[2 * v + 1]];
-    for (int v : post)
-        if (tips[v] <= HK_TREE_SUB && (parent[v] < 0 || tips[parent[v]] > HK_TREE_SUB)) subs.push_back(v);
-    const int R = (int)subs.size() <= HK_TREE_MAX_ROOTS ? (int)subs.size() : 0;
+    // the cut: maximal subtrees of at most HK_TREE_SUB tips, in post-order, so that
+    // they and the leaves of each node are contiguous in it
+    const size_t N = (size_t)n_nodes;
+    std::vector<int> tips(N, 0), tip0(1, 0), tipv;
     std::vector<int64_t> mat0;
-    std::vector<double> mat, wgt, Q((size_t)R * R), qrow(R);
-    if (R > 0) {
-        std::vector<double> mean(n_nodes, 0.0), adj(n_nodes, 0.0);
-        // the recursions over the internal nodes `in` (children before parents):
-        // from the means of what lies below them and the adjoint of the last one
-        const auto up_down = [&](const std::vector<int> &in) {
-            for (int v : in)
-                mean[v] = coef[3 * (size_t)v] * mean[child[2 * v]] + coef[3 * (size_t)v + 1] * mean[child[2 * v + 1]];
-            for (auto it = in.rbegin(); it != in.rend(); ++it) {
-                const int v = *it, b = child[2 * v], c = child[2 * v + 1];
-                const double d = (mean[b] - mean[c]) * coef[3 * (size_t)v + 2];
-                adj[b] = coef[3 * (size_t)v] * adj[v] + d;
-                adj[c] = coef[3 * (size_t)v + 1] * adj[v] - d;
-            }
-        };
-        std::vector<int> at(n_nodes, 0);  // place in the post-order
-        for (size_t k = 0; k < post.size(); ++k) at[post[k]] = (int)k;
-        for (int s = 0; s < R; ++s) {
-            // a subtree's nodes end at its root in the post-order
-            const int v = subs[s], nt = tips[v], first = at[v] - (2 * nt - 2);
-            std::vector<int> in, leaf;
-            for (int k = first; k <= at[v]; ++k) (post[k] < m ? leaf : in).push_back(post[k]);
-            mat0.push_back((int64_t)mat.size());
-            for (int k : leaf) mean[k] = 0.0;
-            for (int j = 0; j < nt; ++j) {  // column j of M_s: unit mean at tip j, no adjoint from above
-                mean[leaf[j]] = 1.0;
-                adj[v] = 0.0;
-                up_down(in);
-                for (int k : leaf) mat.push_back(adj[k]);
-                mean[leaf[j]] = 0.0;
-            }
-            adj[v] = 1.0;  // the weights: no means, unit adjoint from above
-            up_down(in);
-            for (int k : leaf) {
-                wgt.push_back(adj[k]);
-                tipv.push_back(k);
-                subv.push_back(s);
-            }
-            tip0.push_back((int)tipv.size());
-        }
-        std::vector<int> top;
-        for (int v : post)
-            if (tips[v] > HK_TREE_SUB) top.push_back(v);
-        for (int v : subs) mean[v] = 0.0;
-        for (int s = 0; s <= R; ++s) {  // columns of Q, then (all means 1) its row sums
-            for (int v : subs) mean[v] = s == R ? 1.0 : 0.0;
-            if (s < R) mean[subs[s]] = 1.0;
-            // the root's mean is needed before its adjoint
-            for (int v : top)
-                mean[v] = coef[3 * (size_t)v] * mean[child[2 * v]] + coef[3 * (size_t)v + 1] * mean[child[2 * v + 1]];
-            adj[root] = mean[root] / rv;
-            up_down(top);
-            for (int r = 0; r < R; ++r) (s < R ? Q[(size_t)s * R + r] : qrow[r]) = adj[subs[r]];
-        }
+    std::vector<char> is_sub(N, 0);
+    size_t n_mat = 0;
+    for (int v : post) {
+        tips[v] = v < m ? 1 : tips[child[2 * v]] + tips[child[2 * v + 1]];
+        if (v < m) tipv.push_back(v);
     }
+    for (int v : post) {
+        if (tips[v] > HK_TREE_SUB || (parent[v] >= 0 && tips[parent[v]] <= HK_TREE_SUB)) continue;
+        is_sub[v] = 1;
+        mat0.push_back((int64_t)n_mat);
+        tip0.push_back(tip0.back() + tips[v]);
+        n_mat += (size_t)tips[v] * tips[v];
+    }
+    const int R = mat0.size() <= HK_TREE_MAX_ROOTS ? (int)mat0.size() : 0;
+    // its steps for k_tree_cut: the subtrees' inner nodes, then the top's, children first
+    std::vector<int> step0(1, 0), sub(m);
+    std::vector<TreeStep> steps;
+    if (R > 0) {
+        std::vector<double> kappa(N, 0.0), x(N, 0.0);
+        kappa[root] = 1.0 / rv;
+        for (auto it = post.rbegin(); it != post.rend(); ++it) {
+            const int v = *it;
+            if (is_sub[v]) kappa[v] = 0.0;
+            if (v < m) continue;
+            const double ab = coef[3 * (size_t)v], ac = coef[3 * (size_t)v + 1], is = coef[3 * (size_t)v + 2];
+            x[v] = ab * ac * kappa[v] - is;
+            kappa[child[2 * v]] = ab * ab * kappa[v] + is;
+            kappa[child[2 * v + 1]] = ac * ac * kappa[v] + is;
+        }
+        std::vector<int> first(N), last(N);  // leaves of each node within its piece
+        steps.reserve(N - M);
+        const auto step = [&](int v) {
+            const int b = child[2 * v], c = child[2 * v + 1];
+            steps.push_back({x[v], coef[3 * (size_t)v], coef[3 * (size_t)v + 1], first[b], last[b], first[c], last[c]});
+            first[v] = std::min(first[b], first[c]);
+            last[v] = std::max(last[b], last[c]);
+        };
+        int leaf = 0, r = 0;
+        for (int v : post) {
+            if (tips[v] > HK_TREE_SUB) continue;
+            if (v < m) {
+                sub[tip0[r] + leaf] = r;
+                first[v] = leaf++;
+                last[v] = leaf;
+            } else {
+                step(v);
+            }
+            if (is_sub[v]) {
+                step0.push_back((int)steps.size());
+                first[v] = r++;
+                last[v] = r;
+                leaf = 0;
+            }
+        }
+        for (int v : post)
+            if (tips[v] > HK_TREE_SUB) step(v);
+        step0.push_back((int)steps.size());
+    } else {
+        mat0.clear();
+        tip0.clear();
+        tipv.clear();
+        sub.clear();
+        n_mat = 0;
+    }
+
+    // one allocation, filled by one copy: 8-byte arrays, then integers; then what the
+    // device writes
+    std::vector<char> host;
+    host.reserve(8 * (4 * N + M + R) + sizeof(TreeStep) * steps.size() + 4 * (6 * N + 2 * M + R) + 256);
+    const auto put = [&](const auto &v) {
+        const size_t at = (host.size() + 7) / 8 * 8, bytes = sizeof(v[0]) * v.size();
+        host.resize(at + bytes);
+        if (bytes) memcpy(host.data() + at, v.data(), bytes);
+        return at;
+    };
+    const size_t o_coef = put(coef), o_pdiag = put(pdiag), o_steps = put(steps), o_mat0 = put(mat0), o_order = put(order),
+                 o_level0 = put(start), o_child = put(child), o_step0 = put(step0), o_tip0 = put(tip0), o_tip = put(tipv),
+                 o_sub = put(sub);
+    const size_t RR = (size_t)R, host_bytes = (host.size() + 7) / 8 * 8;
+    const size_t n_dev = 2 * N + (R > 0 ? n_mat + 2 * M + RR * RR + 4 * RR : 0);
 
     hk_tree_free(p);
     hk_tree *t = new hk_tree();
     p->tree = t;
     t->dense = TreeDense{};
-    t->store = nullptr;
     t->m = m;
-    t->n_int = n_nodes - m;
     t->levels = H;
     t->logdet = logdet;
     t->root = (int)root;
     t->root_inv = 1.0 / rv;
-    t->level0_h = new int[H + 1];
-    for (int l = 0; l <= H; ++l) t->level0_h[l] = start[l];
-#define TC(call)                                                              \
-    do {                                                                      \
-        hipError_t e_ = (call);                                               \
-        if (e_ != hipSuccess) {                                               \
-            hk_tree_free(p);                                                  \
-            return e_ == hipErrorOutOfMemory ? HAWKES_E_NOMEM : HAWKES_E_DEVICE; \
-        }                                                                     \
-    } while (0)
-    TC(dalloc(&t->order, order.size()));
-    TC(dalloc(&t->level0, (size_t)H + 1));
-    TC(dalloc(&t->child, child.size()));
-    TC(dalloc(&t->coef, coef.size()));
-    TC(dalloc(&t->mv, (size_t)n_nodes));
-    TC(dalloc(&t->dd, (size_t)n_nodes));
-    TC(dalloc(&t->pdiag, (size_t)m));
-    TC(hipMemcpy(t->order, order.data(), sizeof(int) * order.size(), hipMemcpyHostToDevice));
-    TC(hipMemcpy(t->level0, start.data(), sizeof(int) * (H + 1), hipMemcpyHostToDevice));
-    TC(hipMemcpy(t->child, child.data(), sizeof(int) * child.size(), hipMemcpyHostToDevice));
-    TC(hipMemcpy(t->coef, coef.data(), sizeof(double) * coef.size(), hipMemcpyHostToDevice));
-    TC(hipMemcpy(t->pdiag, pdiag.data(), sizeof(double) * m, hipMemcpyHostToDevice));
-    if (R > 0) {
-        // one allocation for the cut tree: 8-byte arrays, then the integers
-        const size_t nd = mat.size() + 2 * (size_t)m + Q.size() + 4 * (size_t)R, ni = 2 * (size_t)m + R + 1;
-        double *d;
-        TC(hipMalloc((void **)&d, sizeof(double) * (nd + R) + sizeof(int) * ni + 64));
-        t->store = d;
+    t->store = nullptr;
+    hipError_t e = hipMalloc(&t->store, host_bytes + 8 * n_dev);
+    if (e == hipSuccess) e = hipMemcpy(t->store, host.data(), host.size(), hipMemcpyHostToDevice);
+    char *const base = (char *)t->store;
+    double *dev = (double *)(base + host_bytes);
+    const auto take = [&](size_t n) { return std::exchange(dev, dev + n); };
+    t->coef = (double *)(base + o_coef);
+    t->pdiag = (double *)(base + o_pdiag);
+    t->order = (int *)(base + o_order);
+    t->level0 = (int *)(base + o_level0);
+    t->child = (int *)(base + o_child);
+    t->mv = take(N);
+    t->dd = take(N);
+    if (R > 0 && e == hipSuccess) {
+        double *mat = take(n_mat), *w = take(M), *Q = take(RR * RR), *qrow = take(RR);
         TreeDense &td = t->dense;
-        td.m = (int)m;
         td.R = R;
-        const auto put = [&](const void *src, size_t bytes) {
-            void *dst = d;
-            d = (double *)((char *)d + (bytes + 7) / 8 * 8);
-            return src ? hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice) : hipSuccess;
-        };
-        td.mat = d;
-        TC(put(mat.data(), sizeof(double) * mat.size()));
-        td.w = d;
-        TC(put(wgt.data(), sizeof(double) * m));
-        td.Q = d;
-        TC(put(Q.data(), sizeof(double) * Q.size()));
-        td.qrow = d;
-        TC(put(qrow.data(), sizeof(double) * R));
-        td.mat0 = (const int64_t *)d;
-        TC(put(mat0.data(), sizeof(int64_t) * R));
-        td.y = d;
-        TC(put(nullptr, sizeof(double) * m));
-        td.mean = d;
-        TC(put(nullptr, sizeof(double) * R));
-        td.qlow = d;
-        TC(put(nullptr, sizeof(double) * R));
-        td.quad = d;
-        TC(put(nullptr, sizeof(double) * R));
-        td.tip0 = (const int *)d;
-        TC(put(tip0.data(), sizeof(int) * (R + 1)));
-        td.tip = (const int *)d;
-        TC(put(tipv.data(), sizeof(int) * m));
-        td.sub = (const int *)d;
-        TC(put(subv.data(), sizeof(int) * m));
+        td.tip0 = (int *)(base + o_tip0);
+        td.tip = (int *)(base + o_tip);
+        td.sub = (int *)(base + o_sub);
+        td.mat0 = (int64_t *)(base + o_mat0);
+        td.mat = mat;
+        td.w = w;
+        td.Q = Q;
+        td.qrow = qrow;
+        td.y = take(M);
+        td.mean = take(RR);
+        td.qlow = take(RR);
+        td.quad = take(RR);
+        hipLaunchKernelGGL(k_tree_cut, dim3(R + 1), dim3(TREE_CUT_THREADS), 0, 0, (const TreeStep *)(base + o_steps),
+                           (const int *)(base + o_step0), R, td.tip0, td.mat0, t->root_inv, mat, w, Q, qrow);
+        e = hipGetLastError();
+        if (e == hipSuccess) e = hipStreamSynchronize(0);
     }
-#undef TC
+    if (e != hipSuccess) {
+        hk_tree_free(p);
+        return e == hipErrorOutOfMemory ? HAWKES_E_NOMEM : HAWKES_E_DEVICE;
+    }
     return HAWKES_OK;
+}
+
+extern "C" hawkes_status hawkes_plan_set_tree(hawkes_plan p, int64_t n_nodes, const int64_t *parent,
+                                              const double *length, double tau0) {
+    try {
+        return set_tree(p, n_nodes, parent, length, tau0);
+    } catch (const std::bad_alloc &) {  // (the plan's former tree, if any, is still set)
+        return HAWKES_E_NOMEM;
+    }
 }
 
 extern "C" hawkes_status hawkes_tree_prior(hawkes_plan p, const double *d_z, double sigma, double *d_logp,

@@ -712,3 +712,61 @@ def test_subset_row_forms_by_chunks_match_full_evaluation(gpu, n):
     assert np.max(np.abs(g - gi) / np.maximum(gi + 2 * a, 1e-300)) < 2e-6
     assert h_rel_all(h, hi) < 2e-6
     plan.close()
+
+
+@pytest.mark.parametrize("name", ["balanced-2048", "balanced-2049", "coalescent-130", "caterpillar-200"])
+def test_tree_prior_with_zero_branches(gpu, name):
+    """Trees with zero-length branches (a tip, or a subtree, at its parent), against the
+    recursions node by node: log p, its gradient and the quadratic form, FP64
+    throughout, 1e-10 relative."""
+    import torch
+
+    from paper_2103_03348_amd import _lib
+    from paper_2103_03348_amd.hawkes import Plan
+
+    par, ln = (np.ascontiguousarray(v) for v in _tree_shape(name))
+    n = par.shape[0]
+    m, tau0, sigma = (n + 1) // 2, 0.9, 0.5
+    rng = np.random.default_rng(m)
+    kids = [np.where(par == v)[0] for v in range(m, n)]
+    ln = ln.copy()
+    for b, c in kids:
+        if rng.random() < 0.3:
+            ln[b if rng.random() < 0.5 else c] = 0.0
+    # nodes m.. are numbered children first
+    z = rng.standard_normal(m)
+    mean, var, logdet, quad = np.concatenate([z, np.zeros(m - 1)]), np.zeros(n), 0.0, 0.0
+    for v, (b, c) in zip(range(m, n), kids):
+        vb, vc = var[b] + ln[b], var[c] + ln[c]
+        var[v] = vb * vc / (vb + vc)
+        mean[v] = (vc * mean[b] + vb * mean[c]) / (vb + vc)
+        logdet += np.log(vb + vc)
+        quad += (mean[b] - mean[c]) ** 2 / (vb + vc)
+    logdet += np.log(var[-1] + tau0)
+    quad += mean[-1] ** 2 / (var[-1] + tau0)
+    adj = np.zeros(n)
+    adj[-1] = mean[-1] / (var[-1] + tau0)
+    for v, (b, c) in reversed(list(zip(range(m, n), kids))):
+        vb, vc = var[b] + ln[b], var[c] + ln[c]
+        d = (mean[b] - mean[c]) / (vb + vc)
+        adj[b], adj[c] = vc / (vb + vc) * adj[v] + d, vb / (vb + vc) * adj[v] - d
+    logp = -0.5 * (m * np.log(2 * np.pi * sigma ** 2) + logdet + quad / sigma ** 2)
+
+    es = synth.small(300, seed=46)
+    plan = Plan.from_numpy(es.t, es.x, es.y, es.t0)
+    _lib.check(_lib.lib().hawkes_plan_set_tree(plan.handle, n, par.ctypes.data_as(ctypes.c_void_p),
+                                               ln.ctypes.data_as(ctypes.c_void_p), tau0), "set_tree")
+    dz = torch.as_tensor(z, device="cuda:0")
+    lp, q = (torch.zeros(1, dtype=torch.float64, device="cuda:0") for _ in range(2))
+    g = torch.zeros(m, dtype=torch.float64, device="cuda:0")
+    for want in ((lp, g), (lp, None), (None, None)):
+        lp.zero_(), g.zero_(), q.zero_()
+        _lib.check(_lib.lib().hawkes_tree_prior(plan.handle, _lib.ptr(dz), sigma, _lib.ptr(want[0]),
+                                                _lib.ptr(want[1]), _lib.ptr(q), _lib.stream_handle()), "tree_prior")
+        torch.cuda.synchronize()
+        assert abs(q.item() - quad) <= 1e-10 * quad
+        if want[0] is not None:
+            assert abs(lp.item() - logp) <= 1e-10 * abs(logp)
+        if want[1] is not None:
+            assert np.max(np.abs(g.cpu().numpy() + adj[:m] / sigma ** 2)) <= 1e-10 * np.max(np.abs(adj[:m])) / sigma ** 2
+    plan.close()
