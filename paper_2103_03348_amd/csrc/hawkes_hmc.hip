@@ -1640,7 +1640,7 @@ extern "C" hawkes_status hmc_step(hawkes_plan p, const hawkes_hyper *hyper, hawk
                            off, s->p, a->d_mass, s->slot, s->a, m,
                            td ? td->quad : walk ? s->quad : (const double *)nullptr, td ? td->R : walk ? 1 : 0, e);
     };
-    if (walk && (st = hk_tree_launch(p, a->d_z, s->vz, s->quad, stream)) != HAWKES_OK) return st;
+    if (walk && (st = hk_tree_walk(p, a->d_z, s->vz, s->quad, stream)) != HAWKES_OK) return st;
     SubUpd upd{s->slot, a->d_z, off, pv, inv_s2, s->p, a->d_mass, 0.5 * a->eps, a->eps, s->tv, s->sts, s->qwide,
                kc.omega};
     // (the energy comes before the first kick and drift, and after the prior's top
@@ -1653,7 +1653,7 @@ extern "C" hawkes_status hmc_step(hawkes_plan p, const hawkes_hyper *hyper, hawk
         // closing half kick after the last one
         const bool last = l == a->L - 1;
         sub_rows(p, SUB_STAGED, a->d_z, off, a->d_theta, kc, fc, stream, td);
-        if (walk && (st = hk_tree_launch(p, a->d_z, s->vz, s->quad, stream)) != HAWKES_OK) return st;
+        if (walk && (st = hk_tree_walk(p, a->d_z, s->vz, s->quad, stream)) != HAWKES_OK) return st;
         upd.a_p = last ? 0.5 * a->eps : a->eps;
         upd.a_z = last ? 0.0 : a->eps;
         sub_col_pass(p, false, kc, stream, td);

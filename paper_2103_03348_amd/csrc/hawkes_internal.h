@@ -149,9 +149,9 @@ struct hawkes_plan_s {
 };
 
 hipError_t hk_sort_pairs(double *key, int *idx, int64_t n2, hipStream_t stream);
-// Phylogenetic prior (hawkes_tree.hip): d_vz [m] = V^{-1} z and d_quad [1] =
-// z^T V^{-1} z for z [m] in subset slot order (either output may be NULL).
-hawkes_status hk_tree_launch(hawkes_plan p, const double *d_z, double *d_vz, double *d_quad, hipStream_t stream);
+// Phylogenetic prior (hawkes_tree.hip) by its level walk: d_vz [m] = V^{-1} z and
+// d_quad [1] = z^T V^{-1} z for z [m] in subset slot order (either output may be NULL).
+hawkes_status hk_tree_walk(hawkes_plan p, const double *d_z, double *d_vz, double *d_quad, hipStream_t stream);
 int64_t hk_tree_tips(hawkes_plan p);
 // diagonal of V^{-1} of the plan's tree [m], slot order (device), or NULL
 const double *hk_tree_precision_diag(hawkes_plan p);

@@ -64,6 +64,12 @@ struct hk_tree {
 namespace {
 
 constexpr int TREE_THREADS = 1024;
+// hawkes_tree_prior alone takes the level walk for a tree of at most this many levels:
+// one launch of some 10 dependent levels against the dense steps' two (a balanced tree
+// of 400 / 1,600 / 3,000 / 6,000 tips, 9 / 11 / 12 / 13 levels, walk 12.1 / 14.9 / 17.4 /
+// 23.2 us, dense 15.6 / 16.2 / 16.4 / 17.6; a random one of 128 / 800, 15 / 23 levels,
+// 14.8 / 21.3 and 14.0 / 15.4).  In hmc_step the dense steps cost no launch.
+constexpr int TREE_WALK_LEVELS = 11;
 
 __global__ __launch_bounds__(TREE_THREADS) void k_tree_prior(const double *__restrict__ z, int64_t m,
                                                              const int *__restrict__ order,
@@ -183,21 +189,23 @@ __global__ __launch_bounds__(TREE_CUT_THREADS) void k_tree_cut(const TreeStep *_
     }
 }
 
-// z^T V^{-1} z from the subtrees' parts, by one wavefront in a fixed order
-__global__ __launch_bounds__(HK_WAVE) void k_tree_quad(const TreeDense t, double *__restrict__ quad) {
-    double q = 0.0;
-    for (int r = threadIdx.x; r < t.R; r += HK_WAVE) q += t.quad[r];
-    for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o);
-    if (threadIdx.x == 0) quad[0] = q;
-}
-
-// log p(z) = -(m log(2 pi sigma^2) + log|V| + z^T V^{-1} z / sigma^2) / 2 and
-// its gradient -V^{-1} z / sigma^2
-__global__ void k_tree_logp(const double *__restrict__ quad, const double *__restrict__ vz, int64_t m,
-                            double sigma2, double logdet, double *__restrict__ logp, double *__restrict__ grad) {
+// z^T V^{-1} z from the subtrees' parts (by one wavefront in a fixed order; without
+// parts it is in `quad`), log p(z) = -(m log(2 pi sigma^2) + log|V| + z^T V^{-1} z /
+// sigma^2) / 2 and its gradient -V^{-1} z / sigma^2
+__global__ void k_tree_logp(const double *__restrict__ parts, int np, double *__restrict__ quad,
+                            const double *__restrict__ vz, int64_t m, double sigma2, double logdet,
+                            double *__restrict__ logp, double *__restrict__ grad) {
     const int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (k == 0 && logp)
-        logp[0] = -0.5 * ((double)m * log(2.0 * 3.141592653589793 * sigma2) + logdet + quad[0] / sigma2);
+    if (k < HK_WAVE) {
+        double q = 0.0;
+        for (int r = (int)k; r < np; r += HK_WAVE) q += parts[r];
+        for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o);
+        if (k == 0) {
+            if (parts) quad[0] = q;
+            else q = quad[0];
+            if (logp) logp[0] = -0.5 * ((double)m * log(2.0 * 3.141592653589793 * sigma2) + logdet + q / sigma2);
+        }
+    }
     if (k < m && grad) grad[k] = -vz[k] / sigma2;
 }
 
@@ -217,18 +225,11 @@ const double *hk_tree_precision_diag(hawkes_plan p) { return p->tree ? p->tree->
 
 const TreeDense *hk_tree_dense(hawkes_plan p) { return p->tree && p->tree->dense.R > 0 ? &p->tree->dense : nullptr; }
 
-hawkes_status hk_tree_launch(hawkes_plan p, const double *d_z, double *d_vz, double *d_quad, hipStream_t stream) {
+hawkes_status hk_tree_walk(hawkes_plan p, const double *d_z, double *d_vz, double *d_quad, hipStream_t stream) {
     hk_tree *t = p->tree;
     if (!t) return HAWKES_E_UNSUPPORTED;
-    if (const TreeDense *td = hk_tree_dense(p)) {
-        hipLaunchKernelGGL(k_tree_low, dim3(td->R), dim3(HK_WAVE), 0, stream, *td, d_z);
-        hipLaunchKernelGGL(k_tree_top, dim3(hk_tree_top_blocks(td->R)), dim3(HK_TREE_TOP_THREADS), 0, stream, *td,
-                           d_vz ? d_vz : t->mv);
-        if (d_quad) hipLaunchKernelGGL(k_tree_quad, dim3(1), dim3(HK_WAVE), 0, stream, *td, d_quad);
-    } else {
-        hipLaunchKernelGGL(k_tree_prior, dim3(1), dim3(TREE_THREADS), 0, stream, d_z, t->m, t->order, t->level0,
-                           t->levels, t->child, t->coef, t->root, t->root_inv, t->mv, t->dd, d_vz, d_quad);
-    }
+    hipLaunchKernelGGL(k_tree_prior, dim3(1), dim3(TREE_THREADS), 0, stream, d_z, t->m, t->order, t->level0, t->levels,
+                       t->child, t->coef, t->root, t->root_inv, t->mv, t->dd, d_vz, d_quad);
     HK_CHECK(hipGetLastError());
     return HAWKES_OK;
 }
@@ -485,12 +486,20 @@ extern "C" hawkes_status hawkes_tree_prior(hawkes_plan p, const double *d_z, dou
     hk_tree *t = p->tree;
     if (!t) return HAWKES_E_UNSUPPORTED;
     p->last_stream = stream;
-    double *vz = t->mv;  // the adjoints of the tips are left in mv[0..m)
-    hawkes_status st = hk_tree_launch(p, d_z, nullptr, d_quad, stream);
-    if (st != HAWKES_OK) return st;
-    if (d_logp || d_grad)
-        hipLaunchKernelGGL(k_tree_logp, dim3((unsigned)((t->m + 255) / 256)), dim3(256), 0, stream, d_quad, vz, t->m,
-                           sigma * sigma, t->logdet, d_logp, d_grad);
+    // the walk leaves the adjoints of the tips in mv[0..m), the dense steps V^{-1} z there
+    const TreeDense *td = t->levels > TREE_WALK_LEVELS ? hk_tree_dense(p) : nullptr;
+    if (td) {
+        hipLaunchKernelGGL(k_tree_low, dim3(td->R), dim3(HK_WAVE), 0, stream, *td, d_z);
+        hipLaunchKernelGGL(k_tree_top, dim3(hk_tree_top_blocks(td->R)), dim3(HK_TREE_TOP_THREADS), 0, stream, *td,
+                           t->mv);
+    } else {
+        const hawkes_status st = hk_tree_walk(p, d_z, nullptr, d_quad, stream);
+        if (st != HAWKES_OK) return st;
+    }
+    if (td || d_logp || d_grad)
+        hipLaunchKernelGGL(k_tree_logp, dim3(d_grad ? (unsigned)((t->m + 255) / 256) : 1), dim3(256), 0, stream,
+                           td ? td->quad : (const double *)nullptr, td ? td->R : 0, d_quad, t->mv, t->m, sigma * sigma,
+                           t->logdet, d_logp, d_grad);
     HK_CHECK(hipGetLastError());
     return HAWKES_OK;
 }

@@ -716,7 +716,8 @@ def test_subset_row_forms_by_chunks_match_full_evaluation(gpu, n):
 
 @pytest.mark.parametrize("name", ["balanced-2048", "balanced-2049", "coalescent-130", "caterpillar-200"])
 def test_tree_prior_with_zero_branches(gpu, name):
-    """Trees with zero-length branches (a tip, or a subtree, at its parent), against the
+    """Trees with zero-length branches (a tip, or a subtree, at its parent), on either
+    side of the 11 levels up to which the prior alone walks them, against the
     recursions node by node: log p, its gradient and the quadratic form, FP64
     throughout, 1e-10 relative."""
     import torch
