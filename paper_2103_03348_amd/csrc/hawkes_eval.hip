@@ -420,7 +420,12 @@ __global__ __launch_bounds__(HK_TILE, 4) void k_row(const double *__restrict__ t
         bool have_ui = false;
         // a chunk's columns are loaded one chunk ahead, after the previous chunk's
         // sweep: their latency overlaps its column reduction (and, for a piece's
-        // first chunk, the row's own loads), and they hold no registers in a sweep
+        // first chunk, the row's own loads), and they hold no registers in a sweep.  Not
+        // for the log-likelihood alone, whose row pass then has 90 registers instead of
+        // 98 and five wavefronts per SIMD instead of four: N = 23,422 / 70,000 / 150,000 /
+        // 250,000, 170 / 1,273 / 5,816 / 16,189 us with it, 167 / 1,240 / 5,752 / 16,036
+        // without, under the cutoff 139 / 632 / 1,859 / 3,190 and 136 / 601 / 1,772 / 3,037
+        constexpr bool AHEAD = SELF || MODE >= HK_MODE_GRAD;
         double st = 0.0, sx = 0.0, sy = 0.0;
         float sv = 0.0f;
         double sth = 0.0;
@@ -434,7 +439,7 @@ __global__ __launch_bounds__(HK_TILE, 4) void k_row(const double *__restrict__ t
                 sy = ys[j];
             }
         };
-        fetch(it.c_end - 1);
+        if (AHEAD) fetch(it.c_end - 1);
         for (int c = it.c_end - 1; c >= it.c_begin; --c) {
             if (SELF) have_ui = false;
             if (have_ui) ui *= tstep[c];
@@ -448,6 +453,7 @@ __global__ __launch_bounds__(HK_TILE, 4) void k_row(const double *__restrict__ t
             // fast form: times relative to the chunk's first event, rounded to FP32
             const double Tc = ts[(int64_t)c * HK_WAVE];
             const float ti = (float)((tsi - Tc) * kc.st);  // scaled time
+            bool fact = AHEAD || chunk_precise[c] == 0;
             if (SELF && tid < HK_WAVE) {
                 if (bad_rate(sth)) atomicOr(status, HK_ST_BADTHETA);
                 const bool precise = __any((int64_t)c * HK_WAVE + tid < n && st - Tc > kc.span_max);
@@ -455,6 +461,7 @@ __global__ __launch_bounds__(HK_TILE, 4) void k_row(const double *__restrict__ t
                 if (tid == 0) L.precise = precise;
             }
             if (block_live && tid < HK_WAVE) {
+                if (!AHEAD) fetch(c);
                 float2 r;
                 r.x = (float)((st - Tc) * kc.st);
                 r.y = sv;  // theta_j, times exp(omega (t_j - T_c)) on a fast chunk
@@ -466,7 +473,7 @@ __global__ __launch_bounds__(HK_TILE, 4) void k_row(const double *__restrict__ t
                 rtd[tid] = rtd[tid + HK_WAVE] = st * kc.st;  // the precise form's FP64 scaled time
             }
             __syncthreads();
-            const bool fact = SELF ? L.precise == 0 : chunk_precise[c] == 0;
+            if (AHEAD) fact = SELF ? L.precise == 0 : chunk_precise[c] == 0;
             // the wave's column slots start at zero (the previous chunk's reads of
             // them ended before the barrier above)
             colacc0[wv][lane] = 0.0;
@@ -513,7 +520,7 @@ __global__ __launch_bounds__(HK_TILE, 4) void k_row(const double *__restrict__ t
                     have_ui = false;
                 }
             }
-            if (c > it.c_begin) fetch(c - 1);
+            if (AHEAD && c > it.c_begin) fetch(c - 1);
             // after 64 rotation steps lane l holds the accumulators of column (l - 1) mod 64
             const int col = (lane + HK_WAVE - 1) & (HK_WAVE - 1);
 #pragma unroll
@@ -1490,9 +1497,10 @@ void hk_launch_row_loglik(hawkes_plan p, const PairConst &kc, const double *d_th
 // two rounds of equal-weight blocks measured faster than one (the hardware
 // dispatcher then evens out the blocks' run-time differences), while more
 // rounds cost more partial-sum traffic than they gain.  The column pass, whose
-// pieces are shorter in time, takes half as many again (evaluation of N = 23,422
-// events, 16 / 20 / 24 / 32 / 48 blocks: 362.3 / 361.6 / 361.0 / 363.1 / 366.5 us;
-// gradient of 60,000: 1,650 / 1,647 / 1,638 / 1,638 / 1,633).
+// pieces are shorter in time, takes half as many again, which evens out what the
+// cutoff leaves of them (gradient, timed in turn, 16 / 24 blocks: N = 23,422 289.0 /
+// 286.4 us, under the cutoff 234.5 / 231.4, 40,000 751.0 / 747.4 and 480.3 / 466.5,
+// 65,280 1,899 / 1,888 and 960.5 / 918.1; runs of one side differ by some 0.5%).
 #ifndef HK_BLOCKS_PER_CU
 #define HK_BLOCKS_PER_CU 16
 #endif
