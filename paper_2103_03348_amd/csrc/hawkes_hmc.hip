@@ -46,6 +46,7 @@ struct hk_subset {
     int *slot;           // [mpad] caller's subset slot k of entry r
     int64_t *cidx;       // [m] caller index of slot k (copy of the caller's idx)
     unsigned char *member;  // [npad] 1 where the sorted event is in the subset
+    int *sched;          // the integers of the schedules below, one allocation
     int *cnt;            // [nchunks] subset entries before each row chunk's end (a prefix)
     // row pass schedule of larger sets (n_ritems = 0: a block per row chunk instead):
     // (row chunk, range of subset entries before its end)
@@ -1264,7 +1265,7 @@ inline unsigned nblk(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
 void hk_subset_free(hawkes_plan p) {
     hk_subset *s = p->sub;
     if (!s) return;
-    void *ptrs[] = {s->pos, s->slot, s->cidx, s->cnt, s->ritems, s->ritem0, s->rnseg, s->xpart, s->items, s->item0, s->nseg,
+    void *ptrs[] = {s->pos, s->slot, s->cidx, s->sched, s->xpart,
                     s->member, s->lam_static, s->Lam_static, s->a, s->tv, s->sxy, s->sts, s->qwide, s->qstep, s->lw, s->colG, s->gsub, s->z0, s->p, s->off, s->vz, s->scal, s->quad,
                     s->grid};
     for (void *q : ptrs)
@@ -1350,6 +1351,7 @@ extern "C" hawkes_status hawkes_plan_set_subset(hawkes_plan p, int64_t m, const 
                                                                                    (SUB_ROW_ITEMS * HK_WAVE))) *
                        HK_WAVE;
     std::vector<hk_item> ritems;
+    ritems.reserve(batches * HK_WAVE / br + nch);
     std::vector<int> ritem0(nch), rnseg(nch);
     const bool blocks = batches <= SUB_BLOCK_ITEMS && m <= SUB_BLOCK_ENTRIES && nch <= SUB_BLOCK_CHUNKS;
     for (int b = 0; b < nch && !blocks; ++b) {
@@ -1368,6 +1370,7 @@ extern "C" hawkes_status hawkes_plan_set_subset(hawkes_plan p, int64_t m, const 
     const int sc = (int)std::min<int64_t>(SUB_ITEM_BATCHES,
                                           std::max<int64_t>(1, (wcol + SUB_COL_ITEMS - 1) / SUB_COL_ITEMS));
     std::vector<hk_item> items;
+    items.reserve(wcol / sc + nq_live);
     std::vector<int> item0(s->nq, 0), nseg(s->nq, 0);
     for (int q = 0; q < nq_live; ++q) {
         const int first = hpos[(size_t)q * HK_WAVE] / HK_WAVE;
@@ -1379,24 +1382,28 @@ extern "C" hawkes_status hawkes_plan_set_subset(hawkes_plan p, int64_t m, const 
     for (int q = nq_live; q < s->nq; ++q) item0[q] = (int)items.size();
     s->max_nseg = *std::max_element(nseg.begin(), nseg.end());
     s->n_items = (int)items.size();
-    SC(dalloc(&s->cnt, nch));
-    SC(hipMemcpy(s->cnt, cnt.data(), sizeof(int) * nch, hipMemcpyHostToDevice));
     s->n_ritems = (int)ritems.size();
-    if (s->n_ritems > 0) {
-        SC(dalloc(&s->ritems, ritems.size()));
-        SC(dalloc(&s->ritem0, nch));
-        SC(dalloc(&s->rnseg, nch));
-        SC(dalloc(&s->xpart, ritems.size() * HK_WAVE));
-        SC(hipMemcpy(s->ritems, ritems.data(), sizeof(hk_item) * ritems.size(), hipMemcpyHostToDevice));
-        SC(hipMemcpy(s->ritem0, ritem0.data(), sizeof(int) * nch, hipMemcpyHostToDevice));
-        SC(hipMemcpy(s->rnseg, rnseg.data(), sizeof(int) * nch, hipMemcpyHostToDevice));
-    }
-    SC(dalloc(&s->items, items.size()));
-    SC(dalloc(&s->item0, s->nq));
-    SC(dalloc(&s->nseg, s->nq));
-    SC(hipMemcpy(s->items, items.data(), sizeof(hk_item) * items.size(), hipMemcpyHostToDevice));
-    SC(hipMemcpy(s->item0, item0.data(), sizeof(int) * s->nq, hipMemcpyHostToDevice));
-    SC(hipMemcpy(s->nseg, nseg.data(), sizeof(int) * s->nq, hipMemcpyHostToDevice));
+    // the schedules in one allocation, filled by one copy (all of them integers)
+    std::vector<int> host;
+    host.reserve(4 * (ritems.size() + items.size()) + 3 * (size_t)nch + 2 * (size_t)s->nq);
+    const auto put = [&](const auto &v) {
+        const size_t at = host.size();
+        host.resize(at + sizeof(v[0]) / sizeof(int) * v.size());
+        if (!v.empty()) memcpy(host.data() + at, v.data(), sizeof(v[0]) * v.size());
+        return at;
+    };
+    const size_t o_ritems = put(ritems), o_items = put(items), o_cnt = put(cnt), o_ritem0 = put(ritem0),
+                 o_rnseg = put(rnseg), o_item0 = put(item0), o_nseg = put(nseg);
+    SC(dalloc(&s->sched, host.size()));
+    SC(hipMemcpy(s->sched, host.data(), sizeof(int) * host.size(), hipMemcpyHostToDevice));
+    s->ritems = (hk_item *)(s->sched + o_ritems);
+    s->items = (hk_item *)(s->sched + o_items);
+    s->cnt = s->sched + o_cnt;
+    s->ritem0 = s->sched + o_ritem0;
+    s->rnseg = s->sched + o_rnseg;
+    s->item0 = s->sched + o_item0;
+    s->nseg = s->sched + o_nseg;
+    if (s->n_ritems > 0) SC(dalloc(&s->xpart, ritems.size() * HK_WAVE));
     SC(dalloc(&s->lam_static, p->npad));
     SC(dalloc(&s->Lam_static, 1));
     SC(dalloc(&s->a, s->mpad));
