@@ -661,3 +661,96 @@ def test_infinite_row_pass_constants(gpu, n, t_end, change):
             g = out["grad_theta"].cpu().numpy()
             assert np.max(np.abs(g - ref["grad_theta"]) / np.maximum(ref["grad_theta"] + 2 * a, 1e-300)) < 1e-6
     plan.close()
+
+
+def _hyper_term_magnitudes(es):
+    """Per hyperparameter the sums over events of the magnitudes, without
+    cancellation, of the terms of log lambda's first derivative and of its second
+    (with twice the square of the first)."""
+    mu0, tx, tt, th0, om, hb = [float(v) for v in es.hyper]
+    cb, ce = oracle.constants(es.hyper)
+    B0, B1, B2, B11, B22, X0, X1, X2, X11, X22 = oracle.row_sums(es.t, es.x, es.y, es.theta, es.hyper).T
+    lam = np.maximum(cb * B0 + ce * X0, 1e-300)
+    d1 = np.array([cb * B0 / mu0, cb * (2 * B0 / tx + B1 / tx ** 3), cb * (B0 / tt + B2 / tt ** 3), ce * X0 / th0,
+                   ce * (X0 / om + X1), ce * (2 * X0 / hb + X2 / hb ** 3)]) / lam
+    d2 = np.array([0.0 * B0, cb * (6 * B0 / tx ** 2 + 7 * B1 / tx ** 4 + B11 / tx ** 6),
+                   cb * (2 * B0 / tt ** 2 + 5 * B2 / tt ** 4 + B22 / tt ** 6), 0.0 * X0, ce * (X11 + 2 * X1 / om),
+                   ce * (6 * X0 / hb ** 2 + 7 * X2 / hb ** 4 + X22 / hb ** 6)]) / lam
+    return d1.sum(1), (d2 + 2 * d1 ** 2).sum(1)
+
+
+@pytest.mark.parametrize("dense", [True, False])
+@pytest.mark.parametrize("n", [200, 1056, 3072, 3073, 3840, 3841, 5120, 5121, 11264, 11265])
+def test_small_set_forms_dense_and_sparse_match_oracle(gpu, n, dense):
+    """The sizes where the small sets' forms begin and end (split row pass up to
+    3,072 events with the Hessian and 3,840 without, columns that finish themselves
+    up to 5,120, rates staged by the row pass up to 11,264), on sets whose 64-event
+    chunks take the row pass's fast form (at most 40 / omega and tau_t / 2 in time)
+    and on sets whose chunks take its precise form, each set checked for that: the
+    log-likelihood alone, each combination of derivatives, with and without the
+    cutoff.  The bounds of the other parity tests; a hyperparameter derivative is a sum
+    over events of ratios of pair sums (64 FP32 additions per chunk, 4e-6 relative at
+    most) to lambda (2e-6), held to 8e-6 of its terms' magnitudes."""
+    import torch
+
+    from paper_2103_03348_amd.hawkes import Plan
+
+    es = synth.small(n, seed=900 + n, t_end=(0.03 if dense else 0.5) * n, ties=n // 20)
+    t = np.sort(es.t)
+    spans = [t[min(c + 64, n) - 1] - t[c] for c in range(0, n, 64) if c + 1 < n]
+    fast = np.mean(np.array(spans) <= min(40.0 / es.hyper[4], 0.5 * es.hyper[2]))
+    assert fast >= 0.9 if dense else fast == 0.0
+    ref = oracle.evaluate_es(es)
+    a = es.hyper[3] * (1.0 - np.exp(-es.hyper[4] * (es.t.max() - es.t)))
+    mag = _hyper_term_magnitudes(es)
+    plan = Plan.from_numpy(es.t, es.x, es.y, es.t0)
+    th = torch.as_tensor(es.theta, device="cuda:0")
+    for cutoff in (False, True):
+        plan.set_cutoff(cutoff)
+        for col in (False, True):
+            for grad, hess in ((False, False), (True, False), (True, True)):
+                out = plan.eval(th, es.hyper, loglik=True, grad_theta=col, grad_hyper=grad, negH_theta=col and hess,
+                                negH_hyper=hess)
+                assert plan.status() == 0
+                assert abs(float(out["loglik"].item()) - ref["loglik"]) <= 2e-6 * n
+                lam = plan.lam().cpu().numpy()
+                assert np.all(np.abs(lam - ref["lam"]) <= 2e-6 * ref["lam"])
+                if col:
+                    g = out["grad_theta"].cpu().numpy()
+                    assert np.max(np.abs(g - ref["grad_theta"]) / np.maximum(ref["grad_theta"] + 2 * a, 1e-300)) < 1e-6
+                if col and hess:
+                    h = out["negH_theta"].cpu().numpy()
+                    assert np.max(np.abs(h - ref["negH_theta"]) / (ref["negH_theta"] + 1e-30)) < 1e-6
+                if grad:
+                    assert np.all(np.abs(out["grad_hyper"].cpu().numpy() - ref["grad_hyper"]) <= 8e-6 * mag[0])
+                if hess:
+                    assert np.all(np.abs(out["negH_hyper"].cpu().numpy() - ref["negH_hyper"]) <= 8e-6 * mag[1])
+    plan.close()
+
+
+@pytest.mark.parametrize("n,t_end", [(1, 10.0), (1056, 4.0e5)])
+def test_events_without_intensity(gpu, n, t_end):
+    """A single event, and a set so sparse that some events have no intensity in
+    FP64 either: the log-likelihood is -inf and reported, every lambda is the
+    oracle's (zeros included), and so is Eq. 4 wherever the oracle has a finite
+    value (no later event without intensity)."""
+    import torch
+
+    from paper_2103_03348_amd.hawkes import Plan
+
+    es = synth.small(n, seed=900 + n, t_end=t_end, ties=n // 20)
+    ref = oracle.evaluate_es(es)
+    assert ref["loglik"] == -np.inf and (ref["lam"] == 0.0).any()
+    a = es.hyper[3] * (1.0 - np.exp(-es.hyper[4] * (es.t.max() - es.t)))
+    plan = Plan.from_numpy(es.t, es.x, es.y, es.t0)
+    out = plan.eval(torch.as_tensor(es.theta, device="cuda:0"), es.hyper, loglik=True, grad_theta=True)
+    assert plan.status() != 0
+    assert float(out["loglik"].item()) == -np.inf
+    lam = plan.lam().cpu().numpy()
+    assert np.all(np.abs(lam - ref["lam"]) <= 2e-6 * ref["lam"])
+    ok = np.isfinite(ref["grad_theta"])
+    assert ok.any()
+    g = out["grad_theta"].cpu().numpy()[ok]
+    gr = ref["grad_theta"][ok]
+    assert np.max(np.abs(g - gr) / np.maximum(gr + 2 * a[ok], 1e-300)) < 1e-6
+    plan.close()
