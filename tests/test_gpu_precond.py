@@ -423,3 +423,42 @@ def test_features_of_long_windows_match_oracle(gpu, n, spread):
     torch.cuda.synchronize()
     ref = ofeat.features(es.t, es.x, es.y, es.subset, z, es.hyper, es.t0, gx0, gy0)
     np.testing.assert_allclose(feat.cpu().numpy(), ref, rtol=1e-6, atol=1e-6)
+
+
+@pytest.mark.parametrize("steps,batch", [(1, 100), (150, 100), (150, 5000)])
+def test_training_steps_one_by_one(gpu, steps, batch):
+    """train() draws its batch rows in blocks, through two host buffers in turn: the
+    weights and moments are those, bit for bit, of its steps driven one by one on
+    rows drawn at once and copied synchronously (blocks of 4, 4, 8, 16, 32, 32, ...
+    steps; a batch larger than the data is cut to it)."""
+    import torch
+
+    from paper_2103_03348_amd import _lib
+    from paper_2103_03348_amd.preconditioner import LearnedPreconditioner
+    from paper_2103_03348_amd.sampler import HmcSampler
+
+    es = synth.small(300, seed=12, all_free=False)
+    plan = _plan_with_subset(es)
+    smp = HmcSampler(plan, _t(es.theta), _t(es.subset), es.hyper)
+    rng = np.random.default_rng(9)
+    n = 777
+    X, T = _t(rng.standard_normal((n, 12)).astype(np.float32)), _t(rng.standard_normal(n).astype(np.float32))
+    t, xy = _t(es.t), _t(np.stack([es.x, es.y], 1))
+    a, b = (LearnedPreconditioner(smp, t, xy, seed=2) for _ in range(2))
+    for seed in (3, 4):  # a second call goes on from the first
+        a.train(X, T, steps=steps, batch=batch, lr=1e-3, seed=seed)
+        B = min(batch, n)
+        rows = _t(np.random.default_rng(seed).integers(0, n, size=(steps, B)).astype(np.int32))
+        work = torch.empty(int(_lib.lib().hawkes_mlp_workspace_floats(B)), dtype=torch.float32, device="cuda:0")
+        grad = torch.empty(b.np, dtype=torch.float64, device="cuda:0")
+        for it in range(steps):
+            b.step_no += 1
+            _lib.check(_lib.lib().hawkes_mlp_train_step(
+                _lib.ptr(b.params), _lib.ptr(b.adam_m), _lib.ptr(b.adam_v), b.step_no, ctypes.c_float(1e-3),
+                _lib.ptr(X), n, _lib.ptr(rows[it]), _lib.ptr(T), B, _lib.ptr(work), _lib.ptr(grad), None, None,
+                _lib.stream_handle()), "train_step")
+        torch.cuda.synchronize()
+        assert a.step_no == b.step_no
+        for u, v in ((a.params, b.params), (a.adam_m, b.adam_m), (a.adam_v, b.adam_v)):
+            assert torch.equal(u, v)
+    plan.close()
