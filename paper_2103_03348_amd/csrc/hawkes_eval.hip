@@ -93,22 +93,7 @@ __device__ __forceinline__ float rot_next(float v) {
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x134, 0xf, 0xf, true));
 }
 
-__device__ __forceinline__ double rot_next_d(double v) {
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x134, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x134, 0xf, 0xf, true);
-    return __hiloint2double(hi, lo);
-}
-
 __device__ __forceinline__ float fexp2(float x) { return __builtin_amdgcn_exp2f(x); }
-
-// Knuth's TwoSum: (hi, lo) += v with the rounding error of the high add kept.
-__device__ __forceinline__ void two_sum_acc(float &hi, float &lo, float v) {
-    float s = hi + v;
-    float bp = s - hi;
-    float err = (hi - (s - bp)) + (v - bp);
-    hi = s;
-    lo += err;
-}
 
 // ------------------------------------------------------------------------------------
 // A chunk's staged rates: theta_v_j = theta_j exp(omega (t_j - T_c)) with T_c the
@@ -1451,7 +1436,6 @@ extern "C" hawkes_status hawkes_eval(hawkes_plan p, const hawkes_hyper *hyper, c
     // only need lambda), first moments for the hyperparameter gradient, second
     // moments for its Hessian diagonal
     const int mode = d_negH_hyper ? HK_MODE_HESS : (d_grad_hyper ? HK_MODE_GRAD : HK_MODE_LOGLIK);
-    const int64_t npad = p->npad;
 
     hk_prof_mark(p, HK_PROF_EVAL, true, stream);
     if (!p->row_single || kc.floor) launch_tfac(p, kc, d_theta, nullptr, stream);

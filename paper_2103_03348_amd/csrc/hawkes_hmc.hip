@@ -154,14 +154,6 @@ constexpr int kSubUnroll = HK_SUB_UNROLL;
 
 __device__ __forceinline__ float fexp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-__device__ __forceinline__ void two_sum_acc(float &hi, float &lo, float v) {
-    float s = hi + v;
-    float bp = s - hi;
-    float err = (hi - (s - bp)) + (v - bp);
-    hi = s;
-    lo += err;
-}
-
 __global__ void k_invperm(const int *__restrict__ perm, int64_t n, int *__restrict__ inv) {
     int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i < n) inv[perm[i]] = (int)i;

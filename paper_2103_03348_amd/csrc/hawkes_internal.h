@@ -115,7 +115,6 @@ struct hawkes_plan_s {
     int *row_item0;           // [ntiles] first item of each row tile (device)
     int *row_nseg;            // [ntiles] items per row tile (device)
     int64_t *colpart_off;     // [ntiles] offset of tile I's column partials (device)
-    int64_t colpart_len;
     // column pass schedule
     int n_col_items;
     hk_item *col_items;
@@ -135,8 +134,7 @@ struct hawkes_plan_s {
     double *lam;              // [npad] lambda_i, sorted
     double *a;                // [npad] theta0 (1 - exp(-omega (T1 - t_i)))
     double *colG;             // [n_col_items][2][HK_TILE]: G and H of each column piece
-    int nfin_blocks;          // npad / 256 (subset-path reductions)
-    double *blockpart;        // [nchunks][HK_NSUM] per-block partial sums
+    double *blockpart;        // [HK_NSUM][nchunks] per-chunk partial sums (subset path: [nchunks])
     int *status;              // sticky device status bits
     hipStream_t last_stream;
     int64_t epoch;            // intensity evaluations so far (host counter)

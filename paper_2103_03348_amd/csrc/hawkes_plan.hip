@@ -332,7 +332,6 @@ extern "C" hawkes_status hawkes_plan_create(hawkes_plan *out, int64_t n, const d
         cpoff[I] = cpl;
         cpl += (int64_t)HK_NCOL * (I + 1) * HK_TILE;
     }
-    p->colpart_len = cpl;
     p->n_row_items = (int)rs.items.size();
     p->n_row_blocks = (int)rs.block0.size() - 1;
     p->row_single = rs.single;
@@ -369,7 +368,6 @@ extern "C" hawkes_status hawkes_plan_create(hawkes_plan *out, int64_t n, const d
     PC(dalloc(&p->lam, npad));
     PC(dalloc(&p->a, npad));
     PC(dalloc(&p->colG, (size_t)p->n_col_items * 2 * HK_TILE));
-    p->nfin_blocks = (int)(npad / 256);
     PC(dalloc(&p->blockpart, (size_t)p->nchunks * HK_NSUM));
     PC(dalloc(&p->status, 1));
     PC(hipMemsetAsync(p->status, 0, sizeof(int), stream));

@@ -27,10 +27,10 @@
 //
 // The v, alpha, s depend on the tree only and are formed once on the host in
 // FP64.  On the device the prior is two dense steps over the tree cut into
-// subtrees (hawkes_tree.h), or, for a tree that needs too many of them, one block
-// walks the levels of the tree (nodes grouped by height, so that all children of
-// a level are done before it), one thread per node of a level, with a barrier
-// between levels.
+// subtrees (hawkes_tree.h); for a tree that needs too many of them, and alone for a
+// shallow one, one block walks the levels of the tree (nodes grouped by height, so
+// that all children of a level are done before it), one thread per node of a level,
+// with a barrier between levels.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <string.h>
