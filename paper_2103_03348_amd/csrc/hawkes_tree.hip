@@ -64,11 +64,12 @@ struct hk_tree {
 namespace {
 
 constexpr int TREE_THREADS = 1024;
-// hawkes_tree_prior alone takes the level walk for a tree of at most this many levels:
-// one launch of some 10 dependent levels against the dense steps' two (a balanced tree
-// of 400 / 1,600 / 3,000 / 6,000 tips, 9 / 11 / 12 / 13 levels, walk 12.1 / 14.9 / 17.4 /
-// 23.2 us, dense 15.6 / 16.2 / 16.4 / 17.6; a random one of 128 / 800, 15 / 23 levels,
-// 14.8 / 21.3 and 14.0 / 15.4).  In hmc_step the dense steps cost no launch.
+// hawkes_tree_prior alone takes the level walk for a tree of at most this many levels
+// (two more where a level is one node per thread): one launch of some 10 dependent
+// levels against the dense steps' two (a balanced tree of 400 / 1,600 / 3,000 / 6,000
+// tips, 9 / 11 / 12 / 13 levels, walk 12.1 / 14.9 / 17.4 / 23.2 us, dense 15.6 / 16.2 /
+// 16.4 / 17.6; a random one of 64 / 128 / 800, 13 / 15 / 23 levels, walk 12.4 / 14.8 /
+// 21.3, dense 13.4 / 14.0 / 15.4).  In hmc_step the dense steps cost no launch.
 constexpr int TREE_WALK_LEVELS = 11;
 
 __global__ __launch_bounds__(TREE_THREADS) void k_tree_prior(const double *__restrict__ z, int64_t m,
@@ -487,7 +488,8 @@ extern "C" hawkes_status hawkes_tree_prior(hawkes_plan p, const double *d_z, dou
     if (!t) return HAWKES_E_UNSUPPORTED;
     p->last_stream = stream;
     // the walk leaves the adjoints of the tips in mv[0..m), the dense steps V^{-1} z there
-    const TreeDense *td = t->levels > TREE_WALK_LEVELS ? hk_tree_dense(p) : nullptr;
+    const bool walk = t->levels <= TREE_WALK_LEVELS + (t->m <= TREE_THREADS ? 2 : 0);
+    const TreeDense *td = walk ? nullptr : hk_tree_dense(p);
     if (td) {
         hipLaunchKernelGGL(k_tree_low, dim3(td->R), dim3(HK_WAVE), 0, stream, *td, d_z);
         hipLaunchKernelGGL(k_tree_top, dim3(hk_tree_top_blocks(td->R)), dim3(HK_TREE_TOP_THREADS), 0, stream, *td,
