@@ -24,7 +24,7 @@
 // under this prior 1,117 us with the level walk, 638 us with these (619 us under
 // the independent prior).
 #define HK_TREE_SUB 64           // tips per subtree: one wavefront
-#define HK_TREE_MAX_ROOTS 1024   // more subtrees (a tree of over ~15,000 tips) take the level walk
+#define HK_TREE_MAX_ROOTS 1024   // more subtrees (a random tree of over some 33,000 tips) take the level walk
 
 struct TreeDense {
     int R;                // subtrees (0: none)

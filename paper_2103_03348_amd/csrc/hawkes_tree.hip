@@ -422,8 +422,8 @@ static hawkes_status set_tree(hawkes_plan p, int64_t n_nodes, const int64_t *par
     const size_t RR = (size_t)R, host_bytes = (host.size() + 7) / 8 * 8;
     const size_t n_dev = 2 * N + (R > 0 ? n_mat + 2 * M + RR * RR + 4 * RR : 0);
 
-    hk_tree_free(p);
     hk_tree *t = new hk_tree();
+    hk_tree_free(p);
     p->tree = t;
     t->dense = TreeDense{};
     t->m = m;
